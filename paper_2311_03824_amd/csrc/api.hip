@@ -186,6 +186,7 @@ struct altgdmin_handle {
   float* H;
   double* colrr;
   int* colflags;
+  float* colbound;
   float* gpart;
   int KS;
   float* U;
@@ -273,6 +274,7 @@ size_t carve(altgdmin_handle* h, void* base) {
   h->Tpow = c.take<float>(q * r);
   h->rlog_len = h->par.t_max > 0 ? h->par.t_max : 1;
   h->rlog = c.take<double>(h->rlog_len);
+  h->colbound = c.take<float>(q);
   if (p.r == 0) h->rank_ws = c.take<unsigned char>(rank_scratch(nullptr, rank_shape(p.n, p.q, p.m)).bytes);
   return (c.off + kAlign - 1) / kAlign * kAlign;
 }
@@ -396,6 +398,30 @@ ColArgs col_args(const altgdmin_handle* h) {
   a.H = h->H; a.Bt = h->Bt; a.rr = h->colrr; a.flags = h->colflags;
   a.seed = p.a_seed; a.table = p.normal_table;
   a.waves = h->col_waves;
+  return a;
+}
+
+// The column kernel of a GDmin iteration: projection by the P_k, tau IHT steps from
+// the current support (with the column norm bound of this iteration's A_k U), the LS
+// and gradient tail.
+ColArgs gd_col_args(const altgdmin_handle* h) {
+  ColArgs a = col_args(h);
+  a.tau = h->par.tau; a.project = 1; a.has_support = 1; a.tail = TAIL_LSGRAD;
+  a.bound = h->colbound;
+  return a;
+}
+
+// A_k U of a GDmin iteration from U.
+AUArgs gd_au_args(const altgdmin_handle* h, const float* U) {
+  const altgdmin_problem& p = h->prob;
+  AUArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.n = p.n; a.q = p.q; a.m = p.m; a.r = p.r;
+  a.A = p.A; a.Alo = p.A_lo; a.lda = p.lda; a.sA = p.a_stride_k;
+  a.U = U; a.P = h->P; a.Ginv = h->Ginv; a.flags = h->colflags;
+  a.seed = p.a_seed; a.table = p.normal_table;
+  a.waves = au_waves(p);
+  a.bound = h->colbound;
   return a;
 }
 
@@ -531,17 +557,12 @@ int autotune(altgdmin_handle* h, hipStream_t st) {
   // U, then the column kernel as in a GDmin iteration; every buffer they write
   // is rewritten by the initialisation or the first iteration
   HIPCHK(launch_fill_basis(h->Utmp, p.n, p.r, st));
-  AUArgs au;
-  std::memset(&au, 0, sizeof(au));
-  au.n = p.n; au.q = p.q; au.m = p.m; au.r = p.r;
-  au.A = p.A; au.Alo = p.A_lo; au.lda = p.lda; au.sA = p.a_stride_k;
-  au.U = h->Utmp; au.P = h->P; au.Ginv = h->Ginv; au.flags = h->colflags;
-  au.waves = au_waves(h->prob);
+  const AUArgs au = gd_au_args(h, h->Utmp);
   // the column kernel in its GDmin configuration (projection by the P_k, G_k^{-1}
   // the A_k U runs just wrote, tau IHT iterations, the LS / gradient tail), from
   // an empty support
-  ColArgs ca = col_args(h);
-  ca.tau = h->par.tau; ca.project = 1; ca.has_support = 0; ca.tail = TAIL_LSGRAD;
+  ColArgs ca = gd_col_args(h);
+  ca.has_support = 0;
   EventPair ev;
   HIPCHK(ev.create());
   hipEvent_t e0 = ev.e[0], e1 = ev.e[1];
@@ -666,15 +687,8 @@ int enqueue_iteration(altgdmin_handle* h, hipStream_t st) {
     return ALTGDMIN_OK;
   }
   const altgdmin_problem& p = h->prob;
-  AUArgs au;
-  au.n = p.n; au.q = p.q; au.m = p.m; au.r = p.r;
-  au.A = p.A; au.Alo = p.A_lo; au.lda = p.lda; au.sA = p.a_stride_k;
-  au.U = h->U; au.P = h->P; au.Ginv = h->Ginv; au.flags = h->colflags;
-  au.gate = nullptr; au.gate_want = 0;
-  au.seed = p.a_seed; au.table = p.normal_table;
-  au.waves = au_waves(h->prob);
-  ColArgs ca = col_args(h);
-  ca.tau = h->par.tau; ca.project = 1; ca.has_support = 1; ca.tail = TAIL_LSGRAD;
+  AUArgs au = gd_au_args(h, h->U);
+  ColArgs ca = gd_col_args(h);
   if (h->hi_phase) {
     // both variants are in the graph; the phase flag in the control block picks one
     au.gate = &h->ctl->phase; ca.gate = &h->ctl->phase;
@@ -933,15 +947,8 @@ int altgdmin_profile_iteration(altgdmin_handle* h, int32_t iters, void* stream, 
     if (e != hipSuccess) rc = fail(ALTGDMIN_EHIP, std::string("profile: ") + hipGetErrorString(e));
   }
   for (int it = 0; it < iters && rc == ALTGDMIN_OK && h->fmt != FMT_PFOURIER; ++it) {
-    AUArgs au;
-    au.n = p.n; au.q = p.q; au.m = p.m; au.r = p.r;
-    au.A = p.A; au.Alo = p.A_lo; au.lda = p.lda; au.sA = p.a_stride_k;
-    au.U = h->U; au.P = h->P; au.Ginv = h->Ginv; au.flags = h->colflags;
-    au.gate = nullptr; au.gate_want = 0;
-    au.seed = p.a_seed; au.table = p.normal_table;
-    au.waves = au_waves(h->prob);
-    ColArgs ca = col_args(h);
-    ca.tau = h->par.tau; ca.project = 1; ca.has_support = 1; ca.tail = TAIL_LSGRAD;
+    const AUArgs au = gd_au_args(h, h->U);
+    const ColArgs ca = gd_col_args(h);
     hipError_t e = hipEventRecord(ev[0], st);
     if (e == hipSuccess) e = au_launch(h, h->fmt, au, st);
     if (e == hipSuccess) e = hipEventRecord(ev[1], st);
@@ -1256,19 +1263,12 @@ int plan_group(altgdmin_handle* const* hs, int count, GroupPlan& g) {
     if (h->hi_phase) return fail(ALTGDMIN_EINVAL, "a BF16X2 problem with a hi-only phase cannot be batched");
     if (h->fmt == FMT_PFOURIER) return fail(ALTGDMIN_EINVAL, "batched stepping takes the real A formats only");
     const altgdmin_problem& p = h->prob;
-    AUArgs au;
-    std::memset(&au, 0, sizeof(au));
-    au.n = p.n; au.q = p.q; au.m = p.m; au.r = p.r;
-    au.A = p.A; au.Alo = p.A_lo; au.lda = p.lda; au.sA = p.a_stride_k;
-    au.U = h->U; au.P = h->P; au.Ginv = h->Ginv; au.flags = h->colflags;
-    au.seed = p.a_seed; au.table = p.normal_table;
-    au.waves = au_waves(h->prob);
+    AUArgs au = gd_au_args(h, h->U);
     // with tol_resid > 0 a problem whose residual reached it is frozen (every kernel skips it)
     const int* done = h->par.tol_resid > 0.0 ? &h->ctl->done : nullptr;
     au.gate = done; au.gate_want = 0;
     g.au.push_back(au);
-    ColArgs ca = col_args(h);
-    ca.tau = h->par.tau; ca.project = 1; ca.has_support = 1; ca.tail = TAIL_LSGRAD;
+    ColArgs ca = gd_col_args(h);
     ca.gate = done; ca.gate_want = 0;
     g.col.push_back(ca);
     GradArgs ga;
@@ -1441,6 +1441,7 @@ int altgdmin_op_au(const altgdmin_problem* prob, const float* U, float* P, doubl
   if (!U || !P || !Lc) return fail(ALTGDMIN_EINVAL, "null U/P/Ginv");
   NEED_STREAM(stream);
   AUArgs au;
+  std::memset(&au, 0, sizeof(au));
   au.n = prob->n; au.q = prob->q; au.m = prob->m; au.r = prob->r;
   au.A = prob->A; au.Alo = prob->A_lo; au.lda = prob->lda; au.sA = prob->a_stride_k;
   au.U = U; au.P = P; au.Ginv = Lc; au.flags = flags;

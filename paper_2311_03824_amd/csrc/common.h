@@ -67,6 +67,8 @@ struct ColArgs {
   unsigned long long seed;  // Philox form: key of A
   const float* table;       // Philox form: normal table (kNormalTable FP32)
   int waves;                // waves of the column workgroup: 4 (also for 0), 8 or 16
+  const float* bound;       // optional q: an upper bound of every ||(A_k)_j|| (A_k U kernel); lets a step that
+                            // provably keeps its support read the support columns alone
 };
 
 struct AUArgs {
@@ -83,6 +85,7 @@ struct AUArgs {
   unsigned long long seed;  // Philox form: key of A
   const float* table;       // Philox form: normal table (kNormalTable FP32)
   int waves;                // waves per workgroup: 8 (at most 512 columns) or 4 (0 reads as 4)
+  float* bound;             // optional q: receives an upper bound of the column norms of A_k
 };
 
 // ---------------------------------------------------------------- wave reductions
@@ -180,6 +183,11 @@ __device__ __forceinline__ uint2 ld_a(const uint16_t* p) {
 
 template <int FMT, int POL = POL_STREAM> struct ALoader;
 
+// The column norm bound is raised by 1 %: it then also covers the FP32 rounding of
+// the squares it is summed from and of the products A_j^T u it is used to bound
+// (worst case m 2^-24 of ||A_j|| ||u||, 6e-5 at m = 1024).
+constexpr float kBoundSlack = 1.01f;
+
 template <int POL> struct ALoader<FMT_F32, POL> {
   const float* base;
   long long lda;
@@ -193,6 +201,9 @@ template <int POL> struct ALoader<FMT_F32, POL> {
   typedef float4 raw_t;
   __device__ __forceinline__ raw_t fetch(int j, int ch) const { return ld_a<POL>(base + (long long)j * lda + 4 * ch); }
   __device__ static __forceinline__ float4 expand(raw_t v) { return v; }
+  // magnitude() bounds, entry by entry, the magnitudes of every view of A_k that a
+  // column kernel of this form streams (for the column norm bound of the A_k U kernel).
+  __device__ static __forceinline__ float4 magnitude(raw_t v) { return v; }
   __device__ __forceinline__ float4 load(int j, int ch) const { return fetch(j, ch); }
 };
 
@@ -221,6 +232,13 @@ template <int POL> struct ALoader<FMT_BF16X2, POL> {
     o.w = bf16_to_f32(v.y >> 16) + bf16_to_f32(v.w >> 16);
     return o;
   }
+  // |hi| + |lo| bounds both |hi + lo| and the |hi| that the mixed form streams
+  __device__ static __forceinline__ float4 magnitude(raw_t v) {
+    return make_float4(fabsf(bf16_to_f32(v.x & 0xffffu)) + fabsf(bf16_to_f32(v.z & 0xffffu)),
+                       fabsf(bf16_to_f32(v.x >> 16)) + fabsf(bf16_to_f32(v.z >> 16)),
+                       fabsf(bf16_to_f32(v.y & 0xffffu)) + fabsf(bf16_to_f32(v.w & 0xffffu)),
+                       fabsf(bf16_to_f32(v.y >> 16)) + fabsf(bf16_to_f32(v.w >> 16)));
+  }
   __device__ __forceinline__ float4 load(int j, int ch) const { return expand(fetch(j, ch)); }
 };
 
@@ -237,6 +255,7 @@ template <int POL> struct ALoader<FMT_BF16HI, POL> {
     return make_float4(bf16_to_f32(h.x & 0xffffu), bf16_to_f32(h.x >> 16),
                        bf16_to_f32(h.y & 0xffffu), bf16_to_f32(h.y >> 16));
   }
+  __device__ static __forceinline__ float4 magnitude(raw_t h) { return expand(h); }
   __device__ __forceinline__ float4 load(int j, int ch) const { return expand(fetch(j, ch)); }
 };
 
@@ -294,6 +313,7 @@ template <int POL> struct ALoader<FMT_PHILOX, POL> {   // generated, not loaded:
                        word_to_normal(c[3], tab));
   }
   __device__ static __forceinline__ float4 expand(raw_t v) { return v; }
+  __device__ static __forceinline__ float4 magnitude(raw_t v) { return v; }
   __device__ __forceinline__ float4 load(int j, int ch) const { return fetch(j, ch); }
 };
 

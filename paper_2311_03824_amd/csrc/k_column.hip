@@ -339,6 +339,86 @@ __device__ __forceinline__ void fused_pass(const ALoader<FMT, POL>& L, const Lan
   if (g < groups) consume(wave + g * step, a0);
 }
 
+// The T part of a column pass: gT[t] = A_j^T u, j = Ti[t], for this wave's support
+// entries, wacc += gT[t] A_j and gT2 += gT[t]^2 over them.  list[0..cnt) holds the
+// wave's entries t, the ones with j % W == wave in ascending order: the columns,
+// and the order, that fused_pass gives this wave, so every sum has the same bits
+// as there.
+template <int FMT, int NC, int W, int POL>
+__device__ __forceinline__ void support_pass(const ALoader<FMT, POL>& L, const Lane<NC>& ln, const float4 (&u)[NC],
+                                             const int* Ti, const int* list, int cnt, float* gT, float4 (&wacc)[NC],
+                                             double& gT2, int lane) {
+  constexpr int JT = NC == 1 ? 4 : (NC == 2 ? 2 : 1);   // columns per group; two groups in flight
+  typedef typename ALoader<FMT, POL>::raw_t raw_t;
+  if (cnt <= 0) return;
+  auto load = [&](int e0, raw_t (&ar)[JT][NC]) {
+#pragma unroll
+    for (int ju = 0; ju < JT; ++ju) {
+      const int e = e0 + ju < cnt ? e0 + ju : cnt - 1;
+      const int j = __builtin_amdgcn_readfirstlane(Ti[list[e]]);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) ar[ju][c] = L.fetch(j, ln.chc[c]);
+    }
+  };
+  auto consume = [&](int e0, const raw_t (&ar)[JT][NC]) {
+    float4 av[JT][NC];
+    float d[JT];
+#pragma unroll
+    for (int ju = 0; ju < JT; ++ju) {
+      av[ju][0] = ALoader<FMT, POL>::expand(ar[ju][0]);
+      float s = dot4(av[ju][0], u[0]);
+#pragma unroll
+      for (int c = 1; c < NC; ++c) {
+        av[ju][c] = ALoader<FMT, POL>::expand(ar[ju][c]);
+        s += dot4(av[ju][c], u[c]);
+      }
+      d[ju] = s;
+    }
+    const float tot = col_totals<JT>(d, lane);
+    if (lane < JT && e0 + lane < cnt) gT[list[e0 + lane]] = tot;
+#pragma unroll
+    for (int ju = 0; ju < JT; ++ju) {
+      if (e0 + ju < cnt) {
+        const float dj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(tot), ju));
+#pragma unroll
+        for (int c = 0; c < NC; ++c) wacc[c] = axpy4(dj, mask_rows(av[ju][c], ln.nv[c]), wacc[c]);
+        gT2 = fma((double)dj, (double)dj, gT2);
+      }
+    }
+  };
+  const int groups = (cnt + JT - 1) / JT;   // as in fused_pass: loads without a condition, one exit
+  raw_t a0[JT][NC], a1[JT][NC];
+  load(0, a0);
+  int g = 0;
+  for (; g + 1 < groups; g += 2) {
+    load((g + 1) * JT, a1);
+    consume(g * JT, a0);
+    load((g + 2) * JT, a0);
+    consume((g + 1) * JT, a1);
+  }
+  if (g < groups) consume(g * JT, a0);
+}
+
+// The support entries of wave w for support_pass: start and count of its segment of
+// `list` (a permutation of 0..rho-1 by j % W, ascending within a wave), which this
+// wave writes.  No barrier: a wave reads back its own segment only.
+template <int W>
+__device__ __forceinline__ int2 support_list(const int* Ti, int rho, int* list, int lane, int wave) {
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  int start = 0, cnt = 0;
+  for (int t0 = 0; t0 < rho; t0 += 64) {
+    const int w = t0 + lane < rho ? (Ti[t0 + lane] & (W - 1)) : W;
+    start += __popcll(__ballot(w < wave));
+  }
+  for (int t0 = 0; t0 < rho; t0 += 64) {
+    const bool mine = t0 + lane < rho && (Ti[t0 + lane] & (W - 1)) == wave;
+    const unsigned long long b = __ballot(mine);
+    if (mine) list[start + cnt + __popcll(b & lt)] = t0 + lane;
+    cnt += __popcll(b);
+  }
+  return make_int2(start, cnt);
+}
+
 // HardThreshold of Alg. 2 on vals[0..n) (LDS): the rho entries of largest
 // |v|, lower index first on ties, written ascending to idx/val (LDS).
 // Exact: the rho-th largest magnitude T is found by a radix select on the FP32
@@ -482,12 +562,17 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   const int nwords = (n + 31) >> 5;
 
   constexpr int GF = gather_fmt(FMT), SF = stream_fmt(FMT);
-  ALoader<GF, POL> L(a, k);    // A_k s_k: exact
-  ALoader<SF, POL> Ls(a, k);   // A_k^T u and the step length: the streaming view
+  // The support columns are read several times per launch (once per gather and per
+  // step on T): ordinary loads, which the caches keep (rho columns of each A_k; 0.402
+  // -> 0.360 ms for a settled iteration at n = q = 1000 against non-temporal ones).
+  ALoader<GF, POL_CACHED> L(a, k);    // A_k s_k: exact
+  ALoader<SF, POL_CACHED> Lt(a, k);   // the streaming view of the support columns
+  ALoader<SF, POL> Ls(a, k);          // A_k^T u and the step length: the streaming view
   if constexpr (FMT == FMT_PHILOX) {
     float* tab = reinterpret_cast<float*>(smem + lay.tab);
     for (int t = tid; t < kNormalTable; t += kT) tab[t] = a.table[t];
     L.tab = tab;   // read only after the barrier that ends the LDS set-up below
+    Lt.tab = tab;
     Ls.tab = tab;
   }
   const Lane<NC> ln(lane, m);
@@ -552,6 +637,27 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   bool hasT = !invalid && vote > 0.0;
   int nan_seen = 0;
 
+  // Steps that provably keep their support.  Off the support T, HardThreshold sees
+  // |mu g_j| <= mu ||A_j|| ||u|| (Cauchy-Schwarz); when mu times the bound of the
+  // column norms times ||u|| is below every magnitude on T, T is kept whatever the
+  // g_j off it are, and the step needs g on T alone: rho columns of A_k instead of
+  // n.  That holds from the moment the error of s is below its smallest entry, so
+  // most iterations of a solve read A_k twice (A_k U, the tail) instead of five
+  // times.  The values on T come from the same sums in the same order as in a full
+  // pass (support_pass), so the result is the same bit for bit; a step whose test
+  // fails, or without a bound, takes the full pass.  The full passes were bound by
+  // HBM (96 % of a plain read): a settled iteration's k_col at n = q = 1000, m = 400,
+  // r = 10, rho = 50 went from 0.99 to 0.36 ms in FP32 and from 0.61 to 0.27 in the
+  // mixed form, and at q = 125 from 0.173 to 0.105.  Above rho = n / 4 the support
+  // columns are no longer a small part of a pass, and their list needs 2 rho words
+  // of g's LDS.
+  const float bnd = a.bound && a.project && 4 * rho <= n ? a.bound[k] : 0.f;
+  const bool screen = bnd > 0.f && isfinite(bnd);
+  int* list = reinterpret_cast<int*>(gl);   // rho entries, then the rho values of g on T (2 rho <= n)
+  float* gT = gl + rho;
+  bool have_list = false;
+  int2 seg = make_int2(0, 0);
+
   for (int it = 0; it < a.tau; ++it) {
     // u = Pi (A_k s - y_k)   (Pi = I in the initialisation)
     float4 v[NC];
@@ -560,30 +666,88 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     for (int c = 0; c < NC; ++c) v[c] = sub4(v[c], yv[c]);
     if (a.project) project<NC, W>(v, ln, Pl, Gi, r, lane, wave, cbuf, nullptr);
 
-    // g = A_k^T u; w = A_k g_T on the current support
-    float4 w[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) w[c] = make_float4(0.f, 0.f, 0.f, 0.f);
-    double gT2 = 0.0;
-    fused_pass<SF, NC, JU, W>(Ls, ln, v, n, gl, hasT ? inT : nullptr, w, gT2, lane, wave);
-    __syncthreads();
-    if (hasT) {
-      xwave_sum<NC, W>(w, ln, wpart, mq, wave);
-      gT2 = xwave_sum_scalar<W>(gT2, redd, lane, wave);
-    } else {
-      // no support yet (s = 0): restrict to the support of HardThreshold(g, rho)
-      nan_seen += block_select<W>(gl, n, rho, Ti, Tv, hist);
-      gather<SF, NC, W>(Ls, ln, Ti, Tv, rho, w, wpart, mq, wave);
-      gT2 = 0.0;
-      for (int t = 0; t < rho; ++t) gT2 = fma((double)Tv[t], (double)Tv[t], gT2);
-    }
-    if (a.project) project<NC, W>(w, ln, Pl, Gi, r, lane, wave, cbuf, nullptr);
-    const double ww = sumsq<NC>(w);
-    const double mu = (ww > 0.0 && isfinite(ww) && isfinite(gT2)) ? gT2 / ww : 0.0;
     const bool last = (it == a.tau - 1);
+    // the test can only hold when ||u|| / bound, a lower estimate of its left side, is
+    // below the smallest magnitude of s
+    bool on_T = false;
+    double un = 0.0;
+    if (screen && hasT && !(last && a.G_out)) {
+      un = sqrt(sumsq<NC>(v));
+      unsigned smin = 0x7f800000u;
+      for (int t = lane; t < rho; t += 64) smin = min(smin, __float_as_uint(Tv[t]) & 0x7fffffffu);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) smin = min(smin, (unsigned)__shfl_xor((int)smin, o));
+      on_T = un < (double)bnd * (double)__uint_as_float(smin);
+    }
+
+    // g = A_k^T u; w = A_k g_T on the current support; mu.  A step whose test holds
+    // ends after the support columns; one whose test fails after them has its mu and
+    // takes the full pass for the rest of g.
+    double mu = 0.0;
+    bool kept = false, have_mu = false;
+    for (;;) {
+      float4 w[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) w[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+      double gT2 = 0.0;
+      if (on_T) {
+        if (!have_list) seg = support_list<W>(Ti, rho, list, lane, wave);
+        have_list = true;
+        support_pass<SF, NC, W>(Lt, ln, v, Ti, list + seg.x, seg.y, gT, w, gT2, lane);
+      } else {
+        fused_pass<SF, NC, JU, W>(Ls, ln, v, n, gl, hasT && !have_mu ? inT : nullptr, w, gT2, lane, wave);
+        have_list = false;
+        __syncthreads();
+        if (have_mu) break;
+      }
+      if (hasT) {
+        xwave_sum<NC, W>(w, ln, wpart, mq, wave);
+        gT2 = xwave_sum_scalar<W>(gT2, redd, lane, wave);
+      } else {
+        // no support yet (s = 0): restrict to the support of HardThreshold(g, rho)
+        nan_seen += block_select<W>(gl, n, rho, Ti, Tv, hist);
+        gather<SF, NC, W>(Lt, ln, Ti, Tv, rho, w, wpart, mq, wave);
+        gT2 = 0.0;
+        for (int t = 0; t < rho; ++t) gT2 = fma((double)Tv[t], (double)Tv[t], gT2);
+      }
+      if (a.project) project<NC, W>(w, ln, Pl, Gi, r, lane, wave, cbuf, nullptr);
+      const double ww = sumsq<NC>(w);
+      mu = (ww > 0.0 && isfinite(ww) && isfinite(gT2)) ? gT2 / ww : 0.0;
+      if (!on_T) break;
+      // s - mu g on T, its smallest magnitude (0 if one is NaN) against the bound off T
+      unsigned* slot = reinterpret_cast<unsigned*>(hist);
+      unsigned kmin = 0x7f800000u;
+      for (int t = tid; t < rho; t += kT) {
+        const float x = (float)fma(-mu, (double)gT[t], (double)sd[Ti[t]]);
+        const unsigned key = __float_as_uint(x) & 0x7fffffffu;
+        kmin = min(kmin, key > 0x7f800000u ? 0u : key);
+        gT[t] = x;
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) kmin = min(kmin, (unsigned)__shfl_xor((int)kmin, o));
+      if (lane == 0) slot[wave] = kmin;
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < W; ++q) kmin = min(kmin, slot[q]);
+      kept = mu * (double)bnd * un < (double)__uint_as_float(kmin);
+      if (kept) {
+        for (int t = tid; t < rho; t += kT) {   // the entries this thread wrote above
+          Tv[t] = gT[t];
+          sd[Ti[t]] = gT[t];
+        }
+        break;
+      }
+      have_mu = true;
+      on_T = false;
+      __syncthreads();   // every thread has read gT and the slots: gl takes the full gradient
+    }
+    if (last && a.mu_out && tid == 0) a.mu_out[k] = mu;
+    if (kept) {
+      __syncthreads();
+      continue;
+    }
     if (last && a.G_out)
       for (int j = tid; j < n; j += kT) a.G_out[(long long)k * n + j] = gl[j];
-    if (last && a.mu_out && tid == 0) a.mu_out[k] = mu;
     // s - mu g, then HardThreshold
     for (int j = tid; j < n; j += kT) gl[j] = (float)fma(-mu, (double)gl[j], (double)sd[j]);
     __syncthreads();
@@ -763,6 +927,15 @@ __device__ __forceinline__ void au_body(const AUArgs& a, int k, unsigned char* s
 #pragma unroll
       for (int rr = 0; rr < R; ++rr) acc[e][rr] = fmaf(get4(a4, e), u[rr], acc[e][rr]);
   };
+  // Column norm bound: the largest sum of squares of this lane's 4 rows over its
+  // columns; summed over the lanes that is at least every ||A_j||^2 (2.2 times the
+  // norm for Gaussian A at n = 1000: one reduction per workgroup instead of one
+  // per column).  A NaN in A reaches P_k, and so every use of the bound.
+  float sqmax = 0.f;
+  auto bound_col = [&](raw_t a4) {
+    const float4 b = mask_rows(ALoader<FMT, POL>::magnitude(a4), nv);
+    sqmax = fmaxf(sqmax, dot4(b, b));
+  };
   auto stage = [&](int t) {             // wave-local: the LDS accesses of one wave complete in order
     __builtin_amdgcn_wave_barrier();
     load_rows(t);
@@ -787,6 +960,7 @@ __device__ __forceinline__ void au_body(const AUArgs& a, int k, unsigned char* s
         const int tt = t + d;
         if ((tt & 63) == 0) stage(tt);
         fetch(jw + (tt + AUD) * js, buf[(d + AUD) % NB]);
+        bound_col(buf[d]);
         fma_col(ALoader<FMT, POL>::expand(buf[d]), tt & 63);
       }
     }
@@ -796,11 +970,24 @@ __device__ __forceinline__ void au_body(const AUArgs& a, int k, unsigned char* s
       if (tt < cols) {
         if ((tt & 63) == 0) stage(tt);
         if (d + AUD < NB) fetch(jw + (tt + AUD) * js, buf[d + AUD]);
+        bound_col(buf[d]);
         fma_col(ALoader<FMT, POL>::expand(buf[d]), tt & 63);
       }
     }
   }
+  float* bl = reinterpret_cast<float*>(gpart);   // W x 64 (the Gram's partial sums come later)
+  if (a.bound) bl[wave * 64 + lane] = sqmax;
   __syncthreads();   // the staged rows of U share LDS with P
+  if (a.bound && wave == 0) {
+    float s = 0.f;
+    for (int c = 0; c < nch; ++c) {
+      float mx = 0.f;
+      for (int w = 0; w < js; ++w) mx = fmaxf(mx, bl[(c * js + w) * 64 + lane]);
+      s += mx;
+    }
+    s = wave_sum(s);
+    if (lane == 0) a.bound[k] = kBoundSlack * sqrtf(s);
+  }
 
   // partial P of the waves sharing a chunk, added in column-split order.  In
   // LDS, P is column-major with row stride mp (lane-contiguous 16-byte stores);
