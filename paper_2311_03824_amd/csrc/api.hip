@@ -335,7 +335,7 @@ int validate(const altgdmin_problem* p, const altgdmin_params* par) {
   if (p->ldy < p->m) return fail(ALTGDMIN_EINVAL, "ldy must be >= m");
   if (!au_supported(p->m, re)) return fail(ALTGDMIN_ENOTBUILT, "no A_k U instantiation for this (m, r)");
   const int phx = p->a_format == ALTGDMIN_A_PHILOX;
-  if (col_lds_bytes(p->n, p->m, re, p->rho, 1, phx) > kColLdsMax || au_lds_bytes(p->m, re, phx, 8) > kMaxLds)
+  if (col_lds_accept(p->n, p->m, re, p->rho, phx) > kColLdsMax || au_lds_bytes(p->m, re, phx, 8) > kMaxLds)
     return fail(ALTGDMIN_ENOTBUILT, "problem needs more than 160 KiB of LDS per column workgroup");
   return ALTGDMIN_OK;
 }

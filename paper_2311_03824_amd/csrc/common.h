@@ -397,9 +397,15 @@ __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~size_t(
 // LDS layout of the column kernel in bytes; used by the host to size the
 // launch and by the kernel to carve its dynamic shared memory.
 constexpr size_t kPInLdsMax = 32 * 1024;   // P_k is staged in LDS up to this size
+// A column workgroup takes at most 64 KiB of LDS by default and up to the CU's
+// 160 KiB for large n (g, the step and the support bitmap are n-long LDS arrays;
+// a CU then holds one column workgroup).
+constexpr size_t kColLdsDefault = 64 * 1024;
+constexpr size_t kColLdsMax = 160 * 1024;
 
 struct ColLayout {
   size_t ginv, P, wpart, g, sd, inT, Ti, Tv, red, hist, cbuf, tab, total;
+  size_t accept;   // the size a problem is accepted or refused by (validate): P_k unpadded
   int mq, p_in_lds;
   // waves: waves of the column workgroup (its per-wave partial vectors and sums)
   __host__ __device__ ColLayout(int n, int m, int r, int rho, int project, int philox = 0, int waves = kWaves) {
@@ -407,7 +413,6 @@ struct ColLayout {
     p_in_lds = 4 * (size_t)m * r <= kPInLdsMax;
     size_t o = 0;
     ginv = o; o = align16(o + (project ? 8 * (size_t)r * r : 0));
-    P = o;    o = align16(o + (project && p_in_lds ? 4 * (size_t)m * r : 0));
     wpart = o; o = align16(o + 4 * (size_t)waves * mq);
     g = o;    o = align16(o + 4 * (size_t)n);
     sd = o;   o = align16(o + 4 * (size_t)n);
@@ -418,7 +423,11 @@ struct ColLayout {
     hist = o; o = align16(o + 4 * (256 + 8));
     cbuf = o; o = align16(o + 8 * kRMax);
     tab = o;  o = align16(o + (philox ? 4 * (size_t)kNormalTable : 0));
-    total = o;
+    // P_k (columns padded to mq rows) last; left in global memory where only the padding does not fit
+    P = o;
+    accept = o + (project && p_in_lds ? align16(4 * (size_t)m * r) : 0);
+    if (project && o + 4 * (size_t)mq * r > kColLdsMax) p_in_lds = 0;
+    total = o + (project && p_in_lds ? 4 * (size_t)mq * r : 0);
   }
 };
 

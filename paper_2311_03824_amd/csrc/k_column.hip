@@ -51,14 +51,16 @@ struct Lane {
   }
 };
 
-// Sum the per-wave partial vectors of all waves (fixed order 0..W-1); every
-// wave ends with the same total.  Two barriers.
+// Sum the per-wave partial vectors of all waves (fixed order 0..W-1); every wave
+// ends with the same total.  With x, one double per wave is summed the same way.
+// One barrier; wpart and redd may be rewritten only after another.
 template <int NC, int W = kWaves>
 __device__ __forceinline__ void xwave_sum(float4 (&v)[NC], const Lane<NC>& ln, float* wpart, int mq,
-                                          int wave) {
+                                          int wave, double* x = nullptr, double* redd = nullptr, int lane = 0) {
 #pragma unroll
   for (int c = 0; c < NC; ++c)
     if (ln.nv[c] > 0) *reinterpret_cast<float4*>(wpart + wave * mq + 4 * ln.ch[c]) = v[c];
+  if (x && lane == 0) redd[wave] = *x;
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -69,7 +71,12 @@ __device__ __forceinline__ void xwave_sum(float4 (&v)[NC], const Lane<NC>& ln, f
       v[c] = s;
     }
   }
-  __syncthreads();
+  if (x) {
+    double s = redd[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w) s += redd[w];
+    *x = s;
+  }
 }
 
 template <int W = kWaves>
@@ -84,6 +91,7 @@ __device__ __forceinline__ double xwave_sum_scalar(double x, double* redd, int l
 }
 
 // out = sum_{t < cnt} coef[t] * A_k[:, idx[t]]  (idx, coef in LDS), all waves get the total.
+// One barrier; wpart may be rewritten only after another.
 // Each wave keeps up to 8 support columns in flight when A_k has at most 256 rows
 // (4 otherwise, and in the Philox form, where they are generated, not loaded).
 template <int FMT, int NC, int W = kWaves, int POL = POL_STREAM>
@@ -120,22 +128,45 @@ __device__ __forceinline__ void gather(const ALoader<FMT, POL>& L, const Lane<NC
   for (int c = 0; c < NC; ++c) out[c] = acc[c];
 }
 
+// P_k as the column kernel reads it: in LDS column by column (column c at c * stride,
+// rows padded with zeros to the stride, a multiple of 4), where a wave's 16-byte reads
+// of 4 rows per lane have no bank conflicts (row-major, the 4-byte reads at a stride
+// of 4 r words were 8-way conflicts at r = 10: a settled iteration's k_col 0.105 ->
+// 0.083 ms at q = 125, 0.360 -> 0.342 at q = 1000); or, when it does not fit, the
+// row-major workspace copy in global memory.
+struct PView {
+  const float* lds;    // null: in global memory
+  const float* glob;   // m x r, row-major
+  int stride;
+  // rows 4 ch .. 4 ch + 3 of column c; rows at or beyond m (nv valid ones) are zero
+  __device__ __forceinline__ float4 rows(int ch, int nv, int c, int r) const {
+    if (nv <= 0) return make_float4(0.f, 0.f, 0.f, 0.f);
+    if (lds) return *reinterpret_cast<const float4*>(lds + c * stride + 4 * ch);
+    float t[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = e < nv ? glob[(4 * ch + e) * r + c] : 0.f;
+    return make_float4(t[0], t[1], t[2], t[3]);
+  }
+};
+
 // v <- v - P_k d with d = G_k^{-1} P_k^T v (FP64 products and solve).  The r
 // reductions of P_k^T v are split across the waves and exchanged through cbuf
 // (LDS, r doubles); every wave then applies the same d to its own copy of v.
+// v is zero on rows at or beyond m and stays so.
 // If bl != nullptr, lane i < r receives b_i = -d_i (the LS coefficients when
 // v = A_k s_k - y_k).  One barrier; cbuf may be rewritten only after another.
 template <int NC, int W = kWaves>
-__device__ __forceinline__ void project(float4 (&v)[NC], const Lane<NC>& ln, const float* Pl,
+__device__ __forceinline__ void project(float4 (&v)[NC], const Lane<NC>& ln, const PView& P,
                                         const double* Gi, int r, int lane, int wave, double* cbuf,
                                         double* bl) {
   for (int rr = wave; rr < r; rr += W) {
     double part = 0.0;
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+    for (int c = 0; c < NC; ++c) {
+      const float4 p = P.rows(ln.ch[c], ln.nv[c], rr, r);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (e < ln.nv[c]) part = fma((double)Pl[(4 * ln.ch[c] + e) * r + rr], (double)get4(v[c], e), part);
+      for (int e = 0; e < 4; ++e) part = fma((double)get4(p, e), (double)get4(v[c], e), part);
+    }
     const double tot = wave_sum_dpp(part);
     if (lane == 0) cbuf[rr] = tot;
   }
@@ -151,10 +182,11 @@ __device__ __forceinline__ void project(float4 (&v)[NC], const Lane<NC>& ln, con
   for (int rr = 0; rr < r; ++rr) {
     const double drr = readlane_f64(myd, __builtin_amdgcn_readfirstlane(rr));
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
+    for (int c = 0; c < NC; ++c) {
+      const float4 p = P.rows(ln.ch[c], ln.nv[c], rr, r);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (e < ln.nv[c]) acc[c][e] = fma(-(double)Pl[(4 * ln.ch[c] + e) * r + rr], drr, acc[c][e]);
+      for (int e = 0; e < 4; ++e) acc[c][e] = fma(-(double)get4(p, e), drr, acc[c][e]);
+    }
   }
 #pragma unroll
   for (int c = 0; c < NC; ++c)
@@ -548,7 +580,8 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   const ColLayout lay(n, m, r, rho, a.project, FMT == FMT_PHILOX, W);
   double* Gi = reinterpret_cast<double*>(smem + lay.ginv);
   // P_k in LDS when it fits, else read from the workspace copy in global memory
-  float* Pl = lay.p_in_lds ? reinterpret_cast<float*>(smem + lay.P) : const_cast<float*>(a.P + (long long)k * m * r);
+  float* Pl = reinterpret_cast<float*>(smem + lay.P);
+  const PView Pv = {lay.p_in_lds ? Pl : nullptr, a.P + (long long)k * m * r, lay.mq};
   float* wpart = reinterpret_cast<float*>(smem + lay.wpart);
   float* gl = reinterpret_cast<float*>(smem + lay.g);
   float* sd = reinterpret_cast<float*>(smem + lay.sd);
@@ -593,8 +626,13 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   for (int w = tid; w < nwords; w += kT) inT[w] = 0u;
   if (a.project) {
     const float* Pk = a.P + (long long)k * m * r;
-    if (lay.p_in_lds)
-      for (int t = tid; t < m * r; t += kT) Pl[t] = Pk[t];
+    if (lay.p_in_lds) {   // consecutive threads take consecutive columns of a row: coalesced, spread over the banks
+      const int mq = lay.mq;
+      for (int t = tid; t < mq * r; t += kT) {
+        const int i = t / r, c = t - i * r;
+        Pl[c * mq + i] = i < m ? Pk[t] : 0.f;
+      }
+    }
     const double* Gk = a.Ginv + (long long)k * r * r;
     for (int t = tid; t < r * r; t += kT) Gi[t] = Gk[t];
   }
@@ -658,13 +696,34 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   bool have_list = false;
   int2 seg = make_int2(0, 0);
 
+  // u = Pi (A_k s - y_k) and w = Pi A_k g_T.  A step that keeps T moves s by -mu g_T
+  // and so u by -mu w, which is at hand: the next step needs neither the gather of
+  // A_k s nor its projection (equal up to rounding; the tail gathers A_k s afresh):
+  // 0.083 -> 0.075 ms at q = 125, 0.342 -> 0.323 at q = 1000.
+  // Not in the mixed form, whose w comes from the hi plane and u from hi + lo.
+  // smin: the smallest magnitude of s on T as a bit pattern, when known.
+  float4 v[NC], w[NC];
+  bool have_u = false, have_smin = false;
+  unsigned smin = 0u;
+
   for (int it = 0; it < a.tau; ++it) {
-    // u = Pi (A_k s - y_k)   (Pi = I in the initialisation)
-    float4 v[NC];
-    gather<GF, NC, W>(L, ln, Ti, Tv, hasT ? rho : 0, v, wpart, mq, wave);
+    if (!have_u) {
+      gather<GF, NC, W>(L, ln, Ti, Tv, hasT ? rho : 0, v, wpart, mq, wave);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) v[c] = sub4(v[c], yv[c]);
-    if (a.project) project<NC, W>(v, ln, Pl, Gi, r, lane, wave, cbuf, nullptr);
+      for (int c = 0; c < NC; ++c) v[c] = sub4(v[c], yv[c]);
+      if (a.project) project<NC, W>(v, ln, Pv, Gi, r, lane, wave, cbuf, nullptr);
+    }
+    auto move_u = [&](double mu) {
+      if constexpr (GF == SF) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          v[c] = make_float4((float)fma(-mu, (double)w[c].x, (double)v[c].x),
+                             (float)fma(-mu, (double)w[c].y, (double)v[c].y),
+                             (float)fma(-mu, (double)w[c].z, (double)v[c].z),
+                             (float)fma(-mu, (double)w[c].w, (double)v[c].w));
+        have_u = true;
+      }
+    };
 
     const bool last = (it == a.tau - 1);
     // the test can only hold when ||u|| / bound, a lower estimate of its left side, is
@@ -673,10 +732,13 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     double un = 0.0;
     if (screen && hasT && !(last && a.G_out)) {
       un = sqrt(sumsq<NC>(v));
-      unsigned smin = 0x7f800000u;
-      for (int t = lane; t < rho; t += 64) smin = min(smin, __float_as_uint(Tv[t]) & 0x7fffffffu);
+      if (!have_smin) {
+        smin = 0x7f800000u;
+        for (int t = lane; t < rho; t += 64) smin = min(smin, __float_as_uint(Tv[t]) & 0x7fffffffu);
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) smin = min(smin, (unsigned)__shfl_xor((int)smin, o));
+        for (int o = 32; o > 0; o >>= 1) smin = min(smin, (unsigned)__shfl_xor((int)smin, o));
+        have_smin = true;
+      }
       on_T = un < (double)bnd * (double)__uint_as_float(smin);
     }
 
@@ -686,10 +748,10 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     double mu = 0.0;
     bool kept = false, have_mu = false;
     for (;;) {
-      float4 w[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) w[c] = make_float4(0.f, 0.f, 0.f, 0.f);
       double gT2 = 0.0;
+      if (!have_mu)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) w[c] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (on_T) {
         if (!have_list) seg = support_list<W>(Ti, rho, list, lane, wave);
         have_list = true;
@@ -701,8 +763,7 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
         if (have_mu) break;
       }
       if (hasT) {
-        xwave_sum<NC, W>(w, ln, wpart, mq, wave);
-        gT2 = xwave_sum_scalar<W>(gT2, redd, lane, wave);
+        xwave_sum<NC, W>(w, ln, wpart, mq, wave, &gT2, redd, lane);
       } else {
         // no support yet (s = 0): restrict to the support of HardThreshold(g, rho)
         nan_seen += block_select<W>(gl, n, rho, Ti, Tv, hist);
@@ -710,7 +771,7 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
         gT2 = 0.0;
         for (int t = 0; t < rho; ++t) gT2 = fma((double)Tv[t], (double)Tv[t], gT2);
       }
-      if (a.project) project<NC, W>(w, ln, Pl, Gi, r, lane, wave, cbuf, nullptr);
+      if (a.project) project<NC, W>(w, ln, Pv, Gi, r, lane, wave, cbuf, nullptr);
       const double ww = sumsq<NC>(w);
       mu = (ww > 0.0 && isfinite(ww) && isfinite(gT2)) ? gT2 / ww : 0.0;
       if (!on_T) break;
@@ -735,6 +796,9 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
           Tv[t] = gT[t];
           sd[Ti[t]] = gT[t];
         }
+        have_u = false;
+        move_u(mu);
+        smin = kmin;
         break;
       }
       have_mu = true;
@@ -751,8 +815,10 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     // s - mu g, then HardThreshold
     for (int j = tid; j < n; j += kT) gl[j] = (float)fma(-mu, (double)gl[j], (double)sd[j]);
     __syncthreads();
+    have_smin = have_u = false;
     if (hasT && block_support_kept<W>(gl, n, inT, reinterpret_cast<unsigned*>(hist))) {
       // most steps keep T: Ti (ascending) and inT stand, s takes the new values on T
+      move_u(mu);
       for (int t = tid; t < rho; t += kT) {
         const int j = Ti[t];
         Tv[t] = gl[j];
@@ -774,14 +840,13 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   }
 
   if (a.tail != TAIL_NONE) {
-    float4 v[NC];
     gather<GF, NC, W>(L, ln, Ti, Tv, hasT ? rho : 0, v, wpart, mq, wave);
 #pragma unroll
     for (int c = 0; c < NC; ++c) v[c] = sub4(v[c], yv[c]);   // A_k s_k - y_k
     if (a.tail == TAIL_LSGRAD) {
       // b_k = G^{-1} P^T (y - A s); r_k = P b + A s - y = Pi (A s - y)
       double b = 0.0;
-      project<NC, W>(v, ln, Pl, Gi, r, lane, wave, cbuf, &b);
+      project<NC, W>(v, ln, Pv, Gi, r, lane, wave, cbuf, &b);
       const double rr = sumsq<NC>(v);
       if (wave == 0 && lane < r) a.Bt[(long long)k * r + lane] = (float)b;
       if (tid == 0 && a.rr) a.rr[k] = rr;
@@ -791,7 +856,6 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
       const double yy = sumsq<NC>(yv);
       if (tid == 0 && a.rr) a.rr[k] = yy;
     }
-    float4 w[NC];
     double dummy = 0.0;
     fused_pass<SF, NC, JU, W>(Ls, ln, v, n, gl, nullptr, w, dummy, lane, wave);
     __syncthreads();
@@ -1266,6 +1330,8 @@ hipError_t launch_au_grp(int fmt, int rmax, int waves, const AUArgs* tab, const 
 size_t col_lds_bytes(int n, int m, int r, int rho, int project, int philox, int waves) {
   return ColLayout(n, m, r, rho, project, philox, waves).total;
 }
+
+size_t col_lds_accept(int n, int m, int r, int rho, int philox) { return ColLayout(n, m, r, rho, 1, philox).accept; }
 
 // Raise the dynamic LDS limit of each kernel in `fns` to kColLdsMax (null entries skipped).
 template <class F>
