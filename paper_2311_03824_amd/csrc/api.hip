@@ -75,6 +75,14 @@ struct Carver {
 // chip for small n, one split when every split would hold few columns
 int grad_splits(int q) { return q >= 512 ? 4 : (q >= 64 ? 2 : 1); }
 
+// column splits of a GDmin iteration's gradient: none up to 256 columns (k_urows sums
+// all columns of its rows: the same 171 us an iteration at q = 125 with 1, 4 or 8
+// splits); above, about a 64-row workgroup per CU with at least 64 columns each (an
+// iteration at n = q = 1000 takes 626 us with 15 splits, 631 with 4, 632 with none)
+int upd_splits(int n, int q) {
+  return q <= 256 ? 1 : std::max(2, std::min(std::min(16, 256 / ((n + 63) / 64)), q / 64));
+}
+
 // Automatic rank (Sec. 2.6): K = max(1, floor(min(n, q, m) / 10)) leading singular
 // values of L_0 decide r; the block subspace iteration carries b = K + 8 columns
 // (capped by the LDS of its b x b FP64 matrices and by min(n, q)).
@@ -188,7 +196,10 @@ struct altgdmin_handle {
   int* colflags;
   float* colbound;
   float* gpart;
-  int KS;
+  int KS;                  // column splits of the subspace iteration
+  int KSu;                 // column splits of the gradient
+  double* upart;           // U update: Gram parts, what to do
+  int* upd;
   float* U;
   float* Uprev;
   float* Utmp;
@@ -267,7 +278,8 @@ size_t carve(altgdmin_handle* h, void* base) {
   h->colrr = c.take<double>(q);
   h->colflags = c.take<int>(q);
   h->KS = grad_splits(p.q);
-  h->gpart = c.take<float>((size_t)h->KS * n * r);
+  h->KSu = upd_splits(p.n, p.q);
+  h->gpart = c.take<float>((size_t)std::max(h->KS, h->KSu) * n * r);
   h->U = c.take<float>(n * r);
   h->Uprev = c.take<float>(n * r);
   h->Utmp = c.take<float>(n * r);
@@ -275,6 +287,8 @@ size_t carve(altgdmin_handle* h, void* base) {
   h->rlog_len = h->par.t_max > 0 ? h->par.t_max : 1;
   h->rlog = c.take<double>(h->rlog_len);
   h->colbound = c.take<float>(q);
+  h->upart = c.take<double>(upd_part_doubles(p.n, (int)r));
+  h->upd = c.take<int>(1);
   if (p.r == 0) h->rank_ws = c.take<unsigned char>(rank_scratch(nullptr, rank_shape(p.n, p.q, p.m)).bytes);
   return (c.off + kAlign - 1) / kAlign * kAlign;
 }
@@ -429,9 +443,19 @@ QRArgs qr_args(const altgdmin_handle* h, int mode) {
   QRArgs a;
   std::memset(&a, 0, sizeof(a));
   a.n = h->prob.n; a.r = h->prob.r; a.KS = h->KS; a.mode = mode;
-  a.gpart = h->gpart; a.U = h->U; a.Uprev = h->Uprev; a.Utmp = h->Utmp; a.ctl = h->ctl;
-  a.eta_c = h->par.eta_c; a.power_tol = h->par.power_tol;
-  a.colrr = h->colrr; a.colflags = h->colflags; a.q = h->prob.q;
+  a.gpart = h->gpart; a.U = h->U; a.Utmp = h->Utmp; a.ctl = h->ctl;
+  a.power_tol = h->par.power_tol;
+  return a;
+}
+
+UpdArgs upd_args(const altgdmin_handle* h) {
+  UpdArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.n = h->prob.n; a.q = h->prob.q; a.r = h->prob.r; a.KS = h->KSu;
+  a.H = h->H; a.B = h->Bt; a.gpart = h->gpart; a.U = h->U; a.Uprev = h->Uprev;
+  a.part = h->upart; a.upd = h->upd; a.ctl = h->ctl;
+  a.eta_c = h->par.eta_c;
+  a.colrr = h->colrr; a.colflags = h->colflags;
   a.rlog = h->rlog; a.rlog_len = h->rlog_len;
   a.hi_max = h->par.bf16_hi_max;
   a.stall = h->par.bf16_stall;
@@ -680,6 +704,15 @@ hipError_t fourier_launch(altgdmin_handle* h, int which, hipStream_t st) {
   }
 }
 
+// The gradient's rows with their Gram parts (after its column splits, when it has some).
+hipError_t grad_launch(const altgdmin_handle* h, hipStream_t st) {
+  if (h->KSu > 1) {
+    const hipError_t e = launch_ugrad(upd_args(h), st);
+    if (e != hipSuccess) return e;
+  }
+  return launch_urows(upd_args(h), st);
+}
+
 // One GDmin iteration of Alg. 1 on stream st.
 int enqueue_iteration(altgdmin_handle* h, hipStream_t st) {
   if (h->fmt == FMT_PFOURIER) {
@@ -699,8 +732,8 @@ int enqueue_iteration(altgdmin_handle* h, hipStream_t st) {
   }
   HIPCHK(au_launch(h, h->fmt, au, st));
   HIPCHK(col_launch(h, h->colfmt, ca, st));
-  HIPCHK(launch_grad(h->H, h->Bt, p.n, p.q, p.r, h->KS, h->gpart, nullptr, st));
-  HIPCHK(launch_qr(qr_args(h, QR_GD), st));
+  HIPCHK(grad_launch(h, st));
+  HIPCHK(launch_uapply(upd_args(h), st));
   return ALTGDMIN_OK;
 }
 
@@ -954,9 +987,9 @@ int altgdmin_profile_iteration(altgdmin_handle* h, int32_t iters, void* stream, 
     if (e == hipSuccess) e = hipEventRecord(ev[1], st);
     if (e == hipSuccess) e = col_launch(h, h->colfmt, ca, st);
     if (e == hipSuccess) e = hipEventRecord(ev[2], st);
-    if (e == hipSuccess) e = launch_grad(h->H, h->Bt, p.n, p.q, p.r, h->KS, h->gpart, nullptr, st);
+    if (e == hipSuccess) e = grad_launch(h, st);
     if (e == hipSuccess) e = hipEventRecord(ev[3], st);
-    if (e == hipSuccess) e = launch_qr(qr_args(h, QR_GD), st);
+    if (e == hipSuccess) e = launch_uapply(upd_args(h), st);
     if (e == hipSuccess) e = hipEventRecord(ev[4], st);
     if (e == hipSuccess) e = hipEventSynchronize(ev[4]);
     for (int k = 0; k < 4 && e == hipSuccess; ++k) {
@@ -1246,13 +1279,13 @@ struct Bucket {
 struct GroupPlan {
   std::vector<AUArgs> au;
   std::vector<ColArgs> col;
-  std::vector<GradArgs> grad;
-  std::vector<QRArgs> qr;
+  std::vector<UpdArgs> upd;
   std::map<int, Bucket> au_b, col_b;   // key fmt * 64 + inst
-  std::vector<int4> grad_map;
-  size_t qr_lds = 0;
+  std::vector<int4> grad_map;   // (problem, 64-row block, column split), of problems with splits
+  std::vector<int2> row_map;    // (problem, 64-row block)
+  std::vector<int2> app_map;    // (problem, row block of k_uapply)
   // byte offsets in the group workspace
-  size_t o_au, o_col, o_grad, o_qr, o_gm, total;
+  size_t o_au, o_col, o_upd, o_gm, o_rm, o_am, total;
 };
 
 int plan_group(altgdmin_handle* const* hs, int count, GroupPlan& g) {
@@ -1271,16 +1304,10 @@ int plan_group(altgdmin_handle* const* hs, int count, GroupPlan& g) {
     ColArgs ca = gd_col_args(h);
     ca.gate = done; ca.gate_want = 0;
     g.col.push_back(ca);
-    GradArgs ga;
-    ga.H = h->H; ga.B = h->Bt; ga.n = p.n; ga.q = p.q; ga.r = p.r; ga.KS = h->KS; ga.gpart = h->gpart;
-    ga.skip = done;
-    g.grad.push_back(ga);
-    QRArgs qa = qr_args(h, QR_GD);
-    qa.tol = h->par.tol_resid;
-    qa.gate_done = done ? 1 : 0;
-    qa.lds = (size_t)p.n * p.r * sizeof(float) <= kQRLdsMax ? 1 : 0;
-    if (qa.lds) g.qr_lds = std::max(g.qr_lds, (size_t)p.n * p.r * sizeof(float));
-    g.qr.push_back(qa);
+    UpdArgs ua = upd_args(h);
+    ua.tol = h->par.tol_resid;
+    ua.gate_done = done ? 1 : 0;
+    g.upd.push_back(ua);
     const int f = h->fmt, cf = h->colfmt, phx = f == FMT_PHILOX;
     const int nc = (p.m + 255) / 256, rr = (p.r + 1) / 2 * 2, cw = h->col_waves;
     const int aw = au_waves(p);
@@ -1296,8 +1323,11 @@ int plan_group(altgdmin_handle* const* hs, int count, GroupPlan& g) {
       ab.map.push_back(make_int2(i, k));
       cb.map.push_back(make_int2(i, k));
     }
-    for (int jb = 0; jb < (p.n + 63) / 64; ++jb)
-      for (int ks = 0; ks < h->KS; ++ks) g.grad_map.push_back(make_int4(i, jb, ks, 0));
+    for (int jb = 0; jb < (p.n + 63) / 64; ++jb) {
+      g.row_map.push_back(make_int2(i, jb));
+      for (int ks = 0; ks < h->KSu && h->KSu > 1; ++ks) g.grad_map.push_back(make_int4(i, jb, ks, 0));
+    }
+    for (int jb = 0; jb < uapply_blocks(p.n); ++jb) g.app_map.push_back(make_int2(i, jb));
     ab.lds = std::max(ab.lds, AULayout(p.m, p.r, phx, aw).total);
     cb.lds = std::max(cb.lds, ColLayout(p.n, p.m, p.r, p.rho, 1, phx, cw).total);
   }
@@ -1305,11 +1335,12 @@ int plan_group(altgdmin_handle* const* hs, int count, GroupPlan& g) {
   auto take = [&](size_t bytes) { o = (o + kAlign - 1) / kAlign * kAlign; size_t r = o; o += bytes; return r; };
   g.o_au = take(g.au.size() * sizeof(AUArgs));
   g.o_col = take(g.col.size() * sizeof(ColArgs));
-  g.o_grad = take(g.grad.size() * sizeof(GradArgs));
-  g.o_qr = take(g.qr.size() * sizeof(QRArgs));
+  g.o_upd = take(g.upd.size() * sizeof(UpdArgs));
   for (auto& kv : g.au_b) kv.second.off = take(kv.second.map.size() * sizeof(int2));
   for (auto& kv : g.col_b) kv.second.off = take(kv.second.map.size() * sizeof(int2));
   g.o_gm = take(g.grad_map.size() * sizeof(int4));
+  g.o_rm = take(g.row_map.size() * sizeof(int2));
+  g.o_am = take(g.app_map.size() * sizeof(int2));
   g.total = (o + kAlign - 1) / kAlign * kAlign;
   return ALTGDMIN_OK;
 }
@@ -1378,19 +1409,19 @@ int altgdmin_step_many(altgdmin_handle* const* hs, int32_t count, int32_t iters,
   auto put = [&](size_t off, const void* src, size_t bytes) { if (bytes) std::memcpy(buf.data() + off, src, bytes); };
   put(g.o_au, g.au.data(), g.au.size() * sizeof(AUArgs));
   put(g.o_col, g.col.data(), g.col.size() * sizeof(ColArgs));
-  put(g.o_grad, g.grad.data(), g.grad.size() * sizeof(GradArgs));
-  put(g.o_qr, g.qr.data(), g.qr.size() * sizeof(QRArgs));
+  put(g.o_upd, g.upd.data(), g.upd.size() * sizeof(UpdArgs));
   for (const auto& kv : g.au_b) put(kv.second.off, kv.second.map.data(), kv.second.map.size() * sizeof(int2));
   for (const auto& kv : g.col_b) put(kv.second.off, kv.second.map.data(), kv.second.map.size() * sizeof(int2));
   put(g.o_gm, g.grad_map.data(), g.grad_map.size() * sizeof(int4));
+  put(g.o_rm, g.row_map.data(), g.row_map.size() * sizeof(int2));
+  put(g.o_am, g.app_map.data(), g.app_map.size() * sizeof(int2));
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* dev = static_cast<char*>(group_ws);
   rc = upload_tables(buf, dev, st);
   if (rc) return rc;
   const AUArgs* au_tab = reinterpret_cast<const AUArgs*>(dev + g.o_au);
   const ColArgs* col_tab = reinterpret_cast<const ColArgs*>(dev + g.o_col);
-  const GradArgs* grad_tab = reinterpret_cast<const GradArgs*>(dev + g.o_grad);
-  const QRArgs* qr_tab = reinterpret_cast<const QRArgs*>(dev + g.o_qr);
+  const UpdArgs* upd_tab = reinterpret_cast<const UpdArgs*>(dev + g.o_upd);
   // one load policy for the round: cached loads when the planes streamed by all
   // the problems together fit in the Infinity Cache
   size_t plane_bytes = 0;
@@ -1408,8 +1439,10 @@ int altgdmin_step_many(altgdmin_handle* const* hs, int32_t count, int32_t iters,
       HIPCHK(launch_col_grp(b.fmt, b.inst, b.waves, col_tab, reinterpret_cast<const int2*>(dev + b.off),
                             (int)b.map.size(), b.lds, st, pol));
     }
-    HIPCHK(launch_grad_grp(grad_tab, reinterpret_cast<const int4*>(dev + g.o_gm), (int)g.grad_map.size(), st));
-    HIPCHK(launch_qr_grp(qr_tab, count, g.qr_lds, st));
+    if (!g.grad_map.empty())
+      HIPCHK(launch_ugrad_grp(upd_tab, reinterpret_cast<const int4*>(dev + g.o_gm), (int)g.grad_map.size(), st));
+    HIPCHK(launch_urows_grp(upd_tab, reinterpret_cast<const int2*>(dev + g.o_rm), (int)g.row_map.size(), st));
+    HIPCHK(launch_uapply_grp(upd_tab, reinterpret_cast<const int2*>(dev + g.o_am), (int)g.app_map.size(), st));
   }
   for (int i = 0; i < count; ++i) hs[i]->t_host += iters;
   return ALTGDMIN_OK;
@@ -1561,14 +1594,17 @@ int altgdmin_op_measure(const altgdmin_problem* prob, const double* Xt, float* Y
   return ALTGDMIN_OK;
 }
 
-// scratch layout of the U-side entry points: Ctl | gpart (KS n r) | Utmp (n r) | T (q r)
+// scratch layout of the U-side entry points: Ctl | gpart (KS n r) | Utmp (n r) | T (q r),
+// then what the U update of altgdmin_op_qr_step needs (base: the bytes without it)
 struct OpScratch {
   Ctl* ctl;
   float* gpart;
   float* Utmp;
   float* T;
+  double* part;
+  int* upd;
   int KS;
-  size_t bytes;
+  size_t base, bytes;
 };
 
 static OpScratch op_scratch(void* base, int n, int q, int r) {
@@ -1579,6 +1615,9 @@ static OpScratch op_scratch(void* base, int n, int q, int r) {
   s.gpart = c.take<float>((size_t)s.KS * n * r);
   s.Utmp = c.take<float>((size_t)n * r);
   s.T = c.take<float>((size_t)q * r);
+  s.base = c.off;
+  s.part = c.take<double>(upd_part_doubles(n, r));
+  s.upd = c.take<int>(1);
   s.bytes = c.off;
   return s;
 }
@@ -1594,7 +1633,7 @@ int altgdmin_op_grad(const float* H, const float* Bt, int32_t n, int32_t q, int3
   if (!H || !Bt || !grad || !scratch || n < 1 || q < 1 || r < 1 || r > kRMax) return fail(ALTGDMIN_EINVAL, "bad grad arguments");
   NEED_STREAM(stream);
   OpScratch s = op_scratch(scratch, n, q, r);
-  if (scratch_bytes < s.bytes) return fail(ALTGDMIN_ENOWS, "scratch too small");
+  if (scratch_bytes < s.base) return fail(ALTGDMIN_ENOWS, "scratch too small");
   hipStream_t st = static_cast<hipStream_t>(stream);
   HIPCHK(launch_grad(H, Bt, n, q, r, s.KS, s.gpart, nullptr, st));
   HIPCHK(launch_sum_partials(s.gpart, s.KS, (long long)n * r, grad, st));
@@ -1610,11 +1649,15 @@ int altgdmin_op_qr_step(const float* U, const float* grad, int32_t n, int32_t r,
   if (scratch_bytes < s.bytes) return fail(ALTGDMIN_ENOWS, "scratch too small");
   hipStream_t st = static_cast<hipStream_t>(stream);
   HIPCHK(launch_copy_f(U_out, U, (long long)n * r, st));
-  QRArgs a;
+  UpdArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.n = n; a.r = r; a.KS = 1; a.mode = QR_GD; a.gpart = grad; a.U = U_out; a.Utmp = s.Utmp;
+  a.n = n; a.r = r; a.KS = 1;
+  a.gpart = const_cast<float*>(grad);   // read only with KS = 1
+  a.U = U_out; a.Uprev = s.Utmp;
+  a.part = s.part; a.upd = s.upd;
   a.eta_c = eta_c; a.eta_io = eta_io;
-  HIPCHK(launch_qr(a, st));
+  HIPCHK(launch_urows(a, st));
+  HIPCHK(launch_uapply(a, st));
   return ALTGDMIN_OK;
 }
 
@@ -1626,7 +1669,7 @@ static int subspace_body(const float* L0t, int32_t n, int32_t q, int32_t r, cons
                          double tol, float* U_out, int32_t* iters_out, void* scratch, size_t scratch_bytes,
                          void* stream) {
   OpScratch s = op_scratch(scratch, n, q, r);
-  if (scratch_bytes < s.bytes) return fail(ALTGDMIN_ENOWS, "scratch too small");
+  if (scratch_bytes < s.base) return fail(ALTGDMIN_ENOWS, "scratch too small");
   hipStream_t st = static_cast<hipStream_t>(stream);
   HIPCHK(launch_reset_ctl(s.ctl, 1, st));
   if (U_start) HIPCHK(launch_copy_f(s.Utmp, U_start, (long long)n * r, st));
@@ -1737,7 +1780,7 @@ int altgdmin_op_subspace_noalloc(const float* L0t, int32_t n, int32_t q, int32_t
   int rc = subspace_args_ok(L0t, n, q, r, iters, U_out);
   if (rc) return rc;
   NEED_STREAM(stream);
-  const size_t need = op_scratch(nullptr, n, q, r).bytes;
+  const size_t need = op_scratch(nullptr, n, q, r).base;
   if (need > ALTGDMIN_STATIC_SCRATCH_BYTES)
     return fail(ALTGDMIN_ENOWS, "sizes need " + std::to_string(need) + " bytes of scratch, more than the " +
                                     std::to_string((size_t)ALTGDMIN_STATIC_SCRATCH_BYTES) + " of the static array");

@@ -1,67 +1,18 @@
-// Reductions across columns and the U update of AltGDmin-LR+S for gfx950.
+// Reductions across columns and the spectral start of AltGDmin-LR+S for gfx950.
 //
-//  k_grad  : partials of grad_U f = sum_k h_k b_k^T (Sec. 2.1) over KS column
-//            splits, each summed in a fixed order (deterministic, no atomics).
-//            The same kernel forms Z = L_0 (L_0^T U) in the subspace iteration.
+//  k_grad  : partials of sum_k h_k b_k^T over KS column splits, each summed in a
+//            fixed order (deterministic, no atomics): the gradient entry point, and
+//            Z = L_0 (L_0^T U) in the subspace iteration.
 //  k_ltu   : T = L_0^T U for the subspace iteration (one wave per column).
-//  k_qr    : one workgroup: sums the partials, sets eta = eta_c / ||grad||_2 at
-//            t = 1 (Sec. 2.6), forms U - eta grad and re-orthonormalises it by
-//            CholeskyQR2 (FP64 Gram and Cholesky, positive-diagonal R), the QR of
-//            the projected GD step in Alg. 1; also the subspace-iteration
-//            orthonormalisation and the residual monitor.
+//  k_qr    : one workgroup: orthonormalises the start block, or a step of the
+//            subspace iteration from the summed partials, by CholeskyQR2 (FP64 Gram
+//            and Cholesky, positive-diagonal R), with its stop rule.
 #include <mutex>
 
 #include "launch.h"
+#include "uside.h"
 
 namespace altg {
-
-// One workgroup of 16 waves per block of 64 rows j; wave w sums the columns
-// k = w, w + 16, ... of its split; the 16 wave partials are added in a fixed
-// pairwise order.  Row k of B is fetched by lanes 0..r-1 with one vector load
-// and broadcast with readlane, so that loads of later columns stay in flight.
-__device__ __forceinline__ void grad_body(const float* __restrict__ H, const float* __restrict__ B, int n, int q, int r,
-                                          int KS, float* __restrict__ gpart, int jblock, int ks,
-                                          float (*red)[64][kRMax + 1]) {
-  const int lane = threadIdx.x & 63, ph = wave_id();
-  const int j = jblock * 64 + lane;
-  const int jc = j < n ? j : n - 1;
-  const int k0 = (int)((long long)q * ks / KS), k1 = (int)((long long)q * (ks + 1) / KS);
-  float acc[kRMax];
-#pragma unroll
-  for (int c = 0; c < kRMax; ++c) acc[c] = 0.f;
-  constexpr int KU = 16;   // loads in flight per wave; the order of the k terms does not depend on it
-  for (int kb = k0 + ph; kb < k1; kb += kGradWaves * KU) {
-    float h[KU], bv[KU];
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int k = kb + u * kGradWaves;
-      const int kc = k < k1 ? k : k0;
-      h[u] = H[(long long)kc * n + jc];
-      bv[u] = B[(long long)kc * r + (lane < r ? lane : 0)];
-    }
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const bool ok = kb + u * kGradWaves < k1;
-      const float hu = ok ? h[u] : 0.f;
-#pragma unroll
-      for (int c = 0; c < kRMax; ++c)
-        if (c < r) acc[c] = fmaf(hu, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv[u]), c)), acc[c]);
-    }
-  }
-  // pairwise tree over the waves in a fixed order: (w, w + h) for h = 8, 4, 2, 1
-  for (int hh = kGradWaves / 2; hh >= 1; hh >>= 1) {
-    if (ph >= hh && ph < 2 * hh)
-#pragma unroll
-      for (int c = 0; c < kRMax; ++c) red[ph - hh][lane][c] = acc[c];
-    __syncthreads();
-    if (ph < hh)
-#pragma unroll
-      for (int c = 0; c < kRMax; ++c) acc[c] += red[ph][lane][c];
-    __syncthreads();
-  }
-  if (ph == 0 && j < n)
-    for (int c = 0; c < r; ++c) gpart[((long long)ks * n + j) * r + c] = acc[c];
-}
 
 __global__ __launch_bounds__(kGradWaves * 64) void k_grad(const float* __restrict__ H, const float* __restrict__ B,
                                                           int n, int q, int r, int KS, float* __restrict__ gpart,
@@ -69,15 +20,6 @@ __global__ __launch_bounds__(kGradWaves * 64) void k_grad(const float* __restric
   if (skip && *skip) return;
   __shared__ float red[kGradWaves / 2][64][kRMax + 1];
   grad_body(H, B, n, q, r, KS, gpart, blockIdx.x, blockIdx.y, red);
-}
-
-// Several problems in one launch: block b is (problem, row block, split) = map[b].
-__global__ __launch_bounds__(kGradWaves * 64) void k_grad_grp(const GradArgs* tab, const int4* map) {
-  __shared__ float red[kGradWaves / 2][64][kRMax + 1];
-  const int4 mp = map[blockIdx.x];
-  const GradArgs a = tab[mp.x];
-  if (a.skip && *a.skip) return;
-  grad_body(a.H, a.B, a.n, a.q, a.r, a.KS, a.gpart, mp.y, mp.z, red);
 }
 
 __global__ __launch_bounds__(256) void k_ltu(const float* __restrict__ L0t, const float* __restrict__ U, int n,
@@ -134,40 +76,6 @@ __device__ void block_gram(const float* X, const float* Y, int n, int r, double*
     }
   }
   __syncthreads();
-}
-
-// Largest eigenvalue of a symmetric r x r matrix (cyclic Jacobi, single thread, in place).
-__device__ double jacobi_max_eig(double* W, int r) {
-  for (int sweep = 0; sweep < 60; ++sweep) {
-    double off = 0.0, diag = 0.0;
-    for (int a = 0; a < r; ++a) {
-      diag += W[a * r + a] * W[a * r + a];
-      for (int b = a + 1; b < r; ++b) off += W[a * r + b] * W[a * r + b];
-    }
-    if (off <= 1e-30 * diag || off == 0.0) break;
-    for (int p = 0; p < r; ++p) {
-      for (int q = p + 1; q < r; ++q) {
-        const double apq = W[p * r + q];
-        if (apq == 0.0) continue;
-        const double theta = (W[q * r + q] - W[p * r + p]) / (2.0 * apq);
-        const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-        const double c = 1.0 / sqrt(t * t + 1.0), s = t * c;
-        for (int k = 0; k < r; ++k) {   // columns p, q
-          const double wkp = W[k * r + p], wkq = W[k * r + q];
-          W[k * r + p] = c * wkp - s * wkq;
-          W[k * r + q] = s * wkp + c * wkq;
-        }
-        for (int k = 0; k < r; ++k) {   // rows p, q
-          const double wpk = W[p * r + k], wqk = W[q * r + k];
-          W[p * r + k] = c * wpk - s * wqk;
-          W[q * r + k] = s * wpk + c * wqk;
-        }
-      }
-    }
-  }
-  double lam = W[0];
-  for (int a = 1; a < r; ++a) lam = fmax(lam, W[a * r + a]);
-  return lam;
 }
 
 // In-place lower Cholesky factor of the SPD r x r matrix W (row-major LDS) by
@@ -237,7 +145,6 @@ __device__ __forceinline__ bool block_cholqr_pass(float* X, int n, int r, double
 struct QRShared {
   double sh[kQRThreads];
   double W[kRMax * kRMax], Lf[kRMax];
-  double eta_s;
   int okflag;
 };
 
@@ -245,12 +152,10 @@ __device__ __forceinline__ void qr_body(const QRArgs& a, unsigned char* dsm, QRS
   double* sh = S.sh;
   double* W = S.W;
   double* Lf = S.Lf;
-  double& eta_s = S.eta_s;
   int& okflag = S.okflag;
   const int tid = threadIdx.x;
   const int n = a.n, r = a.r, nr = n * r;
   if (a.mode == QR_POWER && a.ctl && a.ctl->conv) return;
-  if (a.mode == QR_GD && a.gate_done && a.ctl && a.ctl->done) return;
   float* X = a.lds ? reinterpret_cast<float*>(dsm) : a.Utmp;
 
   if (a.mode != QR_ORTH) {
@@ -263,56 +168,27 @@ __device__ __forceinline__ void qr_body(const QRArgs& a, unsigned char* dsm, QRS
           s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
         }
         reinterpret_cast<float4*>(X)[i4] = s;
-        if (a.grad_out) {
-          a.grad_out[4 * i4] = s.x; a.grad_out[4 * i4 + 1] = s.y;
-          a.grad_out[4 * i4 + 2] = s.z; a.grad_out[4 * i4 + 3] = s.w;
-        }
       }
     } else {
       for (int idx = tid; idx < nr; idx += kQRThreads) {
         float s = a.gpart[idx];
         for (int ks = 1; ks < a.KS; ++ks) s += a.gpart[(long long)ks * nr + idx];
         X[idx] = s;
-        if (a.grad_out) a.grad_out[idx] = s;
       }
     }
   } else if (a.lds) {
     for (int idx = tid; idx < nr; idx += kQRThreads) X[idx] = a.Utmp[idx];
   }
   __syncthreads();
-  if (a.mode == QR_GD) {
-    const bool have = a.ctl ? (a.ctl->eta_set != 0) : (*a.eta_io > 0.0);
-    if (!have) {
-      block_gram(X, X, n, r, W, true);
-      if (tid == 0) {
-        const double lam = jacobi_max_eig(W, r);
-        const double eta = lam > 0.0 ? a.eta_c / sqrt(lam) : 0.0;
-        eta_s = eta;
-        if (a.ctl) {
-          a.ctl->eta = eta;
-          a.ctl->eta_set = 1;
-        } else {
-          *a.eta_io = eta;
-        }
-      }
-    } else if (tid == 0) {
-      eta_s = a.ctl ? a.ctl->eta : *a.eta_io;
-    }
-    __syncthreads();
-    const double eta = eta_s;
-    for (int idx = tid; idx < nr; idx += kQRThreads) X[idx] = (float)fma(-eta, (double)X[idx], (double)a.U[idx]);
-    __syncthreads();
-  }
   // CholeskyQR2.  A Gram that is not positive definite (a non-finite step, or a
-  // rank-deficient block) raises error bit 1 and leaves U as it was; a GD step
-  // still records the iteration below (its residual, the column flags, the count).
+  // rank-deficient block) raises error bit 1 and leaves U as it was.
   bool ok = block_cholqr_pass(X, n, r, sh, W, Lf, &okflag);
   if (ok) ok = block_cholqr_pass(X, n, r, sh, W, Lf, &okflag);
   if (!ok) {
     if (tid == 0 && a.ctl) atomicOr(&a.ctl->err, 2);
-    if (a.mode != QR_GD) return;
+    return;
   }
-  if (ok && a.mode == QR_POWER) {
+  if (a.mode == QR_POWER) {
     // subspace change ||U_new - U_old (U_old^T U_new)||_F, summed directly from the
     // residual entries (r - ||U_old^T U_new||_F^2 cancels below angles of ~3e-4 in FP32)
     block_gram(a.U, X, n, r, W, false);   // U_old^T U_new
@@ -346,52 +222,12 @@ __device__ __forceinline__ void qr_body(const QRArgs& a, unsigned char* dsm, QRS
       if (sd <= a.power_tol || (sd <= 1e-3 && prev > 0.0 && sd >= 0.99 * prev)) a.ctl->conv = 1;
     }
   }
-  for (int idx = tid; idx < nr; idx += kQRThreads) {
-    if (a.mode == QR_GD && a.Uprev) a.Uprev[idx] = a.U[idx];
-    if (ok) a.U[idx] = X[idx];
-  }
-  if (a.mode == QR_GD && a.ctl) {
-    double s = 0.0;
-    int fl = 0;
-    for (int k = tid; k < a.q; k += kQRThreads) {
-      s += a.colrr[k];
-      fl |= a.colflags[k];
-    }
-    sh[tid] = s;
-    __syncthreads();
-    for (int st = kQRThreads / 2; st > 0; st >>= 1) {
-      if (tid < st) sh[tid] += sh[tid + st];
-      __syncthreads();
-    }
-    if (fl) atomicOr(&a.ctl->err, fl);
-    if (tid == 0) {
-      const double resid = a.ctl->ynorm2 > 0.0 ? sqrt(sh[0] / a.ctl->ynorm2) : sqrt(sh[0]);
-      const int t = a.ctl->t;
-      if (a.rlog && t < a.rlog_len) a.rlog[t] = resid;
-      a.ctl->resid = resid;
-      a.ctl->t = t + 1;
-      // BF16X2 hi-only phase: switch to hi + lo when the residual stalls or the budget is spent
-      if (a.ctl->phase == 0 && (t + 1 >= a.hi_max || (t > 0 && resid >= a.stall * a.ctl->prev_resid))) {
-        a.ctl->phase = 1;
-        a.ctl->refine_t = t + 1;
-      }
-      a.ctl->prev_resid = resid;
-      if (a.gate_done && a.tol > 0.0 && resid <= a.tol) a.ctl->done = 1;
-    }
-  }
+  for (int idx = tid; idx < nr; idx += kQRThreads) a.U[idx] = X[idx];
 }
 
 __global__ __launch_bounds__(kQRThreads) void k_qr(QRArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dsm[];
   __shared__ QRShared S;
-  qr_body(a, dsm, S);
-}
-
-// Several problems in one launch: block b updates the U of problem b.
-__global__ __launch_bounds__(kQRThreads) void k_qr_grp(const QRArgs* tab) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char dsm[];
-  __shared__ QRShared S;
-  const QRArgs a = tab[blockIdx.x];
   qr_body(a, dsm, S);
 }
 
@@ -523,9 +359,6 @@ static hipError_t qr_allow_lds(size_t bytes) {
   if (done) return hipSuccess;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_qr), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)kQRLdsMax);
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_qr_grp), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kQRLdsMax);
   done = e == hipSuccess;
   return e;
 }
@@ -540,20 +373,6 @@ hipError_t launch_qr(const QRArgs& a_in, hipStream_t st) {
   }
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
   hipLaunchKernelGGL(k_qr, dim3(1), dim3(kQRThreads), a.lds ? bytes : 0, st, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_grad_grp(const GradArgs* tab, const int4* map, int blocks, hipStream_t st) {
-  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  hipLaunchKernelGGL(k_grad_grp, dim3(blocks), dim3(kGradWaves * 64), 0, st, tab, map);
-  return hipGetLastError();
-}
-
-hipError_t launch_qr_grp(const QRArgs* tab, int count, size_t lds, hipStream_t st) {
-  const hipError_t ea = qr_allow_lds(lds);
-  if (ea != hipSuccess) return ea;
-  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  hipLaunchKernelGGL(k_qr_grp, dim3(count), dim3(kQRThreads), lds, st, tab);
   return hipGetLastError();
 }
 

@@ -1,0 +1,461 @@
+// The U update of a GDmin iteration (Alg. 1) over many workgroups, for the real forms:
+// grad_U f = sum_k h_k b_k^T, eta at t = 1, U+ = QR(U - eta grad_U f) with a positive
+// diagonal R, the residual and the iteration's bookkeeping.  Two launches (three when
+// the columns are split for the gradient, see upd_splits in api.hip):
+//
+//  k_ugrad : a workgroup per 64 rows and column split: its part of grad;
+//  k_urows : a workgroup per 64 rows: the rows of grad, U_prev = U, and the block's part
+//            of the FP64 Gram matrix of X = U - eta grad;
+//  k_uapply: a row per thread: every workgroup adds the parts in order and factors the
+//            Gram (the same bits in each), then U = X R^{-1}; one more workgroup does
+//            the bookkeeping.
+//
+// What bounds it is latency: 4 MB of h_k at n = q = 1000, then a chain of small FP64
+// steps.  One 1024-thread workgroup for all of it after a gradient launch took 9 + 41
+// us there (12 us in all at n = q = 100, 18 + 1028 us at n = 16384, q = 100); workgroups
+// that hand over to the last one to arrive cost about 10 us per hand-over in cache
+// write-backs, more than a launch; these launches take 9 + 5 + 12 us there (12 and 28).
+// At t = 1, eta's eigenvalue took 0.4 ms by a cyclic Jacobi in one thread and takes
+// 20 us (wave_lambda_max).
+//
+// The factor comes from the FP64 Gram of the unrounded X, so one CholeskyQR pass gives
+// Q to FP32 rounding whenever cond(X)^2 2^-53 is far below it: a second pass is taken
+// only when the pivots span more than kPivotSpan (each workgroup then forms the Gram of
+// all the rounded rows itself: slow, and only for steps that nearly cancel U).
+#include "launch.h"
+#include "uside.h"
+
+namespace altg {
+
+constexpr int kURowsThreads = kGradWaves * 64;
+constexpr int kUApplyRows = 256;            // rows (threads) of a k_uapply workgroup
+constexpr double kPivotSpan = 1e-6;         // smallest / largest pivot for which one pass is enough
+enum { UPD_FROZEN = 0, UPD_STEP = 1, UPD_FIRST = 2 };
+
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int kUGradWaves = 4;              // waves of a column split's workgroup
+
+union URowsShared {
+  float red[kGradWaves / 2][64][kRMax + 1];
+  struct {
+    double X[64 * kRMax], Y[64 * kRMax];
+  } rows;
+};
+
+// Value of lane I of each 16-lane row, in every lane of the row.
+template <int I>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + I, 0xF, 0xF, false));
+}
+
+// acc[e][c] += h[e] * B[k][c], c < R, where lane c of each 16-lane row holds B[k][c].
+template <int R, int C = 0>
+__device__ __forceinline__ void rank1(float (&acc)[4][R], const float4& h, float b) {
+  if constexpr (C < R) {
+    const float bc = row_bcast<C>(b);
+    acc[0][C] = fmaf(h.x, bc, acc[0][C]);
+    acc[1][C] = fmaf(h.y, bc, acc[1][C]);
+    acc[2][C] = fmaf(h.z, bc, acc[2][C]);
+    acc[3][C] = fmaf(h.w, bc, acc[3][C]);
+    rank1<R, C + 1>(acc, h, b);
+  }
+}
+
+// Rows 64 jb .. + 63 of sum_k h_k b_k^T over the columns k0 <= k < k1, by a workgroup of
+// WV waves: thread i < 64 r gets row i / r, column i % r through put(i, value) (rows at
+// or beyond n are zero).  Quarter p = lane / 16 of wave w takes k = k0 + 4 w + p, then
+// every 4 WV-th, its lanes 4 rows each (16-byte loads, four 256-byte pieces of h_k per
+// wave); the quarters, then (above 8 waves) the waves w and w + 8, then the waves are
+// added in that order.  R: r rounded up to a multiple of 4.
+template <int R, int WV, class Put>
+__device__ __forceinline__ void urows_grad(const UpdArgs& a, int jb, int k0, int k1, float (*red)[64][kRMax + 1],
+                                           Put put) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+  const int n = a.n, r = a.r;
+  const int l = lane & 15, p = lane >> 4, j = jb * 64 + 4 * l;
+  const bool full = (jb + 1) * 64 <= n;
+  float acc[4][R];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int c = 0; c < R; ++c) acc[e][c] = 0.f;
+  constexpr int KU = 4;   // loads in flight per wave; the order of the k terms does not depend on it
+  for (int kb = k0 + 4 * wave; kb < k1; kb += 4 * WV * KU) {
+    float4 h[KU];
+    float bv[KU];
+#pragma unroll
+    for (int u = 0; u < KU; ++u) {
+      const int k = kb + p + u * 4 * WV;
+      const bool in = k < k1;
+      const float* row = a.H + (long long)(in ? k : k0) * n;
+      bv[u] = in && l < r ? a.B[(long long)k * r + l] : 0.f;
+      if (full) {
+        const f32x4_u v = *reinterpret_cast<const f32x4_u*>(row + j);
+        h[u] = make_float4(v.x, v.y, v.z, v.w);
+      } else {
+        h[u] = make_float4(j < n ? row[j] : 0.f, j + 1 < n ? row[j + 1] : 0.f, j + 2 < n ? row[j + 2] : 0.f,
+                           j + 3 < n ? row[j + 3] : 0.f);
+      }
+      if (!in) h[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int u = 0; u < KU; ++u) rank1<R>(acc, h[u], bv[u]);
+  }
+  // quarters: afterwards lane (p, l) holds row 4 l + p
+  float v[R];
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    float t[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = acc[e][c] + __shfl_xor(acc[e][c], 16);
+      t[e] = x + __shfl_xor(x, 32);
+    }
+    v[c] = p == 0 ? t[0] : (p == 1 ? t[1] : (p == 2 ? t[2] : t[3]));
+  }
+  constexpr int WS = WV > 8 ? 8 : WV;   // sums left after the first step
+  const int row = 4 * l + p;
+  if (wave >= WV - WS)
+#pragma unroll
+    for (int c = 0; c < R; ++c) red[wave - (WV - WS)][row][c] = v[c];
+  __syncthreads();
+  if constexpr (WV > 8) {
+    if (wave < WS)
+#pragma unroll
+      for (int c = 0; c < R; ++c) red[wave][row][c] += v[c];
+    __syncthreads();
+  }
+  for (int i = tid; i < 64 * r; i += 64 * WV) {
+    const int rw = i / r, c = i - rw * r;
+    float g = red[0][rw][c];
+#pragma unroll
+    for (int w = 1; w < WS; ++w) g += red[w][rw][c];
+    put(i, g);
+  }
+}
+
+template <int WV, class Put>
+__device__ __forceinline__ void urows_grad_r(const UpdArgs& a, int jb, int k0, int k1, float (*red)[64][kRMax + 1],
+                                             Put put) {
+  if (a.r <= 4) urows_grad<4, WV>(a, jb, k0, k1, red, put);
+  else if (a.r <= 8) urows_grad<8, WV>(a, jb, k0, k1, red, put);
+  else if (a.r <= 12) urows_grad<12, WV>(a, jb, k0, k1, red, put);
+  else urows_grad<16, WV>(a, jb, k0, k1, red, put);
+}
+
+// One column split of the gradient: rows of block jb over the columns of split ks.
+__device__ __forceinline__ void ugrad_body(const UpdArgs& a, int jb, int ks, float (*red)[64][kRMax + 1]) {
+  if (a.gate_done && a.ctl->done) return;
+  const int k0 = (int)((long long)a.q * ks / a.KS), k1 = (int)((long long)a.q * (ks + 1) / a.KS);
+  const long long nr = (long long)a.n * a.r, base = (long long)jb * 64 * a.r;
+  urows_grad_r<kUGradWaves>(a, jb, k0, k1, red, [&](int i, float g) {
+    if (base + i < nr) a.gpart[ks * nr + base + i] = g;
+  });
+}
+
+__global__ __launch_bounds__(64 * kUGradWaves) void k_ugrad(UpdArgs a) {
+  __shared__ float red[kUGradWaves][64][kRMax + 1];
+  ugrad_body(a, blockIdx.x, blockIdx.y, red);
+}
+
+// Several problems in one launch: block b is (problem, row block, split) = map[b].
+__global__ __launch_bounds__(64 * kUGradWaves) void k_ugrad_grp(const UpdArgs* tab, const int4* map) {
+  __shared__ float red[kUGradWaves][64][kRMax + 1];
+  const int4 mp = map[blockIdx.x];
+  const UpdArgs a = tab[mp.x];
+  ugrad_body(a, mp.y, mp.z, red);
+}
+
+// Part of X^T Y over the 64 rows in LDS (row-major, r wide): the upper triangle (a <= b)
+// row by row with sym, all r^2 entries without.
+__device__ __forceinline__ void rows_gram64(const double* X, const double* Y, int r, bool sym, double* dst) {
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int E = sym ? r * (r + 1) / 2 : r * r;
+  for (int e = wave; e < E; e += kGradWaves) {
+    int a = 0, b = 0;
+    if (sym) tri_entry(e, r, a, b);
+    else { a = e / r; b = e - a * r; }
+    const double s = wave_sum_dpp(X[lane * r + a] * Y[lane * r + b]);
+    if (lane == 0) dst[e] = s;
+  }
+}
+
+__device__ __forceinline__ void urows_body(const UpdArgs& a, int jb, URowsShared& S) {
+  const int tid = threadIdx.x;
+  const int n = a.n, r = a.r, E = r * (r + 1) / 2;
+  const bool have = a.ctl ? a.ctl->eta_set != 0 : *a.eta_io > 0.0;
+  if (jb == 0 && tid == 0) *a.upd = a.gate_done && a.ctl->done ? UPD_FROZEN : (have ? UPD_STEP : UPD_FIRST);
+  if (a.gate_done && a.ctl->done) return;
+  const double eta = have ? (a.ctl ? a.ctl->eta : *a.eta_io) : 0.0;
+  const long long base = (long long)jb * 64 * r, nr = (long long)n * r;
+  // thread i < 64 r: row i / r, column i % r (64 r <= kURowsThreads)
+  float g = 0.f;
+  if (a.H && a.KS == 1) {
+    urows_grad_r<kGradWaves>(a, jb, 0, a.q, S.red, [&](int, float v) { g = v; });
+    __syncthreads();   // S is free
+  }
+  if (tid < 64 * r) {
+    double x = 0.0, y = 0.0;
+    const long long i = base + tid;
+    if (i < nr) {
+      if (a.H && a.KS == 1) {
+        a.gpart[i] = g;
+      } else {          // given, or the column splits in order
+        float part[16];
+#pragma unroll
+        for (int s = 0; s < 16; ++s) part[s] = s < a.KS ? a.gpart[s * nr + i] : 0.f;
+        g = part[0];
+#pragma unroll
+        for (int s = 1; s < 16; ++s) g += part[s];
+        if (a.KS > 1) a.gpart[i] = g;
+      }
+      const float u = a.U[i];
+      a.Uprev[i] = u;
+      x = have ? fma(-eta, (double)g, (double)u) : (double)u;
+      y = (double)g;
+    }
+    S.rows.X[tid] = x;
+    S.rows.Y[tid] = y;
+  }
+  __syncthreads();
+  // eta known: the Gram of X; at t = 1: U^T U, G^T G and U^T G
+  double* dst = a.part + (long long)jb * (2 * E + r * r);
+  rows_gram64(S.rows.X, S.rows.X, r, true, dst);
+  if (!have) {
+    rows_gram64(S.rows.Y, S.rows.Y, r, true, dst + E);
+    rows_gram64(S.rows.X, S.rows.Y, r, false, dst + 2 * E);
+  }
+}
+
+__global__ __launch_bounds__(kURowsThreads) void k_urows(UpdArgs a) {
+  __shared__ URowsShared S;
+  urows_body(a, blockIdx.x, S);
+}
+
+// Several problems in one launch: block b is row block map[b].y of problem map[b].x.
+__global__ __launch_bounds__(kURowsThreads) void k_urows_grp(const UpdArgs* tab, const int2* map) {
+  __shared__ URowsShared S;
+  const int2 mp = map[blockIdx.x];
+  const UpdArgs a = tab[mp.x];
+  urows_body(a, mp.y, S);
+}
+
+constexpr int kUPartMax = 2 * (kRMax * (kRMax + 1) / 2) + kRMax * kRMax;   // values of a block's part
+
+struct UApplyShared {
+  double sum[kUPartMax > kUApplyRows ? kUPartMax : kUApplyRows];
+  double W[kUPartMax];
+  double A[2 * kRMax * kRMax];              // the matrix to factor (L afterwards), scratch
+  double rdiag[kRMax];
+  double eta;
+  int mode;                                 // 0: the Gram is not positive definite, 1 or 2 passes
+};
+
+// x <- x R^{-1} for one row, R^T = L (row-major r x r in LDS), by forward substitution.
+__device__ __forceinline__ void solve_row(double (&x)[kRMax], const double* L, const double* rdiag, int r) {
+#pragma unroll
+  for (int c = 0; c < kRMax; ++c) {
+    if (c < r) {
+      double t = x[c];
+#pragma unroll
+      for (int p = 0; p < kRMax; ++p)
+        if (p < c) t = fma(-x[p], L[c * r + p], t);
+      x[c] = t * rdiag[c];
+    }
+  }
+}
+
+// Workgroup jb < kUApplyRows-row blocks of n updates its rows; the one after them does the
+// bookkeeping.
+__device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShared& S) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+  const int n = a.n, r = a.r, rr = r * r, E = r * (r + 1) / 2, PE = 2 * E + rr, nb = (n + 63) / 64;
+  const int upd = *a.upd;
+  if (upd == UPD_FROZEN) return;
+  // this thread's row, loaded ahead of the factorisation
+  const int j = jb * kUApplyRows + tid;
+  const long long o = (long long)j * r;
+  float ru[kRMax], rg[kRMax];
+#pragma unroll
+  for (int c = 0; c < kRMax; ++c) {
+    ru[c] = c < r && j < n ? a.Uprev[o + c] : 0.f;
+    rg[c] = c < r && j < n ? a.gpart[o + c] : 0.f;
+  }
+  // the Gram parts: entry e over a contiguous range of blocks per group of threads,
+  // then the groups in order
+  const bool first = upd == UPD_FIRST;
+  const int used = first ? PE : E;
+  const int grp = kUApplyRows / used > 0 ? kUApplyRows / used : 1;
+  for (int e = tid; e < used * grp; e += kUApplyRows) {
+    const int g = e / used, en = e - g * used;
+    const int b0 = nb * g / grp, b1 = nb * (g + 1) / grp;
+    S.sum[e] = sum_strided(a.part + (long long)b0 * PE + en, PE, b1 - b0);
+  }
+  __syncthreads();
+  for (int e = tid; e < used; e += kUApplyRows) {
+    double s = S.sum[e];
+    for (int g = 1; g < grp; ++g) s += S.sum[g * used + e];
+    S.W[e] = s;
+  }
+  __syncthreads();
+  double* M = S.A;
+  if (wave == 0) {
+    double eta = first ? 0.0 : (a.ctl ? a.ctl->eta : *a.eta_io);
+    if (first) {
+      for (int e = lane; e < rr; e += 64) M[e] = S.W[E + tri_index(e / r, e % r, r)];
+      const double lam = wave_lambda_max(M, S.A + kRMax * kRMax, r);
+      eta = lam > 0.0 ? a.eta_c / sqrt(lam) : 0.0;
+      wave_lds_fence();
+      // X^T X = U^T U - eta (U^T G + G^T U) + eta^2 G^T G
+      for (int e = lane; e < rr; e += 64) {
+        const int i = e / r, jj = e % r, t = tri_index(i, jj, r);
+        M[e] = S.W[t] - eta * (S.W[2 * E + i * r + jj] + S.W[2 * E + jj * r + i]) + eta * eta * S.W[E + t];
+      }
+    } else {
+      for (int e = lane; e < rr; e += 64) M[e] = S.W[tri_index(e / r, e % r, r)];
+    }
+    double lo, hi;
+    const bool pd = wave_cholesky_span(M, S.rdiag, r, lo, hi);
+    if (lane == 0) {
+      S.eta = eta;
+      S.mode = !pd ? 0 : (lo >= kPivotSpan * hi ? 1 : 2);
+    }
+  }
+  __syncthreads();
+  const double eta = S.eta;
+  bool ok = S.mode != 0;
+  double x[kRMax];
+  if (ok && j < n) {
+#pragma unroll
+    for (int c = 0; c < kRMax; ++c)
+      if (c < r) x[c] = fma(-eta, (double)rg[c], (double)ru[c]);
+    solve_row(x, M, S.rdiag, r);
+  }
+  if (S.mode == 2) {   // an ill-conditioned X: once more on the rounded rows
+    for (int e = 0; e < E; ++e) {
+      int ra, rb;
+      tri_entry(e, r, ra, rb);
+      double s = 0.0;
+      for (int i = tid; i < n; i += kUApplyRows) {
+        const long long oi = (long long)i * r;
+        double y[kRMax];
+#pragma unroll
+        for (int c = 0; c < kRMax; ++c)
+          if (c < r) y[c] = fma(-eta, (double)a.gpart[oi + c], (double)a.Uprev[oi + c]);
+        solve_row(y, M, S.rdiag, r);
+        double ya = 0.0, yb = 0.0;
+#pragma unroll
+        for (int c = 0; c < kRMax; ++c) {
+          if (c == ra) ya = (double)(float)y[c];
+          if (c == rb) yb = (double)(float)y[c];
+        }
+        s = fma(ya, yb, s);
+      }
+      s = wave_sum_dpp(s);
+      if (lane == 0) S.sum[wave] = s;
+      __syncthreads();
+      if (tid == 0) S.W[e] = (S.sum[0] + S.sum[1]) + (S.sum[2] + S.sum[3]);
+      __syncthreads();
+    }
+    if (wave == 0) {
+      for (int e = lane; e < rr; e += 64) M[e] = S.W[tri_index(e / r, e % r, r)];
+      double lo, hi;
+      const bool pd = wave_cholesky_span(M, S.rdiag, r, lo, hi);
+      if (lane == 0) S.mode = pd ? 1 : 0;
+    }
+    __syncthreads();
+    ok = S.mode != 0;
+    if (ok && j < n) {
+#pragma unroll
+      for (int c = 0; c < kRMax; ++c)
+        if (c < r) x[c] = (double)(float)x[c];
+      solve_row(x, M, S.rdiag, r);
+    }
+  }
+  if (ok && j < n)
+#pragma unroll
+    for (int c = 0; c < kRMax; ++c)
+      if (c < r) a.U[o + c] = (float)x[c];
+  if (jb * kUApplyRows < n) return;
+  // the last workgroup (no rows): eta, then the residual of the iteration and the
+  // counters, recorded whether or not the factorisation failed
+  if (!a.ctl) {
+    if (first && tid == 0) *a.eta_io = eta;
+    return;
+  }
+  double s = 0.0;
+  int fl = 0;
+  for (int k = tid; k < a.q; k += kUApplyRows) {
+    s += a.colrr[k];
+    fl |= a.colflags[k];
+  }
+  if (fl) atomicOr(&a.ctl->err, fl);
+  s = wave_sum_dpp(s);
+  __syncthreads();   // S.sum is free
+  if (lane == 0) S.sum[wave] = s;
+  __syncthreads();
+  if (tid == 0) {
+    if (!ok) atomicOr(&a.ctl->err, 2);
+    if (first) {
+      a.ctl->eta = eta;
+      a.ctl->eta_set = 1;
+    }
+    record_iteration(a, (S.sum[0] + S.sum[1]) + (S.sum[2] + S.sum[3]));
+  }
+}
+
+__global__ __launch_bounds__(kUApplyRows) void k_uapply(UpdArgs a) {
+  __shared__ UApplyShared S;
+  uapply_body(a, blockIdx.x, S);
+}
+
+__global__ __launch_bounds__(kUApplyRows) void k_uapply_grp(const UpdArgs* tab, const int2* map) {
+  __shared__ UApplyShared S;
+  const int2 mp = map[blockIdx.x];
+  const UpdArgs a = tab[mp.x];
+  uapply_body(a, mp.y, S);
+}
+
+// ---------------------------------------------------------------- launchers
+
+size_t upd_part_doubles(int n, int r) { return (size_t)((n + 63) / 64) * (size_t)(r * (r + 1) + r * r); }
+int uapply_blocks(int n) { return (n + kUApplyRows - 1) / kUApplyRows + 1; }
+
+hipError_t launch_ugrad(const UpdArgs& a, hipStream_t st) {
+  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
+  hipLaunchKernelGGL(k_ugrad, dim3((a.n + 63) / 64, a.KS), dim3(64 * kUGradWaves), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_ugrad_grp(const UpdArgs* tab, const int4* map, int blocks, hipStream_t st) {
+  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
+  hipLaunchKernelGGL(k_ugrad_grp, dim3(blocks), dim3(64 * kUGradWaves), 0, st, tab, map);
+  return hipGetLastError();
+}
+
+hipError_t launch_urows(const UpdArgs& a, hipStream_t st) {
+  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
+  hipLaunchKernelGGL(k_urows, dim3((a.n + 63) / 64), dim3(kURowsThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_uapply(const UpdArgs& a, hipStream_t st) {
+  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
+  hipLaunchKernelGGL(k_uapply, dim3(uapply_blocks(a.n)), dim3(kUApplyRows), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_urows_grp(const UpdArgs* tab, const int2* map, int blocks, hipStream_t st) {
+  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
+  hipLaunchKernelGGL(k_urows_grp, dim3(blocks), dim3(kURowsThreads), 0, st, tab, map);
+  return hipGetLastError();
+}
+
+hipError_t launch_uapply_grp(const UpdArgs* tab, const int2* map, int blocks, hipStream_t st) {
+  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
+  hipLaunchKernelGGL(k_uapply_grp, dim3(blocks), dim3(kUApplyRows), 0, st, tab, map);
+  return hipGetLastError();
+}
+
+}  // namespace altg

@@ -7,25 +7,36 @@ namespace altg {
 enum { QR_GD = 0, QR_POWER = 1, QR_ORTH = 2 };
 
 struct QRArgs {
-  int n, r, KS, mode;
-  const float* gpart;      // KS x n x r partial sums (GD: gradient, POWER: L0 L0^T U)
+  int n, r, KS, mode;      // QR_POWER or QR_ORTH
+  const float* gpart;      // POWER: KS x n x r partial sums of L0 L0^T U
   float* U;                // n x r, in/out
-  float* Uprev;            // n x r, GD: receives the U the step started from
   float* Utmp;             // n x r scratch; ORTH: the block to orthonormalise
   Ctl* ctl;
-  double eta_c, power_tol;
-  const double* colrr;     // q residual norms^2 of the iteration (GD)
-  const int* colflags;     // q column flags (GD)
-  int q;
-  double* rlog;            // residual log (GD)
-  int rlog_len;
-  float* grad_out;         // optional copy of the summed partials
-  double* eta_io;          // op entry: eta in/out (<= 0: compute), used instead of ctl when ctl == nullptr
+  double power_tol;
   int lds;                 // set by launch_qr: the n x r block is staged in LDS
+};
+
+// The U update of a GDmin iteration (k_urows, k_uapply; with KS > 1, at most 16, k_ugrad before them).
+struct UpdArgs {
+  int n, q, r, KS;
+  const float* H;          // q x n; null: grad is given in gpart (KS = 1)
+  const float* B;          // q x r
+  float* gpart;            // n x r: grad; with KS > 1 the KS x n x r column splits, split 0 ends as grad
+  float* U;                // n x r, in/out
+  float* Uprev;            // n x r: receives the U the step started from
+  double* part;            // upd_part_doubles: Gram parts of the 64-row blocks
+  int* upd;                // what k_uapply is to do (set by k_urows)
+  Ctl* ctl;                // null: the entry point, with eta in eta_io (<= 0 on entry: computed)
+  double* eta_io;
+  double eta_c;
+  const double* colrr;     // q residual norms^2 of the iteration
+  const int* colflags;     // q column flags
+  double* rlog;            // residual log
+  int rlog_len;
   int hi_max;              // BF16X2 hi-only budget (iterations)
   double stall;            // BF16X2 stall ratio
-  double tol;              // GD with gate_done: set ctl->done once resid <= tol
-  int gate_done;           // GD: skip the update when ctl->done is set (batched stepping)
+  double tol;              // with gate_done: set ctl->done once resid <= tol
+  int gate_done;           // skip the update when ctl->done is set (batched stepping)
 };
 
 // dynamic LDS for the n x r block of k_qr (with its 10 KiB of static LDS, up to the
@@ -33,14 +44,6 @@ struct QRArgs {
 constexpr size_t kQRLdsMax = 144 * 1024;
 constexpr size_t kQRLdsDefault = 48 * 1024;
 constexpr int kGradWaves = 16;             // waves of a gradient-reduction workgroup
-
-struct GradArgs {
-  const float* H;
-  const float* B;
-  int n, q, r, KS;
-  float* gpart;
-  const int* skip;   // if non-null and *skip != 0, the workgroup does nothing
-};
 
 // pol: POL_STREAM (non-temporal loads of A) or POL_CACHED (ordinary loads; for a
 // streamed plane that fits in the Infinity Cache).  The same bits either way;
@@ -88,8 +91,14 @@ hipError_t launch_grad(const float* H, const float* B, int n, int q, int r, int 
 hipError_t launch_ltu(const float* L0t, const float* U, int n, int q, int r, float* T, const int* skip,
                       hipStream_t st);
 hipError_t launch_qr(const QRArgs& a, hipStream_t st);
-hipError_t launch_grad_grp(const GradArgs* tab, const int4* map, int blocks, hipStream_t st);
-hipError_t launch_qr_grp(const QRArgs* tab, int count, size_t lds, hipStream_t st);
+size_t upd_part_doubles(int n, int r);
+int uapply_blocks(int n);
+hipError_t launch_urows(const UpdArgs& a, hipStream_t st);
+hipError_t launch_uapply(const UpdArgs& a, hipStream_t st);
+hipError_t launch_urows_grp(const UpdArgs* tab, const int2* map, int blocks, hipStream_t st);
+hipError_t launch_ugrad(const UpdArgs& a, hipStream_t st);
+hipError_t launch_ugrad_grp(const UpdArgs* tab, const int4* map, int blocks, hipStream_t st);
+hipError_t launch_uapply_grp(const UpdArgs* tab, const int2* map, int blocks, hipStream_t st);
 hipError_t launch_sum_ctl(const double* colrr, int q, Ctl* ctl, hipStream_t st);
 hipError_t launch_reset_ctl(Ctl* ctl, int full, hipStream_t st);
 hipError_t launch_set_phase(Ctl* ctl, int phase, hipStream_t st);
