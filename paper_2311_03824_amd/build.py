@@ -28,6 +28,7 @@ SOURCES = [
     ("k_column.hip", ["-DALTG_PART=3"], "k_column_cached.o"),
     ("k_small.hip", [], "k_small.o"),
     ("k_update.hip", [], "k_update.o"),
+    ("k_subspace.hip", [], "k_subspace.o"),
     ("k_gen.hip", [], "k_gen.o"),
     ("k_fourier.hip", [], "k_fourier.o"),
     ("k_rank.hip", [], "k_rank.o"),

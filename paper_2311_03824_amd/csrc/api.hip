@@ -287,7 +287,7 @@ size_t carve(altgdmin_handle* h, void* base) {
   h->rlog_len = h->par.t_max > 0 ? h->par.t_max : 1;
   h->rlog = c.take<double>(h->rlog_len);
   h->colbound = c.take<float>(q);
-  h->upart = c.take<double>(upd_part_doubles(p.n, (int)r));
+  h->upart = c.take<double>(std::max(upd_part_doubles(p.n, (int)r), sub_part_doubles(p.n, (int)r)));
   h->upd = c.take<int>(1);
   if (p.r == 0) h->rank_ws = c.take<unsigned char>(rank_scratch(nullptr, rank_shape(p.n, p.q, p.m)).bytes);
   return (c.off + kAlign - 1) / kAlign * kAlign;
@@ -436,15 +436,6 @@ AUArgs gd_au_args(const altgdmin_handle* h, const float* U) {
   a.seed = p.a_seed; a.table = p.normal_table;
   a.waves = au_waves(p);
   a.bound = h->colbound;
-  return a;
-}
-
-QRArgs qr_args(const altgdmin_handle* h, int mode) {
-  QRArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.n = h->prob.n; a.r = h->prob.r; a.KS = h->KS; a.mode = mode;
-  a.gpart = h->gpart; a.U = h->U; a.Utmp = h->Utmp; a.ctl = h->ctl;
-  a.power_tol = h->par.power_tol;
   return a;
 }
 
@@ -903,12 +894,13 @@ int altgdmin_init(const altgdmin_problem* prob, const altgdmin_params* par, void
     e = launch_fill_basis(h->Utmp, p.n, p.r, st);
   }
   if (e != hipSuccess) return bail(e, "start block");
-  if ((e = launch_qr(qr_args(h, QR_ORTH), st)) != hipSuccess) return bail(e, "orth");
-  for (int it = 0; it < par->power_iters; ++it) {
-    if ((e = launch_ltu(h->H, h->U, p.n, p.q, p.r, h->Tpow, &h->ctl->conv, st)) != hipSuccess) return bail(e, "ltu");
-    if ((e = launch_grad(h->H, h->Tpow, p.n, p.q, p.r, h->KS, h->gpart, &h->ctl->conv, st)) != hipSuccess)
-      return bail(e, "power grad");
-    if ((e = launch_qr(qr_args(h, QR_POWER), st)) != hipSuccess) return bail(e, "power qr");
+  {
+    SubArgs sa;
+    std::memset(&sa, 0, sizeof(sa));
+    sa.L0t = h->H; sa.start = h->Utmp; sa.U = h->U; sa.V = h->Utmp; sa.T = h->Tpow; sa.gpart = h->gpart;
+    sa.part = h->upart; sa.n = p.n; sa.q = p.q; sa.r = p.r; sa.iters = par->power_iters;
+    sa.tol = par->power_tol; sa.ctl = h->ctl; sa.bar = &h->ctl->bar; sa.stuck = &h->ctl->stuck;
+    if ((e = launch_subspace(sa, h->KS, st)) != hipSuccess) return bail(e, "subspace");
   }
   if ((e = launch_reset_ctl(h->ctl, 0, st)) != hipSuccess) return bail(e, "reset eta");
   *out = h;
@@ -1595,7 +1587,7 @@ int altgdmin_op_measure(const altgdmin_problem* prob, const double* Xt, float* Y
 }
 
 // scratch layout of the U-side entry points: Ctl | gpart (KS n r) | Utmp (n r) | T (q r),
-// then what the U update of altgdmin_op_qr_step needs (base: the bytes without it)
+// (base), then the parts of the U update and the subspace iteration
 struct OpScratch {
   Ctl* ctl;
   float* gpart;
@@ -1616,7 +1608,7 @@ static OpScratch op_scratch(void* base, int n, int q, int r) {
   s.Utmp = c.take<float>((size_t)n * r);
   s.T = c.take<float>((size_t)q * r);
   s.base = c.off;
-  s.part = c.take<double>(upd_part_doubles(n, r));
+  s.part = c.take<double>(std::max(upd_part_doubles(n, r), sub_part_doubles(n, r)));
   s.upd = c.take<int>(1);
   s.bytes = c.off;
   return s;
@@ -1635,7 +1627,11 @@ int altgdmin_op_grad(const float* H, const float* Bt, int32_t n, int32_t q, int3
   OpScratch s = op_scratch(scratch, n, q, r);
   if (scratch_bytes < s.base) return fail(ALTGDMIN_ENOWS, "scratch too small");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  HIPCHK(launch_grad(H, Bt, n, q, r, s.KS, s.gpart, nullptr, st));
+  UpdArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.n = n; a.q = q; a.r = r; a.KS = s.KS;
+  a.H = H; a.B = Bt; a.gpart = s.gpart;
+  HIPCHK(launch_ugrad(a, st));
   HIPCHK(launch_sum_partials(s.gpart, s.KS, (long long)n * r, grad, st));
   return ALTGDMIN_OK;
 }
@@ -1669,23 +1665,17 @@ static int subspace_body(const float* L0t, int32_t n, int32_t q, int32_t r, cons
                          double tol, float* U_out, int32_t* iters_out, void* scratch, size_t scratch_bytes,
                          void* stream) {
   OpScratch s = op_scratch(scratch, n, q, r);
-  if (scratch_bytes < s.base) return fail(ALTGDMIN_ENOWS, "scratch too small");
+  if (scratch_bytes < s.bytes) return fail(ALTGDMIN_ENOWS, "scratch too small");
   hipStream_t st = static_cast<hipStream_t>(stream);
   HIPCHK(launch_reset_ctl(s.ctl, 1, st));
   if (U_start) HIPCHK(launch_copy_f(s.Utmp, U_start, (long long)n * r, st));
   else HIPCHK(launch_fill_basis(s.Utmp, n, r, st));
-  QRArgs a;
+  SubArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.n = n; a.r = r; a.KS = s.KS; a.gpart = s.gpart; a.U = U_out; a.Utmp = s.Utmp; a.ctl = s.ctl;
-  a.power_tol = tol;
-  a.mode = QR_ORTH;
-  HIPCHK(launch_qr(a, st));
-  a.mode = QR_POWER;
-  for (int it = 0; it < iters; ++it) {
-    HIPCHK(launch_ltu(L0t, U_out, n, q, r, s.T, &s.ctl->conv, st));
-    HIPCHK(launch_grad(L0t, s.T, n, q, r, s.KS, s.gpart, &s.ctl->conv, st));
-    HIPCHK(launch_qr(a, st));
-  }
+  a.L0t = L0t; a.start = s.Utmp; a.U = U_out; a.V = s.Utmp; a.T = s.T; a.gpart = s.gpart; a.part = s.part;
+  a.n = n; a.q = q; a.r = r; a.iters = iters; a.tol = tol;
+  a.ctl = s.ctl; a.bar = &s.ctl->bar; a.stuck = &s.ctl->stuck;
+  HIPCHK(launch_subspace(a, s.KS, st));
   if (iters_out) HIPCHK(hipMemcpyAsync(iters_out, &s.ctl->power_it, sizeof(int), hipMemcpyDeviceToDevice, st));
   return ALTGDMIN_OK;
 }
@@ -1747,7 +1737,12 @@ int altgdmin_op_rank(const float* L0t, int32_t n, int32_t q, int32_t m, double e
 // its device address is taken once per device with hipGetSymbolAddress and only
 // that address is handed to kernels and copies.
 
-static __device__ __align__(256) unsigned char scratch[ALTGDMIN_STATIC_SCRATCH_BYTES];
+// kStaticParts: room for the parts (beyond OpScratch::base) of any sizes whose base fits
+// in ALTGDMIN_STATIC_SCRATCH_BYTES: n r <= 2^21 there, so at most 8 (n / 64 + 1) (2 r^2 +
+// r + 1) <= 8.7e6 bytes (r = 16).
+
+constexpr size_t kStaticParts = 9u << 20;
+static __device__ __align__(256) unsigned char scratch[ALTGDMIN_STATIC_SCRATCH_BYTES + kStaticParts];
 
 namespace {
 
@@ -1787,7 +1782,7 @@ int altgdmin_op_subspace_noalloc(const float* L0t, int32_t n, int32_t q, int32_t
   void* p = nullptr;
   rc = static_scratch(&p);
   if (rc) return rc;
-  return subspace_body(L0t, n, q, r, U_start, iters, tol, U_out, iters_out, p, ALTGDMIN_STATIC_SCRATCH_BYTES, stream);
+  return subspace_body(L0t, n, q, r, U_start, iters, tol, U_out, iters_out, p, ALTGDMIN_STATIC_SCRATCH_BYTES + kStaticParts, stream);
 }
 
 }  // extern "C"

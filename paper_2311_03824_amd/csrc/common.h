@@ -37,7 +37,9 @@ struct Ctl {
   int phase;         // BF16X2 solves: 0 while the hi plane alone is read, 1 once hi + lo are read
   int refine_t;      // first iteration with phase 1 (-1 before)
   int done;          // batched stepping: the residual reached tol_resid; the problem is not advanced further
-  int pad[4];
+  int bar;           // subspace iteration: meeting counter of its workgroups
+  int stuck;         // subspace iteration: a workgroup gave up waiting
+  int pad[2];
   double prev_resid; // residual of the previous iteration (stall test of the hi-only phase)
 };
 

@@ -1,0 +1,337 @@
+// The spectral start of Alg. 1 for the real forms in one launch: orthonormalise the start
+// block, then subspace iteration Z = L_0 (L_0^T U), U = Q of Z (CholeskyQR, positive
+// diagonal), until ||U_new - U_old (U_old^T U_new)||_F meets the stop rule.
+//
+// A step is a chain of small dependent pieces (4 MB of L_0 twice at n = q = 1000, then
+// r x r algebra), and how many steps run is decided by the data.  As launches, each of up
+// to 100 steps took three (55 us a step at n = q = 1000, r = 10, most of it the one
+// workgroup that orthonormalised), and the ones after the stop still cost their launches
+// (1.7 us each, at the host's 4.6 us): 1400 us for 6 steps.  Here sub_blocks() workgroups
+// stay resident and meet at a counter between the pieces (2.6 us for 32 workgroups, 3.3
+// for 64), and the loop ends when the rule fires: 59 us a step, 360 us in all; 20 us a
+// step at n = q = 100.
+//
+// Residency: at most kSubBlocksMax workgroups of 4 waves and about 240 registers, two to a
+// CU: 512 fit the chip, so four launches at once (a process has four hardware queues)
+// all become resident as soon as other kernels drain; none can hold what another waits
+// for.  A wait is bounded all the same: a workgroup that gives up raises *stuck, which
+// ends every other one too (error bit 1).  Rows are dealt to workgroups in a fixed way
+// and every sum runs in a fixed order, so results do not depend on timing.
+#include "launch.h"
+#include "uside.h"
+
+namespace altg {
+
+namespace {
+
+constexpr int kSubThreads = 256, kSubWaves = kSubThreads / 64;
+constexpr int kSubBlocksMax = 96;
+constexpr int kSpinMax = 1 << 26;           // polls before a wait gives up (tens of seconds)
+
+struct SubShared {
+  union {
+    float red[kSubWaves][64][kRMax + 1];
+    struct {
+      double X[64 * kRMax], Y[64 * kRMax];
+    } rows;
+    double sum[kSubThreads];
+  };
+  double M[kRMax * kRMax];                  // the factor, or U_old^T U_new
+  double rdiag[kRMax];
+  double val[2];
+  int flag;
+};
+
+// Part layout of a 64-row unit (doubles): Gram of Z | U_old^T U_new | Gram of U_new | change
+__device__ __forceinline__ int part_stride(int r) { return r * (r + 1) + r * r + 1; }
+
+// Sum of `cnt` entries (offset off) over the parts of all units, into dst (LDS); entry e
+// over a contiguous range of units per group of threads, then the groups in order.
+__device__ __forceinline__ void sum_parts(const SubArgs& a, int off, int cnt, SubShared& S, double* dst, int units) {
+  const int tid = threadIdx.x, ps = part_stride(a.r);
+  const int grp = sum_groups(kSubThreads, cnt, units);
+  __syncthreads();
+  for (int e = tid; e < cnt * grp; e += kSubThreads) {
+    const int g = e / cnt, en = e - g * cnt;
+    const int b0 = units * g / grp, b1 = units * (g + 1) / grp;
+    S.sum[e] = sum_strided(a.part + (long long)b0 * ps + off + en, ps, b1 - b0);
+  }
+  __syncthreads();
+  for (int e = tid; e < cnt; e += kSubThreads) {
+    double s = S.sum[e];
+    for (int g = 1; g < grp; ++g) s += S.sum[g * cnt + e];
+    dst[e] = s;
+  }
+  __syncthreads();
+}
+
+}  // namespace
+
+__global__ __launch_bounds__(kSubThreads) void k_subspace(SubArgs a) {
+  __shared__ SubShared S;
+  __shared__ double tri[kRMax * (kRMax + 1) / 2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), nblk = gridDim.x;
+  const int n = a.n, q = a.q, r = a.r, rr = r * r, E = r * (r + 1) / 2, KS = a.KS;
+  const int units = (n + 63) / 64, ps = part_stride(r);
+  const long long nr = (long long)n * r;
+  int target = 0;
+  bool dead = false;
+
+  // every workgroup's earlier writes are visible to all after it
+  auto meet = [&]() {
+    __syncthreads();
+    if (nblk > 1) {
+      target += nblk;
+      if (tid == 0) {
+        int give_up = 0;
+        __hip_atomic_fetch_add(a.bar, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        for (int spin = 0; __hip_atomic_load(a.bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target; ++spin) {
+          if (spin >= kSpinMax || __hip_atomic_load(a.stuck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            __hip_atomic_store(a.stuck, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            give_up = 1;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        S.flag = give_up;
+      }
+      __syncthreads();
+      dead = dead || S.flag != 0;
+      __syncthreads();
+    }
+  };
+
+  // dst = Q of the thin QR of z (rows of z already in place: summed over `splits` splits,
+  // which end in split 0); with old, also the parts of old^T dst.  False if z is rank
+  // deficient.  Ends with every workgroup's rows of dst and parts visible.
+  auto orth = [&](float* z, int splits, float* dst, const float* old) -> bool {
+    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+      __syncthreads();
+      const long long base = (long long)ru * 64 * r;
+      for (int i = tid; i < 64 * r; i += kSubThreads) {
+        float x = 0.f;
+        if (base + i < nr) {
+          x = z[base + i];
+          for (int s = 1; s < splits; ++s) x += z[s * nr + base + i];
+          if (splits > 1) z[base + i] = x;
+        }
+        S.rows.X[i] = (double)x;
+      }
+      __syncthreads();
+      rows_gram64<kSubWaves>(S.rows.X, S.rows.X, r, true, a.part + (long long)ru * ps);
+    }
+    meet();
+    if (dead) return false;
+    for (int pass = 0; pass < 2; ++pass) {
+      sum_parts(a, pass == 0 ? 0 : E + rr, E, S, tri, units);
+      if (wave == 0) {
+        for (int e = lane; e < rr; e += 64) S.M[e] = tri[tri_index(e / r, e % r, r)];
+        double lo, hi;
+        const bool pd = wave_cholesky_span(S.M, S.rdiag, r, lo, hi);
+        if (lane == 0) S.flag = !pd ? 0 : (lo >= kPivotSpan * hi ? 1 : 2);
+      }
+      __syncthreads();
+      const int mode = S.flag;
+      if (mode == 0) return false;
+      const bool again = pass == 0 && mode == 2;   // ill-conditioned: once more on the rounded rows
+      const float* src = pass == 0 ? z : dst;
+      for (int ru = blockIdx.x; ru < units; ru += nblk) {
+        const int j = ru * 64 + tid;
+        const long long o = (long long)j * r;
+        if (tid < 64) {
+          double x[kRMax];
+#pragma unroll
+          for (int c = 0; c < kRMax; ++c)
+            if (c < r) x[c] = j < n ? (double)src[o + c] : 0.0;
+          solve_row(x, S.M, S.rdiag, r);
+#pragma unroll
+          for (int c = 0; c < kRMax; ++c)
+            if (c < r) {
+              const float v = (float)x[c];
+              if (j < n) dst[o + c] = v;
+              S.rows.X[tid * r + c] = (double)v;
+            }
+        }
+        if (old)
+          for (int i = tid; i < 64 * r; i += kSubThreads)
+            S.rows.Y[i] = (long long)ru * 64 * r + i < nr ? (double)old[(long long)ru * 64 * r + i] : 0.0;
+        __syncthreads();
+        double* pt = a.part + (long long)ru * ps;
+        if (again) rows_gram64<kSubWaves>(S.rows.X, S.rows.X, r, true, pt + E + rr);
+        else if (old) rows_gram64<kSubWaves>(S.rows.Y, S.rows.X, r, false, pt + E);
+        __syncthreads();
+      }
+      meet();
+      if (dead) return false;
+      if (!again) break;
+    }
+    return true;
+  };
+
+  // the change of the last step, from the units' parts in order, and the stop rule
+  double prev = 0.0;
+  auto decide = [&]() -> bool {
+    sum_parts(a, ps - 1, 1, S, S.val, units);
+    const double sd = sqrt(S.val[0]);
+    // converged at tol, or once the change has stopped shrinking below 1e-3 (by less
+    // than 1 % in a step): the FP32 iterate's rounding floor.  A change that still
+    // shrinks by a steady factor above 0.9 is a slow iteration, not the floor.
+    const bool conv = sd <= a.tol || (sd <= 1e-3 && prev > 0.0 && sd >= 0.99 * prev);
+    if (blockIdx.x == 0 && tid == 0) {
+      a.ctl->power_sd = sd;
+      a.ctl->power_it += 1;
+      if (conv) a.ctl->conv = 1;
+    }
+    prev = sd;
+    return conv;
+  };
+
+  float* cur = a.U;
+  float* nxt = a.V;
+  bool ok = orth(a.start, 1, cur, nullptr);
+  bool pending = false;
+  for (int p = 0; ok && p < a.iters; ++p) {
+    // T = L_0^T U on the matrix cores, 16 columns k by r per workgroup, the rows j split
+    // over its waves 16 at a time: lane (i, p) holds 4 rows of column i, and the four
+    // products of a group take row 4 p + e of it, e = 0..3, for both operands.
+    for (int k0 = blockIdx.x * 16; k0 < q; k0 += nblk * 16) {
+      typedef float f32x4 __attribute__((ext_vector_type(4)));
+      const int i = lane & 15, p4 = 4 * (lane >> 4);
+      const float* row = a.L0t + (long long)(k0 + i < q ? k0 + i : q - 1) * n;
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+      constexpr int SU = 4;   // 16-row groups in flight per wave
+      for (int s0 = wave * 16; s0 < n; s0 += kSubWaves * 16 * SU) {
+        float x[SU][4], u[SU][4];
+#pragma unroll
+        for (int g = 0; g < SU; ++g) {
+          const int j = s0 + g * kSubWaves * 16 + p4;
+          if (j + 4 <= n) {
+            const f32x4_u v = *reinterpret_cast<const f32x4_u*>(row + j);
+            x[g][0] = v.x; x[g][1] = v.y; x[g][2] = v.z; x[g][3] = v.w;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[g][e] = j + e < n ? row[j + e] : 0.f;
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) u[g][e] = i < r && j + e < n ? cur[(long long)(j + e) * r + i] : 0.f;
+        }
+#pragma unroll
+        for (int g = 0; g < SU; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[g][e], u[g][e], acc, 0, 0, 0);
+      }
+      // lane (i, p) holds column i of rows 4 p .. 4 p + 3 of the 16 x 16 result
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 4; ++e) S.red[wave][p4 + e][i] = acc[e];
+      __syncthreads();
+      for (int t = tid; t < 16 * r; t += kSubThreads) {
+        const int kk = t / r, c = t - kk * r;
+        float v = S.red[0][kk][c];
+#pragma unroll
+        for (int w = 1; w < kSubWaves; ++w) v += S.red[w][kk][c];
+        if (k0 + kk < q) a.T[(long long)(k0 + kk) * r + c] = v;
+      }
+    }
+    meet();
+    if (dead) break;
+    if (pending) {
+      pending = false;
+      if (decide()) break;
+    }
+    // Z = L_0 T by 64-row units and column splits
+    for (int w = blockIdx.x; w < units * KS; w += nblk) {
+      const int ru = KS == 1 ? w : w / KS, ks = w - ru * KS;
+      const int k0 = (int)((long long)q * ks / KS), k1 = (int)((long long)q * (ks + 1) / KS);
+      const long long base = (long long)ru * 64 * r;
+      __syncthreads();
+      urows_grad_r<kSubWaves>(a.L0t, a.T, n, r, ru, k0, k1, S.red, [&](int i, float g) {
+        if (base + i < nr) a.gpart[ks * nr + base + i] = g;
+      });
+    }
+    if (KS > 1) {
+      meet();
+      if (dead) break;
+    }
+    __syncthreads();
+    ok = orth(a.gpart, KS, nxt, cur);
+    if (!ok) break;
+    // the change ||U_new - U_old W||_F of this workgroup's rows, W = U_old^T U_new,
+    // summed directly from the residual entries; decided after the next meeting
+    sum_parts(a, E, rr, S, S.M, units);
+    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+      if (wave == 0) {
+        const int j = ru * 64 + lane;
+        const long long o = (long long)j * r;
+        double acc = 0.0;
+        if (j < n) {
+          float u[kRMax], v[kRMax];
+#pragma unroll
+          for (int e = 0; e < kRMax; ++e) {
+            u[e] = e < r ? cur[o + e] : 0.f;
+            v[e] = e < r ? nxt[o + e] : 0.f;
+          }
+#pragma unroll
+          for (int c = 0; c < kRMax; ++c)
+            if (c < r) {
+              double d = (double)v[c];
+#pragma unroll
+              for (int e = 0; e < kRMax; ++e)
+                if (e < r) d = fma(-(double)u[e], S.M[e * r + c], d);
+              acc = fma(d, d, acc);
+            }
+        }
+        acc = wave_sum_dpp(acc);
+        if (lane == 0) a.part[(long long)ru * ps + ps - 1] = acc;
+      }
+    }
+    __syncthreads();
+    pending = true;
+    float* x = cur;
+    cur = nxt;
+    nxt = x;
+  }
+  if (!dead && pending) {   // the step limit: record the last change (after a failed step, the one before)
+    meet();
+    if (!dead) decide();
+  }
+  if ((dead || !ok) && blockIdx.x == 0 && tid == 0) atomicOr(&a.ctl->err, 2);
+  if (cur != a.U)           // this workgroup's rows, read by no other one any more
+    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+      const long long base = (long long)ru * 64 * r;
+      for (int i = tid; i < 64 * r; i += kSubThreads)
+        if (base + i < nr) a.U[base + i] = cur[base + i];
+    }
+}
+
+// ---------------------------------------------------------------- launcher
+
+size_t sub_part_doubles(int n, int r) { return (size_t)((n + 63) / 64) * (size_t)(r * (r + 1) + r * r + 1); }
+
+// Workgroups: as many as have 16 columns for L_0^T U or rows of their own, at most
+// kSubBlocksMax.
+static int sub_blocks(int n, int q) {
+  const int cols = (q + 15) / 16, rows = (n + 63) / 64;
+  const int b = cols > rows ? cols : rows;
+  return b < kSubBlocksMax ? b : kSubBlocksMax;
+}
+
+// Column splits of Z: a 64-row unit per workgroup with at least 32 columns each, at most
+// max_splits (the buffers).
+static int sub_splits(int n, int q, int max_splits) {
+  int ks = sub_blocks(n, q) / ((n + 63) / 64);
+  if (ks > q / 32) ks = q / 32;
+  if (ks > max_splits) ks = max_splits;
+  return ks < 1 ? 1 : ks;
+}
+
+hipError_t launch_subspace(const SubArgs& a_in, int max_splits, hipStream_t st) {
+  SubArgs a = a_in;
+  a.KS = sub_splits(a.n, a.q, max_splits);
+  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
+  hipLaunchKernelGGL(k_subspace, dim3(sub_blocks(a.n, a.q)), dim3(kSubThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace altg

@@ -29,10 +29,7 @@ namespace altg {
 
 constexpr int kURowsThreads = kGradWaves * 64;
 constexpr int kUApplyRows = 256;            // rows (threads) of a k_uapply workgroup
-constexpr double kPivotSpan = 1e-6;         // smallest / largest pivot for which one pass is enough
 enum { UPD_FROZEN = 0, UPD_STEP = 1, UPD_FIRST = 2 };
-
-typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kUGradWaves = 4;              // waves of a column split's workgroup
 
@@ -43,113 +40,12 @@ union URowsShared {
   } rows;
 };
 
-// Value of lane I of each 16-lane row, in every lane of the row.
-template <int I>
-__device__ __forceinline__ float row_bcast(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + I, 0xF, 0xF, false));
-}
-
-// acc[e][c] += h[e] * B[k][c], c < R, where lane c of each 16-lane row holds B[k][c].
-template <int R, int C = 0>
-__device__ __forceinline__ void rank1(float (&acc)[4][R], const float4& h, float b) {
-  if constexpr (C < R) {
-    const float bc = row_bcast<C>(b);
-    acc[0][C] = fmaf(h.x, bc, acc[0][C]);
-    acc[1][C] = fmaf(h.y, bc, acc[1][C]);
-    acc[2][C] = fmaf(h.z, bc, acc[2][C]);
-    acc[3][C] = fmaf(h.w, bc, acc[3][C]);
-    rank1<R, C + 1>(acc, h, b);
-  }
-}
-
-// Rows 64 jb .. + 63 of sum_k h_k b_k^T over the columns k0 <= k < k1, by a workgroup of
-// WV waves: thread i < 64 r gets row i / r, column i % r through put(i, value) (rows at
-// or beyond n are zero).  Quarter p = lane / 16 of wave w takes k = k0 + 4 w + p, then
-// every 4 WV-th, its lanes 4 rows each (16-byte loads, four 256-byte pieces of h_k per
-// wave); the quarters, then (above 8 waves) the waves w and w + 8, then the waves are
-// added in that order.  R: r rounded up to a multiple of 4.
-template <int R, int WV, class Put>
-__device__ __forceinline__ void urows_grad(const UpdArgs& a, int jb, int k0, int k1, float (*red)[64][kRMax + 1],
-                                           Put put) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-  const int n = a.n, r = a.r;
-  const int l = lane & 15, p = lane >> 4, j = jb * 64 + 4 * l;
-  const bool full = (jb + 1) * 64 <= n;
-  float acc[4][R];
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-#pragma unroll
-    for (int c = 0; c < R; ++c) acc[e][c] = 0.f;
-  constexpr int KU = 4;   // loads in flight per wave; the order of the k terms does not depend on it
-  for (int kb = k0 + 4 * wave; kb < k1; kb += 4 * WV * KU) {
-    float4 h[KU];
-    float bv[KU];
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int k = kb + p + u * 4 * WV;
-      const bool in = k < k1;
-      const float* row = a.H + (long long)(in ? k : k0) * n;
-      bv[u] = in && l < r ? a.B[(long long)k * r + l] : 0.f;
-      if (full) {
-        const f32x4_u v = *reinterpret_cast<const f32x4_u*>(row + j);
-        h[u] = make_float4(v.x, v.y, v.z, v.w);
-      } else {
-        h[u] = make_float4(j < n ? row[j] : 0.f, j + 1 < n ? row[j + 1] : 0.f, j + 2 < n ? row[j + 2] : 0.f,
-                           j + 3 < n ? row[j + 3] : 0.f);
-      }
-      if (!in) h[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int u = 0; u < KU; ++u) rank1<R>(acc, h[u], bv[u]);
-  }
-  // quarters: afterwards lane (p, l) holds row 4 l + p
-  float v[R];
-#pragma unroll
-  for (int c = 0; c < R; ++c) {
-    float t[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float x = acc[e][c] + __shfl_xor(acc[e][c], 16);
-      t[e] = x + __shfl_xor(x, 32);
-    }
-    v[c] = p == 0 ? t[0] : (p == 1 ? t[1] : (p == 2 ? t[2] : t[3]));
-  }
-  constexpr int WS = WV > 8 ? 8 : WV;   // sums left after the first step
-  const int row = 4 * l + p;
-  if (wave >= WV - WS)
-#pragma unroll
-    for (int c = 0; c < R; ++c) red[wave - (WV - WS)][row][c] = v[c];
-  __syncthreads();
-  if constexpr (WV > 8) {
-    if (wave < WS)
-#pragma unroll
-      for (int c = 0; c < R; ++c) red[wave][row][c] += v[c];
-    __syncthreads();
-  }
-  for (int i = tid; i < 64 * r; i += 64 * WV) {
-    const int rw = i / r, c = i - rw * r;
-    float g = red[0][rw][c];
-#pragma unroll
-    for (int w = 1; w < WS; ++w) g += red[w][rw][c];
-    put(i, g);
-  }
-}
-
-template <int WV, class Put>
-__device__ __forceinline__ void urows_grad_r(const UpdArgs& a, int jb, int k0, int k1, float (*red)[64][kRMax + 1],
-                                             Put put) {
-  if (a.r <= 4) urows_grad<4, WV>(a, jb, k0, k1, red, put);
-  else if (a.r <= 8) urows_grad<8, WV>(a, jb, k0, k1, red, put);
-  else if (a.r <= 12) urows_grad<12, WV>(a, jb, k0, k1, red, put);
-  else urows_grad<16, WV>(a, jb, k0, k1, red, put);
-}
-
 // One column split of the gradient: rows of block jb over the columns of split ks.
 __device__ __forceinline__ void ugrad_body(const UpdArgs& a, int jb, int ks, float (*red)[64][kRMax + 1]) {
   if (a.gate_done && a.ctl->done) return;
   const int k0 = (int)((long long)a.q * ks / a.KS), k1 = (int)((long long)a.q * (ks + 1) / a.KS);
   const long long nr = (long long)a.n * a.r, base = (long long)jb * 64 * a.r;
-  urows_grad_r<kUGradWaves>(a, jb, k0, k1, red, [&](int i, float g) {
+  urows_grad_r<kUGradWaves>(a.H, a.B, a.n, a.r, jb, k0, k1, red, [&](int i, float g) {
     if (base + i < nr) a.gpart[ks * nr + base + i] = g;
   });
 }
@@ -167,20 +63,6 @@ __global__ __launch_bounds__(64 * kUGradWaves) void k_ugrad_grp(const UpdArgs* t
   ugrad_body(a, mp.y, mp.z, red);
 }
 
-// Part of X^T Y over the 64 rows in LDS (row-major, r wide): the upper triangle (a <= b)
-// row by row with sym, all r^2 entries without.
-__device__ __forceinline__ void rows_gram64(const double* X, const double* Y, int r, bool sym, double* dst) {
-  const int lane = threadIdx.x & 63, wave = wave_id();
-  const int E = sym ? r * (r + 1) / 2 : r * r;
-  for (int e = wave; e < E; e += kGradWaves) {
-    int a = 0, b = 0;
-    if (sym) tri_entry(e, r, a, b);
-    else { a = e / r; b = e - a * r; }
-    const double s = wave_sum_dpp(X[lane * r + a] * Y[lane * r + b]);
-    if (lane == 0) dst[e] = s;
-  }
-}
-
 __device__ __forceinline__ void urows_body(const UpdArgs& a, int jb, URowsShared& S) {
   const int tid = threadIdx.x;
   const int n = a.n, r = a.r, E = r * (r + 1) / 2;
@@ -192,7 +74,7 @@ __device__ __forceinline__ void urows_body(const UpdArgs& a, int jb, URowsShared
   // thread i < 64 r: row i / r, column i % r (64 r <= kURowsThreads)
   float g = 0.f;
   if (a.H && a.KS == 1) {
-    urows_grad_r<kGradWaves>(a, jb, 0, a.q, S.red, [&](int, float v) { g = v; });
+    urows_grad_r<kGradWaves>(a.H, a.B, n, r, jb, 0, a.q, S.red, [&](int, float v) { g = v; });
     __syncthreads();   // S is free
   }
   if (tid < 64 * r) {
@@ -221,10 +103,10 @@ __device__ __forceinline__ void urows_body(const UpdArgs& a, int jb, URowsShared
   __syncthreads();
   // eta known: the Gram of X; at t = 1: U^T U, G^T G and U^T G
   double* dst = a.part + (long long)jb * (2 * E + r * r);
-  rows_gram64(S.rows.X, S.rows.X, r, true, dst);
+  rows_gram64<kGradWaves>(S.rows.X, S.rows.X, r, true, dst);
   if (!have) {
-    rows_gram64(S.rows.Y, S.rows.Y, r, true, dst + E);
-    rows_gram64(S.rows.X, S.rows.Y, r, false, dst + 2 * E);
+    rows_gram64<kGradWaves>(S.rows.Y, S.rows.Y, r, true, dst + E);
+    rows_gram64<kGradWaves>(S.rows.X, S.rows.Y, r, false, dst + 2 * E);
   }
 }
 
@@ -252,20 +134,6 @@ struct UApplyShared {
   int mode;                                 // 0: the Gram is not positive definite, 1 or 2 passes
 };
 
-// x <- x R^{-1} for one row, R^T = L (row-major r x r in LDS), by forward substitution.
-__device__ __forceinline__ void solve_row(double (&x)[kRMax], const double* L, const double* rdiag, int r) {
-#pragma unroll
-  for (int c = 0; c < kRMax; ++c) {
-    if (c < r) {
-      double t = x[c];
-#pragma unroll
-      for (int p = 0; p < kRMax; ++p)
-        if (p < c) t = fma(-x[p], L[c * r + p], t);
-      x[c] = t * rdiag[c];
-    }
-  }
-}
-
 // Workgroup jb < kUApplyRows-row blocks of n updates its rows; the one after them does the
 // bookkeeping.
 __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShared& S) {
@@ -286,7 +154,7 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
   // then the groups in order
   const bool first = upd == UPD_FIRST;
   const int used = first ? PE : E;
-  const int grp = kUApplyRows / used > 0 ? kUApplyRows / used : 1;
+  const int grp = sum_groups(kUApplyRows, used, nb);
   for (int e = tid; e < used * grp; e += kUApplyRows) {
     const int g = e / used, en = e - g * used;
     const int b0 = nb * g / grp, b1 = nb * (g + 1) / grp;

@@ -6,16 +6,6 @@ namespace altg {
 
 enum { QR_GD = 0, QR_POWER = 1, QR_ORTH = 2 };
 
-struct QRArgs {
-  int n, r, KS, mode;      // QR_POWER or QR_ORTH
-  const float* gpart;      // POWER: KS x n x r partial sums of L0 L0^T U
-  float* U;                // n x r, in/out
-  float* Utmp;             // n x r scratch; ORTH: the block to orthonormalise
-  Ctl* ctl;
-  double power_tol;
-  int lds;                 // set by launch_qr: the n x r block is staged in LDS
-};
-
 // The U update of a GDmin iteration (k_urows, k_uapply; with KS > 1, at most 16, k_ugrad before them).
 struct UpdArgs {
   int n, q, r, KS;
@@ -39,11 +29,23 @@ struct UpdArgs {
   int gate_done;           // skip the update when ctl->done is set (batched stepping)
 };
 
-// dynamic LDS for the n x r block of k_qr (with its 10 KiB of static LDS, up to the
-// CU's 160 KiB; above the default 48 KiB the kernels' limit is raised on first use)
-constexpr size_t kQRLdsMax = 144 * 1024;
-constexpr size_t kQRLdsDefault = 48 * 1024;
-constexpr int kGradWaves = 16;             // waves of a gradient-reduction workgroup
+// The spectral start in one launch (k_subspace).
+struct SubArgs {
+  const float* L0t;        // q x n
+  float* start;            // n x r: the block to orthonormalise
+  float* U;                // n x r: the result
+  float* V;                // n x r scratch (the other iterate; may be start)
+  float* T;                // q x r scratch
+  float* gpart;            // KS x n x r scratch
+  double* part;            // sub_part_doubles
+  int n, q, r, KS, iters;  // KS: set by launch_subspace; iters = 0: the orthonormal block only
+  double tol;
+  Ctl* ctl;                // power_sd, power_it, conv, err
+  int* bar;                // meeting counter and the give-up flag: zero at launch (launch_reset_ctl)
+  int* stuck;
+};
+
+constexpr int kGradWaves = 16;             // waves of a k_urows workgroup
 
 // pol: POL_STREAM (non-temporal loads of A) or POL_CACHED (ordinary loads; for a
 // streamed plane that fits in the Infinity Cache).  The same bits either way;
@@ -86,13 +88,10 @@ size_t select_lds_bytes(int n, int rho);
 hipError_t launch_select(const float* V, int n, int count, long long ldv, int rho, int* idx, float* val,
                          int* flags, hipStream_t st);
 hipError_t launch_sum_partials(const float* gpart, int KS, long long nr, float* out, hipStream_t st);
-hipError_t launch_grad(const float* H, const float* B, int n, int q, int r, int KS, float* gpart,
-                       const int* skip, hipStream_t st);
-hipError_t launch_ltu(const float* L0t, const float* U, int n, int q, int r, float* T, const int* skip,
-                      hipStream_t st);
-hipError_t launch_qr(const QRArgs& a, hipStream_t st);
 size_t upd_part_doubles(int n, int r);
 int uapply_blocks(int n);
+size_t sub_part_doubles(int n, int r);
+hipError_t launch_subspace(const SubArgs& a, int max_splits, hipStream_t st);
 hipError_t launch_urows(const UpdArgs& a, hipStream_t st);
 hipError_t launch_uapply(const UpdArgs& a, hipStream_t st);
 hipError_t launch_urows_grp(const UpdArgs* tab, const int2* map, int blocks, hipStream_t st);

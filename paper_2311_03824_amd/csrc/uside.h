@@ -6,54 +6,6 @@
 
 namespace altg {
 
-// One workgroup of 16 waves per block of 64 rows j; wave w sums the columns
-// k = w, w + 16, ... of its split; the 16 wave partials are added in a fixed
-// pairwise order.  Row k of B is fetched by lanes 0..r-1 with one vector load
-// and broadcast with readlane, so that loads of later columns stay in flight.
-__device__ __forceinline__ void grad_body(const float* __restrict__ H, const float* __restrict__ B, int n, int q, int r,
-                                          int KS, float* __restrict__ gpart, int jblock, int ks,
-                                          float (*red)[64][kRMax + 1]) {
-  const int lane = threadIdx.x & 63, ph = wave_id();
-  const int j = jblock * 64 + lane;
-  const int jc = j < n ? j : n - 1;
-  const int k0 = (int)((long long)q * ks / KS), k1 = (int)((long long)q * (ks + 1) / KS);
-  float acc[kRMax];
-#pragma unroll
-  for (int c = 0; c < kRMax; ++c) acc[c] = 0.f;
-  constexpr int KU = 16;   // loads in flight per wave; the order of the k terms does not depend on it
-  for (int kb = k0 + ph; kb < k1; kb += kGradWaves * KU) {
-    float h[KU], bv[KU];
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int k = kb + u * kGradWaves;
-      const int kc = k < k1 ? k : k0;
-      h[u] = H[(long long)kc * n + jc];
-      bv[u] = B[(long long)kc * r + (lane < r ? lane : 0)];
-    }
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const bool ok = kb + u * kGradWaves < k1;
-      const float hu = ok ? h[u] : 0.f;
-#pragma unroll
-      for (int c = 0; c < kRMax; ++c)
-        if (c < r) acc[c] = fmaf(hu, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bv[u]), c)), acc[c]);
-    }
-  }
-  // pairwise tree over the waves in a fixed order: (w, w + h) for h = 8, 4, 2, 1
-  for (int hh = kGradWaves / 2; hh >= 1; hh >>= 1) {
-    if (ph >= hh && ph < 2 * hh)
-#pragma unroll
-      for (int c = 0; c < kRMax; ++c) red[ph - hh][lane][c] = acc[c];
-    __syncthreads();
-    if (ph < hh)
-#pragma unroll
-      for (int c = 0; c < kRMax; ++c) acc[c] += red[ph][lane][c];
-    __syncthreads();
-  }
-  if (ph == 0 && j < n)
-    for (int c = 0; c < r; ++c) gpart[((long long)ks * n + j) * r + c] = acc[c];
-}
-
 // Upper-triangle storage of a symmetric r x r matrix, row by row: entry e is (a, b), a <= b.
 __device__ __forceinline__ void tri_entry(int e, int r, int& a, int& b) {
   int base = 0;
@@ -82,6 +34,15 @@ __device__ __forceinline__ double sum_strided(const double* p, long long stride,
   }
   for (; b < count; ++b) s += p[(long long)b * stride];
   return s;
+}
+
+// Groups of threads that share the sum of `cnt` entries over `count` parts: few enough
+// that adding the groups afterwards, one thread per entry, is short.
+__device__ __forceinline__ int sum_groups(int threads, int cnt, int count) {
+  int g = threads / cnt;
+  if (g > 8) g = 8;
+  if (g > count) g = count;
+  return g > 0 ? g : 1;
 }
 
 // Orders one wave's LDS accesses: they complete in program order, so only the
@@ -181,6 +142,139 @@ __device__ inline double wave_lambda_max(double* M, double* T, int r) {
     T = x;
   }
   return first * exp(acc);
+}
+
+// smallest / largest pivot for which one CholeskyQR pass is enough
+constexpr double kPivotSpan = 1e-6;
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Value of lane I of each 16-lane row, in every lane of the row.
+template <int I>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + I, 0xF, 0xF, false));
+}
+
+// acc[e][c] += h[e] * B[k][c], c < R, where lane c of each 16-lane row holds B[k][c].
+template <int R, int C = 0>
+__device__ __forceinline__ void rank1(float (&acc)[4][R], const float4& h, float b) {
+  if constexpr (C < R) {
+    const float bc = row_bcast<C>(b);
+    acc[0][C] = fmaf(h.x, bc, acc[0][C]);
+    acc[1][C] = fmaf(h.y, bc, acc[1][C]);
+    acc[2][C] = fmaf(h.z, bc, acc[2][C]);
+    acc[3][C] = fmaf(h.w, bc, acc[3][C]);
+    rank1<R, C + 1>(acc, h, b);
+  }
+}
+
+// Rows 64 jb .. + 63 of sum_k h_k b_k^T over the columns k0 <= k < k1, by a workgroup of
+// WV waves: thread i < 64 r gets row i / r, column i % r through put(i, value) (rows at
+// or beyond n are zero).  Quarter p = lane / 16 of wave w takes k = k0 + 4 w + p, then
+// every 4 WV-th, its lanes 4 rows each (16-byte loads, four 256-byte pieces of h_k per
+// wave); the quarters, then (above 8 waves) the waves w and w + 8, then the waves are
+// added in that order.  R: r rounded up to a multiple of 4.
+template <int R, int WV, class Put>
+__device__ __forceinline__ void urows_grad(const float* H, const float* B, int n, int r, int jb, int k0, int k1,
+                                           float (*red)[64][kRMax + 1], Put put) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+  const int l = lane & 15, p = lane >> 4, j = jb * 64 + 4 * l;
+  const bool full = (jb + 1) * 64 <= n;
+  float acc[4][R];
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int c = 0; c < R; ++c) acc[e][c] = 0.f;
+  constexpr int KU = 4;   // loads in flight per wave; the order of the k terms does not depend on it
+  for (int kb = k0 + 4 * wave; kb < k1; kb += 4 * WV * KU) {
+    float4 h[KU];
+    float bv[KU];
+#pragma unroll
+    for (int u = 0; u < KU; ++u) {
+      const int k = kb + p + u * 4 * WV;
+      const bool in = k < k1;
+      const float* row = H + (long long)(in ? k : k0) * n;
+      bv[u] = in && l < r ? B[(long long)k * r + l] : 0.f;
+      if (full) {
+        const f32x4_u v = *reinterpret_cast<const f32x4_u*>(row + j);
+        h[u] = make_float4(v.x, v.y, v.z, v.w);
+      } else {
+        h[u] = make_float4(j < n ? row[j] : 0.f, j + 1 < n ? row[j + 1] : 0.f, j + 2 < n ? row[j + 2] : 0.f,
+                           j + 3 < n ? row[j + 3] : 0.f);
+      }
+      if (!in) h[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int u = 0; u < KU; ++u) rank1<R>(acc, h[u], bv[u]);
+  }
+  // quarters: afterwards lane (p, l) holds row 4 l + p
+  float v[R];
+#pragma unroll
+  for (int c = 0; c < R; ++c) {
+    float t[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = acc[e][c] + __shfl_xor(acc[e][c], 16);
+      t[e] = x + __shfl_xor(x, 32);
+    }
+    v[c] = p == 0 ? t[0] : (p == 1 ? t[1] : (p == 2 ? t[2] : t[3]));
+  }
+  constexpr int WS = WV > 8 ? 8 : WV;   // sums left after the first step
+  const int row = 4 * l + p;
+  if (wave >= WV - WS)
+#pragma unroll
+    for (int c = 0; c < R; ++c) red[wave - (WV - WS)][row][c] = v[c];
+  __syncthreads();
+  if constexpr (WV > 8) {
+    if (wave < WS)
+#pragma unroll
+      for (int c = 0; c < R; ++c) red[wave][row][c] += v[c];
+    __syncthreads();
+  }
+  for (int i = tid; i < 64 * r; i += 64 * WV) {
+    const int rw = i / r, c = i - rw * r;
+    float g = red[0][rw][c];
+#pragma unroll
+    for (int w = 1; w < WS; ++w) g += red[w][rw][c];
+    put(i, g);
+  }
+}
+
+template <int WV, class Put>
+__device__ __forceinline__ void urows_grad_r(const float* H, const float* B, int n, int r, int jb, int k0, int k1,
+                                             float (*red)[64][kRMax + 1], Put put) {
+  if (r <= 4) urows_grad<4, WV>(H, B, n, r, jb, k0, k1, red, put);
+  else if (r <= 8) urows_grad<8, WV>(H, B, n, r, jb, k0, k1, red, put);
+  else if (r <= 12) urows_grad<12, WV>(H, B, n, r, jb, k0, k1, red, put);
+  else urows_grad<16, WV>(H, B, n, r, jb, k0, k1, red, put);
+}
+
+// Part of X^T Y over the 64 rows in LDS (row-major, r wide): the upper triangle (a <= b)
+// row by row with sym, all r^2 entries without; by a workgroup of WV waves.
+template <int WV>
+__device__ __forceinline__ void rows_gram64(const double* X, const double* Y, int r, bool sym, double* dst) {
+  const int lane = threadIdx.x & 63, wave = wave_id();
+  const int E = sym ? r * (r + 1) / 2 : r * r;
+  for (int e = wave; e < E; e += WV) {
+    int a = 0, b = 0;
+    if (sym) tri_entry(e, r, a, b);
+    else { a = e / r; b = e - a * r; }
+    const double s = wave_sum_dpp(X[lane * r + a] * Y[lane * r + b]);
+    if (lane == 0) dst[e] = s;
+  }
+}
+
+// x <- x R^{-1} for one row, R^T = L (row-major r x r in LDS), by forward substitution.
+__device__ __forceinline__ void solve_row(double (&x)[kRMax], const double* L, const double* rdiag, int r) {
+#pragma unroll
+  for (int c = 0; c < kRMax; ++c) {
+    if (c < r) {
+      double t = x[c];
+#pragma unroll
+      for (int p = 0; p < kRMax; ++p)
+        if (p < c) t = fma(-x[p], L[c * r + p], t);
+      x[c] = t * rdiag[c];
+    }
+  }
 }
 
 // End of a GDmin iteration (one thread): the residual from the summed ||r_k||^2, the log,
