@@ -27,8 +27,6 @@ SOURCES = [
     ("k_column.hip", ["-DALTG_PART=2"], "k_column_tuned.o"),
     ("k_column.hip", ["-DALTG_PART=3"], "k_column_cached.o"),
     ("k_small.hip", [], "k_small.o"),
-    ("k_update.hip", [], "k_update.o"),
-    ("k_subspace.hip", [], "k_subspace.o"),
     ("k_gen.hip", [], "k_gen.o"),
     ("k_fourier.hip", [], "k_fourier.o"),
     ("k_rank.hip", [], "k_rank.o"),

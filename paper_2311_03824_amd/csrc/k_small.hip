@@ -1,6 +1,9 @@
-// Small kernels of AltGDmin-LR+S for gfx950: sums over the columns, the control block,
-// fills and copies, start blocks and restored supports.
+// The U side of AltGDmin-LR+S for gfx950: the U update of a GDmin iteration (update.h) and
+// the spectral start (subspace.h), and the small kernels beside them: sums over the
+// columns, the control block, fills and copies, start blocks and restored supports.
 #include "launch.h"
+#include "subspace.h"
+#include "update.h"
 
 namespace altg {
 

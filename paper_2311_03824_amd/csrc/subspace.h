@@ -17,6 +17,7 @@
 // for.  A wait is bounded all the same: a workgroup that gives up raises *stuck, which
 // ends every other one too (error bit 1).  Rows are dealt to workgroups in a fixed way
 // and every sum runs in a fixed order, so results do not depend on timing.
+#pragma once
 #include "launch.h"
 #include "uside.h"
 

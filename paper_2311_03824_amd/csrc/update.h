@@ -22,6 +22,7 @@
 // Q to FP32 rounding whenever cond(X)^2 2^-53 is far below it: a second pass is taken
 // only when the pivots span more than kPivotSpan (each workgroup then forms the Gram of
 // all the rounded rows itself: slow, and only for steps that nearly cancel U).
+#pragma once
 #include "launch.h"
 #include "uside.h"
 
