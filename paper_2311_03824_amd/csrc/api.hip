@@ -211,8 +211,6 @@ struct altgdmin_handle {
   // gradient or L_0 L_0^H U), U, Uprev, Utmp and Tpow hold complex values there
   float* FU = nullptr;     // n x r: the 2D DFT of U's columns
   float* tw = nullptr;     // 96 twiddles
-  double* fpart = nullptr; // per-256-row-block partial Grams of the GD update
-  double* frinv = nullptr; // R1^{-1}, R2^{-1} of the GD update
   void* rank_ws = nullptr; // r = 0 (automatic rank): scratch of the rank estimate
   float* rank_embed = nullptr;  // Fourier form, r = 0: the real embedding of L_0 (2q x 2n)
   int col_waves = kWaves;  // waves of the column workgroup (a property of the problem, see choose_col_waves)
@@ -243,16 +241,16 @@ size_t carve_fourier(altgdmin_handle* h, void* base) {
   h->H = c.take<float>(2 * q * n);
   h->colrr = c.take<double>(q);
   h->colflags = c.take<int>(q);
-  h->KS = 1;
-  h->gpart = c.take<float>(2 * n * r);
+  h->KS = fsub_splits(p.n, p.q);
+  h->gpart = c.take<float>((size_t)h->KS * 2 * n * r);
   h->FU = c.take<float>(2 * n * r);
   h->U = c.take<float>(2 * n * r);
   h->Uprev = c.take<float>(2 * n * r);
   h->Utmp = c.take<float>(2 * n * r);
   h->Tpow = c.take<float>(2 * q * r);
   h->tw = c.take<float>(2 * (size_t)std::max(kFN, p.n1 + p.n2));
-  h->fpart = c.take<double>(2 * 3 * r * r * ((n + 255) / 256));
-  h->frinv = c.take<double>(2 * 2 * r * r);
+  h->upart = c.take<double>(fupd_part_doubles(p.n, (int)r));
+  h->upd = c.take<int>(1);
   h->rlog_len = h->par.t_max > 0 ? h->par.t_max : 1;
   h->rlog = c.take<double>(h->rlog_len);
   if (p.r == 0) {   // automatic rank: the real embedding of L_0 and the estimate's scratch
@@ -656,29 +654,20 @@ FColArgs fcol_args(const altgdmin_handle* h, int mode) {
   return a;
 }
 
-FQRArgs fqr_args(const altgdmin_handle* h, int mode) {
-  FQRArgs a;
-  std::memset(&a, 0, sizeof(a));
-  a.n = h->prob.n; a.r = h->prob.r; a.q = h->prob.q; a.mode = mode;
-  a.G = reinterpret_cast<const float2*>(h->gpart);
-  a.U = reinterpret_cast<float2*>(h->U);
-  a.Uprev = reinterpret_cast<float2*>(h->Uprev);
-  a.Utmp = reinterpret_cast<float2*>(h->Utmp);
-  a.ctl = h->ctl;
-  a.eta_c = h->par.eta_c;
-  a.power_tol = h->par.power_tol;
-  a.colrr = h->colrr;
-  a.colflags = h->colflags;
-  a.rlog = h->rlog;
-  a.rlog_len = h->rlog_len;
-  a.part = reinterpret_cast<double2*>(h->fpart);
-  a.rinv = reinterpret_cast<double2*>(h->frinv);
-  a.nb = (h->prob.n + 255) / 256;
-  return a;
-}
-
 #define F2(p) reinterpret_cast<float2*>(p)
 #define CF2(p) reinterpret_cast<const float2*>(p)
+
+FUpdArgs fupd_args(const altgdmin_handle* h) {
+  FUpdArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.n = h->prob.n; a.q = h->prob.q; a.r = h->prob.r;
+  a.H = CF2(h->H); a.B = CF2(h->Bt); a.G = F2(h->gpart); a.U = F2(h->U); a.Uprev = F2(h->Uprev);
+  a.part = h->upart; a.upd = h->upd; a.ctl = h->ctl;
+  a.eta_c = h->par.eta_c;
+  a.colrr = h->colrr; a.colflags = h->colflags;
+  a.rlog = h->rlog; a.rlog_len = h->rlog_len;
+  return a;
+}
 
 // The four launches of one GDmin iteration of the partial Fourier form.
 hipError_t fourier_launch(altgdmin_handle* h, int which, hipStream_t st) {
@@ -688,10 +677,8 @@ hipError_t fourier_launch(altgdmin_handle* h, int which, hipStream_t st) {
       if (p.n1 == kFN && p.n2 == kFN) return launch_fu(CF2(h->U), p.r, CF2(h->tw), F2(h->FU), st);
       return launch_fu_gen(CF2(h->U), p.n, p.r, p.n1, p.n2, CF2(h->tw), F2(h->FU), st);
     case 1: return launch_fcol(fcol_args(h, FCOL_GD), st);
-    case 2:
-      return launch_fgrad_gd(CF2(h->H), CF2(h->Bt), CF2(h->U), p.n, p.q, p.r, F2(h->gpart),
-                             reinterpret_cast<double2*>(h->fpart), nullptr, st);
-    default: return launch_fqr_gd(fqr_args(h, QR_GD), st);
+    case 2: return launch_frows(fupd_args(h), st);
+    default: return launch_fapply(fupd_args(h), st);
   }
 }
 
@@ -846,17 +833,13 @@ int altgdmin_init(const altgdmin_problem* prob, const altgdmin_params* par, void
     if (p.U_start && !h->auto_rank) e = launch_copy_f(h->Utmp, p.U_start, 2LL * p.n * p.r, st);
     else e = launch_fbasis(F2(h->Utmp), p.n, p.r, st);
     if (e != hipSuccess) return bail(e, "start block");
-    if ((e = launch_fqr(fqr_args(h, QR_ORTH), st)) != hipSuccess) return bail(e, "orth");
-    for (int it = 0; it < par->power_iters; ++it) {
-      if ((e = launch_fltu(CF2(h->H), CF2(h->U), p.n, p.q, p.r, F2(h->Tpow), &h->ctl->conv, st)) != hipSuccess)
-        return bail(e, "ltu");
-      // L_0 (L_0^H U) with its per-block partial Grams, then CholeskyQR2 and the
-      // subspace change over many workgroups
-      if ((e = launch_fgrad_gd(CF2(h->H), CF2(h->Tpow), CF2(h->U), p.n, p.q, p.r, F2(h->gpart),
-                               reinterpret_cast<double2*>(h->fpart), &h->ctl->conv, st)) != hipSuccess)
-        return bail(e, "power grad");
-      if ((e = launch_fqr_gd(fqr_args(h, QR_POWER), st)) != hipSuccess) return bail(e, "power qr");
-    }
+    FSubArgs sa;
+    std::memset(&sa, 0, sizeof(sa));
+    sa.L0t = CF2(h->H); sa.start = F2(h->Utmp); sa.U = F2(h->U); sa.V = F2(h->Utmp); sa.T = F2(h->Tpow);
+    sa.gpart = F2(h->gpart); sa.part = h->upart; sa.n = p.n; sa.q = p.q; sa.r = p.r; sa.KS = h->KS;
+    sa.iters = par->power_iters; sa.tol = par->power_tol;
+    sa.ctl = h->ctl; sa.bar = &h->ctl->bar; sa.stuck = &h->ctl->stuck;
+    if ((e = launch_fsub(sa, st)) != hipSuccess) return bail(e, "subspace");
     if ((e = launch_reset_ctl(h->ctl, 0, st)) != hipSuccess) return bail(e, "reset eta");
     *out = h;
     return ALTGDMIN_OK;

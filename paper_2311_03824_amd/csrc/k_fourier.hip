@@ -12,13 +12,10 @@
 //            G_k = P_k^H P_k and its inverse in FP64, the projected IHT of
 //            Alg. 2 (tau iterations, three 2D FFTs each), b_k by least squares
 //            (eq. (bk_LS)), r_k and h_k = A_k^H r_k;
-//   k_fgrad_gd: grad_U f = sum_k h_k b_k^H (four column splits in a fixed order)
-//            and per-block partial Grams;
-//   k_fqr_a .. k_fqr_d: eta at t = 1, U - eta grad, CholeskyQR2 with a real
-//            positive diagonal over many workgroups, the residual.
+//   k_frows, k_fapply (fourier_u.h): grad_U f = sum_k h_k b_k^H, eta at t = 1, U - eta
+//            grad orthonormalised with a real positive diagonal, the residual.
 // The initialisation uses k_fcol with M = A_k (IHT from 0, then the columns of
-// L_0 = [A_k^H (y_k - A_k s_k)]), k_fqr for the orthonormal start block, and the
-// subspace iteration k_fltu / k_fgrad_gd / k_fqr_a .. k_fqr_f.
+// L_0 = [A_k^H (y_k - A_k s_k)]) and k_fsub (the start block and the subspace iteration).
 //
 // 2D FFT.  A frame lives in LDS as 96 rows of 97 complex values (one pad column
 // keeps the column pass free of bank conflicts).  Each 96-point transform is
@@ -37,6 +34,7 @@
 // registers across a barrier, so the passes run in place.  k_fu_gen is the same
 // transform of the columns of U.
 #include "common.h"
+#include "fourier_u.h"
 #include "launch.h"
 
 namespace altg {
@@ -879,378 +877,6 @@ __global__ __launch_bounds__(kFThreads) void k_fu_gen(const float2* U, int n, in
   for (int j = threadIdx.x; j < n; j += kFThreads) FU[(long long)j * r + c] = grid[j];
 }
 
-// Tc[k][c] = sum_j H[k][j] conj(U[j][c]) (so that L_0 (L_0^H U) = sum_k h_k conj(Tc[k]) ^ T).
-template <int R>
-__global__ __launch_bounds__(kFThreads) void k_fltu(const float2* H, const float2* U, int n, int r, float2* Tc,
-                                                    const int* skip) {
-  if (skip && *skip) return;
-  __shared__ double red[kFWaves * 2 * kFRMax];
-  __shared__ double out[2 * kFRMax];
-  const int k = blockIdx.x, tid = threadIdx.x;
-  double v[2 * R];
-#pragma unroll
-  for (int i = 0; i < 2 * R; ++i) v[i] = 0.0;
-  for (int j = tid; j < n; j += kFThreads) {
-    const float2 h = H[(long long)k * n + j];
-#pragma unroll
-    for (int c = 0; c < R; ++c)
-      if (c < r) {
-        const float2 u = U[(long long)j * r + c];
-        v[2 * c] += (double)h.x * u.x + (double)h.y * u.y;
-        v[2 * c + 1] += (double)h.y * u.x - (double)h.x * u.y;
-      }
-  }
-  fblock_sum<2 * R>(v, red, out);
-  if (tid < r) Tc[(long long)k * r + tid] = make_float2((float)out[2 * tid], (float)out[2 * tid + 1]);
-}
-
-// Rows of Gsum[j][c] = sum_k H[k][j] conj(B[k][c]) (grad_U f with B = B_t;
-// L_0 (L_0^H U) with B = Tc) for the 256 rows j of block blockIdx.x, by 1024
-// threads: thread t takes row t % 256 and the k range of split s = t / 256 (the
-// four quarters of 0 .. q - 1, each summed in order); the splits are added as
-// (s0 + s2) + (s1 + s3) through buf (2 x 256 x R float2 of LDS).  Threads of
-// split 0 return true and hold the row in acc.
-constexpr int kFGradSplits = 4;
-
-template <int R>
-__device__ bool fgrad_rows(const float2* H, const float2* B, int n, int q, int r, float2 (&acc)[R], float2* buf) {
-  const int tid = threadIdx.x, row = tid & 255, sp = tid >> 8;
-  const int j = blockIdx.x * 256 + row;
-  const int jc = j < n ? j : n - 1;
-  const int k0 = q * sp / kFGradSplits, k1 = q * (sp + 1) / kFGradSplits;
-#pragma unroll
-  for (int c = 0; c < R; ++c) acc[c] = make_float2(0.f, 0.f);
-  constexpr int KU = 8;   // loads in flight per thread; the k order of the sum does not depend on it
-  for (int kb = k0; kb < k1; kb += KU) {
-    float2 h[KU];
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int k = kb + u < k1 ? kb + u : k0;
-      h[u] = H[(long long)k * n + jc];
-    }
-#pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      if (kb + u < k1) {
-        const int k = kb + u;
-#pragma unroll
-        for (int c = 0; c < R; ++c)
-          if (c < r) {
-            const float2 b = B[(long long)k * r + c];
-            acc[c].x = fmaf(h[u].x, b.x, fmaf(h[u].y, b.y, acc[c].x));
-            acc[c].y = fmaf(h[u].y, b.x, fmaf(-h[u].x, b.y, acc[c].y));
-          }
-      }
-    }
-  }
-  auto put = [&](int slot) {
-#pragma unroll
-    for (int c = 0; c < R; ++c) buf[(slot * 256 + row) * R + c] = acc[c];
-  };
-  auto add = [&](int slot) {
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-      const float2 o = buf[(slot * 256 + row) * R + c];
-      acc[c].x += o.x;
-      acc[c].y += o.y;
-    }
-  };
-  if (sp >= 2) put(sp - 2);
-  __syncthreads();
-  if (sp < 2) add(sp);
-  __syncthreads();
-  if (sp == 1) put(0);
-  __syncthreads();
-  if (sp == 0) add(0);
-  __syncthreads();   // buf is free again
-  return sp == 0;
-}
-
-namespace {
-
-// Largest eigenvalue of a real symmetric N x N matrix (row-major, destroyed) by
-// cyclic Jacobi rotations; one thread.
-__device__ double jacobi_lmax(double* A, int N) {
-  for (int sweep = 0; sweep < 40; ++sweep) {
-    double off = 0.0, tot = 0.0;
-    for (int i = 0; i < N; ++i)
-      for (int j = 0; j < N; ++j) {
-        tot += A[i * N + j] * A[i * N + j];
-        if (i != j) off += A[i * N + j] * A[i * N + j];
-      }
-    if (off <= 1e-30 * tot) break;
-    for (int p = 0; p < N - 1; ++p)
-      for (int q = p + 1; q < N; ++q) {
-        const double apq = A[p * N + q];
-        if (apq == 0.0) continue;
-        const double theta = (A[q * N + q] - A[p * N + p]) / (2.0 * apq);
-        const double t = (theta >= 0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-        const double cs = 1.0 / sqrt(t * t + 1.0), sn = t * cs;
-        for (int k = 0; k < N; ++k) {
-          const double akp = A[k * N + p], akq = A[k * N + q];
-          A[k * N + p] = cs * akp - sn * akq;
-          A[k * N + q] = sn * akp + cs * akq;
-        }
-        for (int k = 0; k < N; ++k) {
-          const double apk = A[p * N + k], aqk = A[q * N + k];
-          A[p * N + k] = cs * apk - sn * aqk;
-          A[q * N + k] = sn * apk + cs * aqk;
-        }
-      }
-  }
-  double l = A[0];
-  for (int i = 1; i < N; ++i) l = fmax(l, A[i * N + i]);
-  return l;
-}
-
-// W (r x r, complex FP64) = X^H Y over the n rows of the row-major n x r X and Y
-// (global memory).  Whole rows are staged through LDS 256 at a time (coalesced
-// copies; the next chunk is loaded into registers while the current one is
-// summed), so each element is read from memory once.  Wave w computes the
-// entries e = w, w + 16, ... (with sym, the entries a <= b only, the others by
-// conjugation); per entry the lanes stride over the rows j = lane, lane + 64, ...
-// in order and the lane sums are added by the fixed DPP tree.  stage holds
-// 2 x 256 x kFRMax float2.  Ends with a barrier.  (Not inlined: inlined at its
-// three call sites it pushed k_fqr<6> past 128 VGPRs.)
-template <int R>
-__device__ __noinline__ void fgram(const float2* X, const float2* Y, int n, int r, float2* stage, double2* W,
-                                   bool sym = true) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-  constexpr int CH = 256;
-  constexpr int kEW = (kFRMax * kFRMax + kFWaves - 1) / kFWaves;   // entries of one wave, at most
-  const bool same = X == Y;
-  float2* Xs = stage;
-  float2* Ys = same ? stage : stage + CH * kFRMax;
-  const int E = sym ? r * (r + 1) / 2 : r * r;
-  int ra[kEW], rb[kEW];
-  double sr[kEW], si[kEW];
-#pragma unroll
-  for (int t = 0; t < kEW; ++t) {
-    const int e = wave + t * kFWaves;
-    int a = 0, b = 0;
-    if (e < E) {
-      if (sym) {
-        int base = 0;
-        while (e >= base + (r - a)) {
-          base += r - a;
-          ++a;
-        }
-        b = a + (e - base);
-      } else {
-        a = e / r;
-        b = e - a * r;
-      }
-    }
-    ra[t] = a;
-    rb[t] = b;
-    sr[t] = 0.0;
-    si[t] = 0.0;
-  }
-  const int nch = (n + CH - 1) / CH;
-  float2 xv[2], yv[2];   // this thread's share of a chunk: at most 256 x 8 / 1024 = 2 elements
-  auto fetch = [&](int c) {
-    const long long o = (long long)c * CH * r;
-    const int cnt = min(CH, n - c * CH) * r;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = tid + u * kFThreads;
-      if (i < cnt) {
-        xv[u] = X[o + i];
-        if (!same) yv[u] = Y[o + i];
-      }
-    }
-  };
-  fetch(0);
-  for (int c = 0; c < nch; ++c) {
-    const int rows = min(CH, n - c * CH);
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = tid + u * kFThreads;
-      if (i < rows * r) {
-        Xs[i] = xv[u];
-        if (!same) Ys[i] = yv[u];
-      }
-    }
-    __syncthreads();
-    if (c + 1 < nch) fetch(c + 1);
-#pragma unroll
-    for (int t = 0; t < kEW; ++t) {
-      if (wave + t * kFWaves < E) {
-        for (int jl = lane; jl < rows; jl += 64) {   // conj(X[j][ra]) Y[j][rb]
-          const float2 x = Xs[jl * r + ra[t]], y = Ys[jl * r + rb[t]];
-          sr[t] = fma((double)x.x, (double)y.x, fma((double)x.y, (double)y.y, sr[t]));
-          si[t] = fma((double)x.x, (double)y.y, fma(-(double)x.y, (double)y.x, si[t]));
-        }
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int t = 0; t < kEW; ++t) {
-    if (wave + t * kFWaves < E) {
-      const double vr = wave_sum_dpp(sr[t]);
-      const double vi = wave_sum_dpp(si[t]);
-      if (lane == 0) {
-        W[ra[t] * r + rb[t]] = make_double2(vr, vi);
-        if (sym) W[rb[t] * r + ra[t]] = make_double2(vr, -vi);
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Cholesky W = L L^H of a Hermitian positive definite r x r matrix (complex FP64,
-// row-major in LDS), real positive diagonal, by one wave in LDS, right-looking:
-// the lower triangle of W is copied to L; at step j column j is scaled by
-// lane-parallel products with 1 / L_jj and the trailing lower triangle is
-// updated by all lanes.  Returns false (wave-uniform) if a pivot is not
-// positive.  All 64 lanes call it; the LDS accesses of one wave complete in order.
-__device__ bool wave_chol_c(const double2* W, double2* L, int r) {
-  const int lane = threadIdx.x & 63;
-  for (int e = lane; e < r * r; e += 64)
-    if (e % r <= e / r) L[e] = W[e];
-  __builtin_amdgcn_s_waitcnt(0);
-  __builtin_amdgcn_wave_barrier();
-  for (int j = 0; j < r; ++j) {
-    const double piv = L[j * r + j].x;
-    if (!(piv > 0.0)) return false;
-    const double d = sqrt(piv);
-    const double inv = 1.0 / d;
-    if (lane == j) {
-      L[j * r + j] = make_double2(d, 0.0);
-    } else if (lane > j && lane < r) {
-      const double2 v = L[lane * r + j];
-      L[lane * r + j] = make_double2(v.x * inv, v.y * inv);
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    const int t = r - j - 1;   // trailing size
-    for (int e = lane; e < t * t; e += 64) {
-      const int i = j + 1 + e / t, k = j + 1 + e % t;
-      if (k <= i) {   // L[i][k] -= L[i][j] conj(L[k][j])
-        const double2 a = L[i * r + j], b = L[k * r + j], w = L[i * r + k];
-        L[i * r + k] = make_double2(w.x - (a.x * b.x + a.y * b.y), w.y - (a.y * b.x - a.x * b.y));
-      }
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-  }
-  return true;
-}
-
-// Rinv = (L^H)^{-1} (upper triangular, complex FP64) from the factor of
-// wave_chol_c, by one wave: lane c solves L m = e_c by forward substitution (the
-// rows of L read from LDS) and writes Rinv[c][i] = conj(m[i]) to dst (r x r,
-// row-major).  All 64 lanes of the wave that factored call it.
-template <int R>
-__device__ void wave_rinv_c(const double2* L, double2* dst, int r) {
-  const int c = threadIdx.x & 63;
-  if (c < r) {
-    double2 mc[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      double mr = 0.0, mi = 0.0;
-      if (i < r && i >= c) {
-        mr = (i == c) ? 1.0 : 0.0;
-#pragma unroll
-        for (int p = 0; p < R; ++p)
-          if (p >= c && p < i) {   // - L[i][p] m[p]
-            const double2 a = L[i * r + p];
-            mr -= a.x * mc[p].x - a.y * mc[p].y;
-            mi -= a.x * mc[p].y + a.y * mc[p].x;
-          }
-        const double dd = L[i * r + i].x;
-        mr /= dd;
-        mi /= dd;
-      }
-      mc[i] = make_double2(mr, mi);
-    }
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-      if (i < r) dst[c * r + i] = make_double2(mc[i].x, -mc[i].y);
-  }
-}
-
-// dst[0 .. count) = src[0 .. count) (complex values, 16-byte aligned arrays) by the
-// workgroup with 16-byte accesses, 8 in flight per thread.
-__device__ __forceinline__ void block_copy_c(float2* dst, const float2* src, int count) {
-  const int tid = threadIdx.x;
-  const int n4 = count >> 1;   // two complex values per float4
-  typedef float f32x4_c __attribute__((ext_vector_type(4)));
-  const f32x4_c* s4 = reinterpret_cast<const f32x4_c*>(src);
-  f32x4_c* d4 = reinterpret_cast<f32x4_c*>(dst);
-  constexpr int U = 8;
-  int i = tid;
-  for (; i + (U - 1) * kFThreads < n4; i += U * kFThreads) {
-    f32x4_c v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = s4[i + u * kFThreads];
-#pragma unroll
-    for (int u = 0; u < U; ++u) d4[i + u * kFThreads] = v[u];
-  }
-  for (; i < n4; i += kFThreads) d4[i] = s4[i];
-  if ((count & 1) && tid == 0) dst[count - 1] = src[count - 1];
-}
-
-// One CholeskyQR pass on X (n x r in global memory): X <- X R^{-1}, R = L^H from
-// X^H X = L L^H.  Returns false if X^H X is not positive definite.
-template <int R>
-__device__ bool fcholqr_pass(float2* X, int n, int r, float2* stage, double2* W, double2* Lm, int* okf) {
-  const int tid = threadIdx.x;
-  fgram<R>(X, X, n, r, stage, W);
-  if (tid < 64) {
-    const bool ok = wave_chol_c(W, Lm, r);
-    if (tid == 0) *okf = ok ? 1 : 0;
-  }
-  __syncthreads();
-  if (!*okf) return false;
-  // row x <- x R^{-1}: q[c] = (x[c] - sum_{p<c} q[p] R[p][c]) / R[c][c], R[p][c] = conj(L[c][p])
-  for (int j = tid; j < n; j += kFThreads) {
-    float2 x[R];
-    double2 qd[R];
-#pragma unroll
-    for (int c = 0; c < R; ++c) x[c] = c < r ? X[(long long)j * r + c] : make_float2(0.f, 0.f);
-#pragma unroll
-    for (int c = 0; c < R; ++c) {
-      double tr = x[c].x, ti = x[c].y;
-#pragma unroll
-      for (int p = 0; p < c; ++p) {   // q[p] * conj(L[c][p])
-        const double2 l = c < r ? Lm[c * r + p] : make_double2(0.0, 0.0);
-        tr -= qd[p].x * l.x + qd[p].y * l.y;
-        ti -= qd[p].y * l.x - qd[p].x * l.y;
-      }
-      const double d = c < r ? Lm[c * r + c].x : 1.0;
-      qd[c] = make_double2(tr / d, ti / d);
-    }
-#pragma unroll
-    for (int c = 0; c < R; ++c)
-      if (c < r) X[(long long)j * r + c] = make_float2((float)qd[c].x, (float)qd[c].y);
-  }
-  __syncthreads();
-  return true;
-}
-
-}  // namespace
-
-// U <- QR(Utmp) (CholeskyQR2, real positive diagonal): the orthonormal start of
-// the subspace iteration.  One workgroup.  (The GD update and the subspace steps
-// run over many workgroups: k_fqr_a .. k_fqr_f.)
-template <int R>
-__global__ __launch_bounds__(kFThreads) void k_fqr(FQRArgs a) {
-  __shared__ float2 stage[2 * 256 * kFRMax];   // rows staged by fgram
-  __shared__ double2 W[kFRMax * kFRMax];
-  __shared__ double2 Lm[kFRMax * kFRMax];
-  __shared__ int okf;
-  const int tid = threadIdx.x, n = a.n, r = a.r, nr = n * r;
-  float2* X = a.Utmp;
-  bool ok = fcholqr_pass<R>(X, n, r, stage, W, Lm, &okf);
-  if (ok) ok = fcholqr_pass<R>(X, n, r, stage, W, Lm, &okf);
-  if (!ok) {
-    if (tid == 0) atomicOr(&a.ctl->err, 2);
-    return;
-  }
-  block_copy_c(a.U, X, nr);
-}
-
 __global__ void k_ftwiddle(float2* tw) {
   const int t = threadIdx.x;
   if (t < kFN) {
@@ -1276,338 +902,6 @@ __global__ void k_fbasis(float2* U, int n, int r) {
     const int j = (int)(i / r), c = (int)(i % r);
     U[i] = make_float2((j % r == c) ? 1.f : 0.f, 0.f);
   }
-}
-
-// ---------------------------------------------------------------- GD update over many workgroups
-//
-// The projected GD step U+ = QR(U - eta grad) of Alg. 1 for the Fourier form,
-// split so that the n x r arrays are streamed by many CUs:
-//   k_fgrad_gd : rows of grad (four column splits per 1024-thread workgroup,
-//                added in a fixed order) and, per 256-row block, the partial
-//                Grams U^H U, U^H G, G^H G (wave per entry, lanes over rows);
-//   k_fqr_a    : one workgroup: sums the partials in block order, eta at t = 1,
-//                the Gram of X = U - eta G by expansion, its Cholesky factor and
-//                R1^{-1} (one wave); the residual and the iteration counter;
-//   k_fqr_b    : X = (U - eta G) R1^{-1} row by row, partial Grams of X;
-//   k_fqr_c    : one workgroup: R2^{-1} from the Gram of X;
-//   k_fqr_d    : U_prev = U, U = X R2^{-1}.
-// CholeskyQR2 as in k_fqr, with the first Gram taken from the expansion
-// U^H U - eta (U^H G + G^H U) + eta^2 G^H G of the unrounded U - eta G.
-//
-// The initialisation's subspace iteration (mode QR_POWER) runs the same chain
-// on G = L_0 (L_0^H U): k_fqr_a takes the first Gram as G^H G, k_fqr_b forms
-// X = G R1^{-1}, and k_fqr_d adds per-block partial Grams U_prev^H U; then
-//   k_fqr_e    : W = U_prev^H U from the partials, per-block sums of
-//                |U - U_prev W|^2 over the rows (the subspace change);
-//   k_fqr_f    : one thread: the change, the step counter and the stop rule.
-// Every kernel of the chain returns at once after the stop rule has fired.
-
-namespace {
-
-// sum over b = 0 .. nb - 1 of p[b * stride], in that order; the loads go out 8 at a time.
-__device__ __forceinline__ double2 sum_blocks(const double2* p, long long stride, int nb) {
-  double sr = 0.0, si = 0.0;
-  int b = 0;
-  for (; b + 8 <= nb; b += 8) {
-    double2 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = p[(long long)(b + u) * stride];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      sr += v[u].x;
-      si += v[u].y;
-    }
-  }
-  for (; b < nb; ++b) {
-    const double2 v = p[(long long)b * stride];
-    sr += v.x;
-    si += v.y;
-  }
-  return make_double2(sr, si);
-}
-
-// Partial Gram of the 256 LDS rows Xl, Yl (rows x r complex): dst[a * r + b] =
-// sum_rows conj(X[a]) Y[b]; the workgroup's waves take entries w, w + waves, ...;
-// with sym only a <= b are summed and the rest mirrored.
-__device__ void rows_gram(const float2* Xl, const float2* Yl, int r, bool sym, double2* dst) {
-  const int lane = threadIdx.x & 63, wave = wave_id(), waves = blockDim.x >> 6;
-  const int E = sym ? r * (r + 1) / 2 : r * r;
-  for (int e = wave; e < E; e += waves) {
-    int ra = 0, rb = 0;
-    if (sym) {
-      int base = 0;
-      while (e >= base + (r - ra)) {
-        base += r - ra;
-        ++ra;
-      }
-      rb = ra + (e - base);
-    } else {
-      ra = e / r;
-      rb = e - ra * r;
-    }
-    double sr = 0.0, si = 0.0;
-    for (int j = lane; j < 256; j += 64) {
-      const float2 x = Xl[j * r + ra], y = Yl[j * r + rb];
-      sr = fma((double)x.x, (double)y.x, fma((double)x.y, (double)y.y, sr));
-      si = fma((double)x.x, (double)y.y, fma(-(double)x.y, (double)y.x, si));
-    }
-    sr = wave_sum_dpp(sr);
-    si = wave_sum_dpp(si);
-    if (lane == 0) {
-      dst[ra * r + rb] = make_double2(sr, si);
-      if (sym) dst[rb * r + ra] = make_double2(sr, -si);
-    }
-  }
-}
-
-}  // namespace
-
-template <int R>
-__global__ __launch_bounds__(kFThreads) void k_fgrad_gd(const float2* H, const float2* B, const float2* U, int n, int q,
-                                                        int r, float2* Gsum, double2* part, const int* skip) {
-  if (skip && *skip) return;
-  __shared__ float2 sm[2 * 256 * R];   // the split sums first, then U and grad rows
-  float2* Ul = sm;
-  float2* Gl = sm + 256 * R;
-  float2 acc[R];
-  const bool mine = fgrad_rows<R>(H, B, n, q, r, acc, sm);
-  const int tid = threadIdx.x, j = blockIdx.x * 256 + (tid & 255);
-  if (mine) {
-#pragma unroll
-    for (int c = 0; c < R; ++c)
-      if (c < r) {
-        const bool in = j < n;
-        if (in) Gsum[(long long)j * r + c] = acc[c];
-        Gl[tid * r + c] = in ? acc[c] : make_float2(0.f, 0.f);
-        Ul[tid * r + c] = in ? U[(long long)j * r + c] : make_float2(0.f, 0.f);
-      }
-  }
-  __syncthreads();
-  double2* slot = part + (long long)blockIdx.x * 3 * r * r;
-  rows_gram(Ul, Ul, r, true, slot);
-  rows_gram(Ul, Gl, r, false, slot + r * r);
-  rows_gram(Gl, Gl, r, true, slot + 2 * r * r);
-}
-
-__global__ __launch_bounds__(256) void k_fqr_a(FQRArgs a) {
-  __shared__ double2 S[3 * kFRMax * kFRMax], Lm[kFRMax * kFRMax];
-  __shared__ double Mr[4 * kFRMax * kFRMax];
-  __shared__ double red[4];
-  __shared__ double eta_s;
-  if (a.mode == QR_POWER && a.ctl->conv) return;
-  const int tid = threadIdx.x, r = a.r, rr = r * r;
-  double2* W = reinterpret_cast<double2*>(Mr);
-  for (int e = tid; e < 3 * rr; e += 256) S[e] = sum_blocks(a.part + e, 3 * rr, a.nb);
-  __syncthreads();
-  const double2* UU = S;
-  const double2* UG = S + rr;
-  const double2* GG = S + 2 * rr;
-  if (tid == 0 && a.mode == QR_POWER) {
-    for (int e = 0; e < rr; ++e) W[e] = GG[e];   // X = G: its Gram
-  } else if (tid == 0) {
-    double eta;
-    if (!a.ctl->eta_set) {
-      const int N = 2 * r;   // Hermitian GG = A + iB -> real symmetric [[A, -B], [B, A]]
-      for (int i = 0; i < r; ++i)
-        for (int jj = 0; jj < r; ++jj) {
-          const double2 w = GG[i * r + jj];
-          Mr[i * N + jj] = w.x;
-          Mr[(i + r) * N + jj + r] = w.x;
-          Mr[i * N + jj + r] = -w.y;
-          Mr[(i + r) * N + jj] = w.y;
-        }
-      const double lam = jacobi_lmax(Mr, N);
-      eta = lam > 0.0 ? a.eta_c / sqrt(lam) : 0.0;
-      a.ctl->eta = eta;
-      a.ctl->eta_set = 1;
-    } else {
-      eta = a.ctl->eta;
-    }
-    eta_s = eta;
-    // Gram of X = U - eta G: UU - eta (UG + UG^H) + eta^2 GG
-    for (int i = 0; i < r; ++i)
-      for (int jj = 0; jj < r; ++jj) {
-        const double2 uu = UU[i * r + jj], ug = UG[i * r + jj], gu = UG[jj * r + i], gg = GG[i * r + jj];
-        W[i * r + jj] = make_double2(uu.x - eta * (ug.x + gu.x) + eta * eta * gg.x,
-                                     uu.y - eta * (ug.y - gu.y) + eta * eta * gg.y);
-      }
-  }
-  __syncthreads();
-  if (tid < 64) {
-    const bool ok = wave_chol_c(W, Lm, r);
-    if (ok) wave_rinv_c<kFRMax>(Lm, a.rinv, r);
-    if (!ok && tid == 0) {
-      atomicOr(&a.ctl->err, 2);
-      for (int e = 0; e < rr; ++e) a.rinv[e] = make_double2((e % (r + 1) == 0) ? 1.0 : 0.0, 0.0);
-    }
-  }
-  if (a.mode == QR_POWER) return;
-  // the residual of the iteration (colrr in column order) and the counters
-  double s = 0.0;
-  int fl = 0;
-  for (int k = tid; k < a.q; k += 256) {
-    s += a.colrr[k];
-    fl |= a.colflags[k];
-  }
-  s = wave_sum_dpp(s);
-  if ((tid & 63) == 0) red[tid >> 6] = s;
-  if (fl) atomicOr(&a.ctl->err, fl);
-  __syncthreads();
-  if (tid == 0) {
-    const double ss = (red[0] + red[1]) + (red[2] + red[3]);
-    const double resid = a.ctl->ynorm2 > 0.0 ? sqrt(ss / a.ctl->ynorm2) : sqrt(ss);
-    const int t = a.ctl->t;
-    if (a.rlog && t < a.rlog_len) a.rlog[t] = resid;
-    a.ctl->resid = resid;
-    a.ctl->t = t + 1;
-    a.ctl->prev_resid = resid;
-  }
-}
-
-// X = (U - eta G) R1^{-1} (FP64 per row, stored FP32) and the partial Grams of X.
-template <int R>
-__global__ __launch_bounds__(256) void k_fqr_b(FQRArgs a) {
-  __shared__ float2 Xl[256 * kFRMax];
-  if (a.mode == QR_POWER && a.ctl->conv) return;
-  const int tid = threadIdx.x, j = blockIdx.x * 256 + tid, r = a.r;
-  const bool power = a.mode == QR_POWER;
-  const double eta = power ? -1.0 : a.ctl->eta;   // POWER: X = G
-  double2 x[R];
-#pragma unroll
-  for (int c = 0; c < R; ++c) {
-    x[c] = make_double2(0.0, 0.0);
-    if (c < r && j < a.n) {
-      const float2 u = power ? make_float2(0.f, 0.f) : a.U[(long long)j * r + c], g = a.G[(long long)j * r + c];
-      x[c] = make_double2(fma(-eta, (double)g.x, (double)u.x), fma(-eta, (double)g.y, (double)u.y));
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < R; ++c)
-    if (c < r) {
-      double tr = 0.0, ti = 0.0;
-#pragma unroll
-      for (int aa = 0; aa < R; ++aa)
-        if (aa <= c) {   // x[aa] Rinv[aa][c]
-          const double2 m = a.rinv[aa * r + c];
-          tr += x[aa].x * m.x - x[aa].y * m.y;
-          ti += x[aa].x * m.y + x[aa].y * m.x;
-        }
-      const float2 v = make_float2((float)tr, (float)ti);
-      if (j < a.n) a.Utmp[(long long)j * r + c] = v;
-      Xl[tid * r + c] = j < a.n ? v : make_float2(0.f, 0.f);
-    }
-  __syncthreads();
-  rows_gram(Xl, Xl, r, true, a.part + (long long)blockIdx.x * r * r);
-}
-
-__global__ __launch_bounds__(256) void k_fqr_c(FQRArgs a) {
-  __shared__ double2 W[kFRMax * kFRMax], Lm[kFRMax * kFRMax];
-  if (a.mode == QR_POWER && a.ctl->conv) return;
-  const int tid = threadIdx.x, rr = a.r * a.r;
-  for (int e = tid; e < rr; e += 256) W[e] = sum_blocks(a.part + e, rr, a.nb);
-  __syncthreads();
-  if (tid < 64) {
-    const bool ok = wave_chol_c(W, Lm, a.r);
-    if (ok) wave_rinv_c<kFRMax>(Lm, a.rinv + rr, a.r);
-    if (!ok && tid == 0) {
-      atomicOr(&a.ctl->err, 2);
-      for (int e = 0; e < rr; ++e) a.rinv[rr + e] = make_double2((e % (a.r + 1) == 0) ? 1.0 : 0.0, 0.0);
-    }
-  }
-}
-
-// U_prev = U; U = X R2^{-1}.  POWER: also the per-block partial Grams U_prev^H U.
-template <int R>
-__global__ __launch_bounds__(256) void k_fqr_d(FQRArgs a) {
-  __shared__ float2 Ol[256 * R], Nl[256 * R];
-  const bool power = a.mode == QR_POWER;
-  if (power && a.ctl->conv) return;
-  const int tid = threadIdx.x, j = blockIdx.x * 256 + tid, r = a.r;
-  const bool in = j < a.n;
-  const double2* Ri = a.rinv + r * r;
-  double2 x[R];
-#pragma unroll
-  for (int c = 0; c < R; ++c) {
-    const float2 v = (in && c < r) ? a.Utmp[(long long)j * r + c] : make_float2(0.f, 0.f);
-    x[c] = make_double2(v.x, v.y);
-  }
-#pragma unroll
-  for (int c = 0; c < R; ++c)
-    if (c < r) {
-      double tr = 0.0, ti = 0.0;
-#pragma unroll
-      for (int aa = 0; aa < R; ++aa)
-        if (aa <= c) {
-          const double2 m = Ri[aa * r + c];
-          tr += x[aa].x * m.x - x[aa].y * m.y;
-          ti += x[aa].x * m.y + x[aa].y * m.x;
-        }
-      const float2 un = make_float2((float)tr, (float)ti);
-      const float2 uo = in ? a.U[(long long)j * r + c] : make_float2(0.f, 0.f);
-      if (in) {
-        a.Uprev[(long long)j * r + c] = uo;
-        a.U[(long long)j * r + c] = un;
-      }
-      if (power) {
-        Ol[tid * r + c] = uo;
-        Nl[tid * r + c] = in ? un : make_float2(0.f, 0.f);
-      }
-    }
-  if (!power) return;
-  __syncthreads();
-  rows_gram(Ol, Nl, r, false, a.part + (long long)blockIdx.x * r * r);
-}
-
-// POWER: W = U_prev^H U summed from the per-block partials (in block order, by
-// every workgroup), then the block's sum of |U[j] - U_prev[j] W|^2 over its rows
-// (FP64 per row, the 256 row sums added by the fixed DPP tree and the 4 wave
-// totals in order) into part[nb r^2 + block].x.
-template <int R>
-__global__ __launch_bounds__(256) void k_fqr_e(FQRArgs a) {
-  __shared__ double2 Wl[kFRMax * kFRMax];
-  __shared__ double wsum[4];
-  if (a.ctl->conv) return;
-  const int tid = threadIdx.x, j = blockIdx.x * 256 + tid, r = a.r, rr = r * r;
-  for (int e = tid; e < rr; e += 256) Wl[e] = sum_blocks(a.part + e, rr, a.nb);
-  __syncthreads();
-  double acc = 0.0;
-  if (j < a.n) {
-    float2 u[R];
-#pragma unroll
-    for (int e = 0; e < R; ++e) u[e] = e < r ? a.Uprev[(long long)j * r + e] : make_float2(0.f, 0.f);
-#pragma unroll
-    for (int c = 0; c < R; ++c)
-      if (c < r) {
-        const float2 xv = a.U[(long long)j * r + c];
-        double dx = (double)xv.x, dy = (double)xv.y;
-#pragma unroll
-        for (int e = 0; e < R; ++e)
-          if (e < r) {
-            const double2 w = Wl[e * r + c];
-            dx -= (double)u[e].x * w.x - (double)u[e].y * w.y;
-            dy -= (double)u[e].x * w.y + (double)u[e].y * w.x;
-          }
-        acc += dx * dx + dy * dy;
-      }
-  }
-  acc = wave_sum_dpp(acc);
-  if ((tid & 63) == 0) wsum[tid >> 6] = acc;
-  __syncthreads();
-  if (tid == 0) a.part[(long long)a.nb * rr + blockIdx.x] = make_double2((wsum[0] + wsum[1]) + (wsum[2] + wsum[3]), 0.0);
-}
-
-// POWER: the subspace change from the block sums (in block order), the step
-// counter and the stop rule.
-__global__ void k_fqr_f(FQRArgs a) {
-  if (threadIdx.x != 0 || a.ctl->conv) return;
-  const double f = sum_blocks(a.part + (long long)a.nb * a.r * a.r, 1, a.nb).x;
-  const double sd = sqrt(f);
-  const double prev = a.ctl->power_sd;   // 0 before the first step
-  a.ctl->power_sd = sd;
-  a.ctl->power_it += 1;
-  // as in k_fqr: converged at power_tol, or once the change has stopped
-  // shrinking below 1e-3 (by less than 1 % in a step)
-  if (sd <= a.power_tol || (sd <= 1e-3 && prev > 0.0 && sd >= 0.99 * prev)) a.ctl->conv = 1;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1667,53 +961,6 @@ hipError_t launch_fu(const float2* U, int r, const float2* tw, float2* FU, hipSt
   const int blocks = kFN * r / 2;   // two 32-lane groups per 64-thread workgroup
   hipLaunchKernelGGL(k_fu<0>, dim3(blocks), dim3(64), 0, st, U, r, tw, FU);
   hipLaunchKernelGGL(k_fu<1>, dim3(blocks), dim3(64), 0, st, U, r, tw, FU);
-  return hipGetLastError();
-}
-
-hipError_t launch_fltu(const float2* H, const float2* U, int n, int q, int r, float2* Tc, const int* skip,
-                       hipStream_t st) {
-  (void)hipGetLastError();
-#define FLTU_CALL(RR) hipLaunchKernelGGL(k_fltu<RR>, dim3(q), dim3(kFThreads), 0, st, H, U, n, r, Tc, skip)
-  FR_SWITCH(fr_bucket(r), FLTU_CALL)
-#undef FLTU_CALL
-  return hipGetLastError();
-}
-
-hipError_t launch_fqr(const FQRArgs& a, hipStream_t st) {
-  (void)hipGetLastError();
-#define FQR_CALL(RR) hipLaunchKernelGGL(k_fqr<RR>, dim3(1), dim3(kFThreads), 0, st, a)
-  FR_SWITCH(fr_bucket(a.r), FQR_CALL)
-#undef FQR_CALL
-  return hipGetLastError();
-}
-
-hipError_t launch_fgrad_gd(const float2* H, const float2* B, const float2* U, int n, int q, int r, float2* Gsum,
-                           double2* part, const int* skip, hipStream_t st) {
-  (void)hipGetLastError();
-#define FGD_CALL(RR) \
-  hipLaunchKernelGGL(k_fgrad_gd<RR>, dim3((n + 255) / 256), dim3(kFThreads), 0, st, H, B, U, n, q, r, Gsum, part, skip)
-  FR_SWITCH(fr_bucket(r), FGD_CALL)
-#undef FGD_CALL
-  return hipGetLastError();
-}
-
-hipError_t launch_fqr_gd(const FQRArgs& a, hipStream_t st) {
-  const int nb = (a.n + 255) / 256;
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(k_fqr_a, dim3(1), dim3(256), 0, st, a);
-#define FQB_CALL(RR) hipLaunchKernelGGL(k_fqr_b<RR>, dim3(nb), dim3(256), 0, st, a)
-  FR_SWITCH(fr_bucket(a.r), FQB_CALL)
-#undef FQB_CALL
-  hipLaunchKernelGGL(k_fqr_c, dim3(1), dim3(256), 0, st, a);
-#define FQD_CALL(RR) hipLaunchKernelGGL(k_fqr_d<RR>, dim3(nb), dim3(256), 0, st, a)
-  FR_SWITCH(fr_bucket(a.r), FQD_CALL)
-#undef FQD_CALL
-  if (a.mode == QR_POWER) {
-#define FQE_CALL(RR) hipLaunchKernelGGL(k_fqr_e<RR>, dim3(nb), dim3(256), 0, st, a)
-    FR_SWITCH(fr_bucket(a.r), FQE_CALL)
-#undef FQE_CALL
-    hipLaunchKernelGGL(k_fqr_f, dim3(1), dim3(64), 0, st, a);
-  }
   return hipGetLastError();
 }
 

@@ -4,8 +4,6 @@
 
 namespace altg {
 
-enum { QR_GD = 0, QR_POWER = 1, QR_ORTH = 2 };
-
 // The U update of a GDmin iteration (k_urows, k_uapply; with KS > 1, at most 16, k_ugrad before them).
 struct UpdArgs {
   int n, q, r, KS;
@@ -143,36 +141,51 @@ struct FColArgs {
   int* flags;            // q
 };
 
-struct FQRArgs {
-  int n, r, q, mode;
-  const float2* G;       // n x r: grad_U f (GD) or L_0 L_0^H U (POWER)
+// The U update of a GDmin iteration of the Fourier form (k_frows, k_fapply).
+struct FUpdArgs {
+  int n, q, r;
+  const float2* H;       // q x n
+  const float2* B;       // q x r
+  float2* G;             // n x r: grad_U f
   float2* U;
   float2* Uprev;
-  float2* Utmp;
+  double* part;          // fupd_part_doubles
+  int* upd;              // whether eta was known (set by k_frows)
   Ctl* ctl;
-  double eta_c, power_tol;
+  double eta_c;
   const double* colrr;
   const int* colflags;
   double* rlog;
   int rlog_len;
-  double2* part;         // over many workgroups: per-block partial Grams (nb x 3 r^2); POWER also
-                         // the per-block change sums after nb r^2
-  double2* rinv;         // R1^{-1}, R2^{-1} (2 r^2)
-  int nb;                // 256-row blocks of n
+};
+
+// The spectral start of the Fourier form in one launch (k_fsub); as SubArgs.
+struct FSubArgs {
+  const float2* L0t;     // q x n
+  float2* start;
+  float2* U;
+  float2* V;             // may be start
+  float2* T;             // q x r
+  float2* gpart;         // KS x n x r
+  double* part;          // fupd_part_doubles
+  int n, q, r, KS, iters;
+  double tol;
+  Ctl* ctl;
+  int* bar;
+  int* stuck;
 };
 
 size_t fcol_lds_bytes(int rho, int r, int n, int m, int n1, int n2);
 hipError_t launch_fu_gen(const float2* U, int n, int r, int n1, int n2, const float2* tw, float2* FU,
                          hipStream_t st);
 hipError_t launch_ftwiddle_gen(float2* tw, int n1, int n2, hipStream_t st);
-hipError_t launch_fgrad_gd(const float2* H, const float2* B, const float2* U, int n, int q, int r, float2* Gsum,
-                           double2* part, const int* skip, hipStream_t st);
-hipError_t launch_fqr_gd(const FQRArgs& a, hipStream_t st);
+size_t fupd_part_doubles(int n, int r);
+int fsub_splits(int n, int q);
+hipError_t launch_frows(const FUpdArgs& a, hipStream_t st);
+hipError_t launch_fapply(const FUpdArgs& a, hipStream_t st);
+hipError_t launch_fsub(const FSubArgs& a, hipStream_t st);
 hipError_t launch_fcol(const FColArgs& a, hipStream_t st);
 hipError_t launch_fu(const float2* U, int r, const float2* tw, float2* FU, hipStream_t st);
-hipError_t launch_fltu(const float2* H, const float2* U, int n, int q, int r, float2* Tc, const int* skip,
-                       hipStream_t st);
-hipError_t launch_fqr(const FQRArgs& a, hipStream_t st);
 hipError_t launch_ftwiddle(float2* tw, hipStream_t st);
 hipError_t launch_fbasis(float2* U, int n, int r, hipStream_t st);
 
