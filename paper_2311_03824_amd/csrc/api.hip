@@ -260,6 +260,34 @@ size_t carve_fourier(altgdmin_handle* h, void* base) {
   return (c.off + kAlign - 1) / kAlign * kAlign;
 }
 
+// Waves of the A_k U workgroup: 8 up to 512 columns, 4 above (n = 1000, m = 400,
+// r = 10: 0.065 against 0.094 ms at q = 125, 0.134 against 0.147 at q = 330 in
+// FP32 and 0.159 against 0.204 with BF16 hi + lo planes, 0.157 against 0.161 at
+// q = 500; 0.223 against 0.192 at q = 700).  It sets the order of the cross-wave
+// sums of P_k, so, like the column width, it is a property of the problem (of q,
+// not of the A format), the same in solo and batched launches.
+// ALTGDMIN_AU_WAVES=4|8 forces a width (tests of the 4-wave tuned depths).
+int au_waves(const altgdmin_problem& p) {
+  int w = p.q <= 512 ? 8 : kWaves;
+  if (const char* f = std::getenv("ALTGDMIN_AU_WAVES")) {
+    const int v = std::atoi(f);
+    if (v == 4 || v == 8) w = v;
+  }
+  return w;
+}
+
+// Workgroups per column of the A_k U launch, each with its own rows (at most one per 256:
+// a wave loads 256 rows at once): as many as keep the launch within the 256 CUs, where a CU
+// without a workgroup is lost.  n = 1000, m = 400, r = 10, FP32, two
+// against one, A_k U and column kernel: q = 8 0.109 against 0.126 ms, q = 125 0.128 against 0.145, but q = 200 0.187
+// against 0.179 and q = 400 0.342 against 0.316; n = 4000, m = 1000, q = 64: four 0.667, three
+// 0.700, two 0.727, one 0.897.  It sets the order of the sums of P_k and G_k: a property of the
+// problem, like the width.
+int au_splits(const altgdmin_problem& p) {
+  if (p.a_format == ALTGDMIN_A_PFOURIER || p.m <= 256 || au_waves(p) != 8) return 1;
+  return std::max(1, std::min((p.m + 255) / 256, 256 / p.q));
+}
+
 // Lays the workspace out; with base == nullptr it only measures.
 size_t carve(altgdmin_handle* h, void* base) {
   if (h->prob.a_format == ALTGDMIN_A_PFOURIER) return carve_fourier(h, base);
@@ -268,7 +296,8 @@ size_t carve(altgdmin_handle* h, void* base) {
   Carver c(base);
   h->ctl = c.take<Ctl>(1);
   h->P = c.take<float>(q * m * r);
-  h->Ginv = c.take<double>(q * r * r);
+  const size_t asp = au_splits(p);
+  h->Ginv = c.take<double>(q * asp * r * r);
   h->Tidx = c.take<int>(q * rho);
   h->Tval = c.take<float>(q * rho);
   h->Bt = c.take<float>(q * r);
@@ -284,7 +313,7 @@ size_t carve(altgdmin_handle* h, void* base) {
   h->Tpow = c.take<float>(q * r);
   h->rlog_len = h->par.t_max > 0 ? h->par.t_max : 1;
   h->rlog = c.take<double>(h->rlog_len);
-  h->colbound = c.take<float>(q);
+  h->colbound = c.take<float>(q * asp);
   h->upart = c.take<double>(std::max(upd_part_doubles(p.n, (int)r), sub_part_doubles(p.n, (int)r)));
   h->upd = c.take<int>(1);
   if (p.r == 0) h->rank_ws = c.take<unsigned char>(rank_scratch(nullptr, rank_shape(p.n, p.q, p.m)).bytes);
@@ -383,22 +412,6 @@ int choose_col_waves(const altgdmin_problem& p, bool mixed) {
   return w;
 }
 
-// Waves of the A_k U workgroup: 8 up to 512 columns, 4 above (n = 1000, m = 400,
-// r = 10: 0.065 against 0.094 ms at q = 125, 0.134 against 0.147 at q = 330 in
-// FP32 and 0.159 against 0.204 with BF16 hi + lo planes, 0.157 against 0.161 at
-// q = 500; 0.223 against 0.192 at q = 700).  It sets the order of the cross-wave
-// sums of P_k, so, like the column width, it is a property of the problem (of q,
-// not of the A format), the same in solo and batched launches.
-// ALTGDMIN_AU_WAVES=4|8 forces a width (tests of the 4-wave tuned depths).
-int au_waves(const altgdmin_problem& p) {
-  int w = p.q <= 512 ? 8 : kWaves;
-  if (const char* f = std::getenv("ALTGDMIN_AU_WAVES")) {
-    const int v = std::atoi(f);
-    if (v == 4 || v == 8) w = v;
-  }
-  return w;
-}
-
 ColArgs col_args(const altgdmin_handle* h) {
   const altgdmin_problem& p = h->prob;
   ColArgs a;
@@ -420,6 +433,7 @@ ColArgs gd_col_args(const altgdmin_handle* h) {
   ColArgs a = col_args(h);
   a.tau = h->par.tau; a.project = 1; a.has_support = 1; a.tail = TAIL_LSGRAD;
   a.bound = h->colbound;
+  a.splits = au_splits(h->prob);
   return a;
 }
 
@@ -434,6 +448,7 @@ AUArgs gd_au_args(const altgdmin_handle* h, const float* U) {
   a.seed = p.a_seed; a.table = p.normal_table;
   a.waves = au_waves(p);
   a.bound = h->colbound;
+  a.splits = au_splits(p);
   return a;
 }
 
@@ -1294,16 +1309,14 @@ int plan_group(altgdmin_handle* const* hs, int count, GroupPlan& g) {
     ab.waves = aw;
     cb.inst = nc;
     cb.waves = cw;
-    for (int k = 0; k < p.q; ++k) {
-      ab.map.push_back(make_int2(i, k));
-      cb.map.push_back(make_int2(i, k));
-    }
+    for (int k = 0; k < p.q * au.splits; ++k) ab.map.push_back(make_int2(i, k));
+    for (int k = 0; k < p.q; ++k) cb.map.push_back(make_int2(i, k));
     for (int jb = 0; jb < (p.n + 63) / 64; ++jb) {
       g.row_map.push_back(make_int2(i, jb));
       for (int ks = 0; ks < h->KSu && h->KSu > 1; ++ks) g.grad_map.push_back(make_int4(i, jb, ks, 0));
     }
     for (int jb = 0; jb < uapply_blocks(p.n); ++jb) g.app_map.push_back(make_int2(i, jb));
-    ab.lds = std::max(ab.lds, AULayout(p.m, p.r, phx, aw).total);
+    ab.lds = std::max(ab.lds, AULayout(au_split_rows(p.m, au.splits), p.r, phx, aw).total);
     cb.lds = std::max(cb.lds, ColLayout(p.n, p.m, p.r, p.rho, 1, phx, cw).total);
   }
   size_t o = 0;
@@ -1456,6 +1469,14 @@ int altgdmin_op_au(const altgdmin_problem* prob, const float* U, float* P, doubl
   au.gate = nullptr; au.gate_want = 0;
   au.seed = prob->a_seed; au.table = prob->normal_table;
   au.waves = au_waves(*prob);   // the width the solver takes for this problem
+  au.splits = au_splits(*prob);   // and the row splits, so the same bits
+  if (au.splits > 1) {
+    AUArgs rows = au;
+    rows.Ginv = nullptr;
+    HIPCHK(launch_au(fmt_of(prob), rows, static_cast<hipStream_t>(stream)));
+    HIPCHK(launch_gram(au, static_cast<hipStream_t>(stream)));
+    return ALTGDMIN_OK;
+  }
   HIPCHK(launch_au(fmt_of(prob), au, static_cast<hipStream_t>(stream)));
   return ALTGDMIN_OK;
 }

@@ -71,6 +71,8 @@ struct ColArgs {
   int waves;                // waves of the column workgroup: 4 (also for 0), 8 or 16
   const float* bound;       // optional q: an upper bound of every ||(A_k)_j|| (A_k U kernel); lets a step that
                             // provably keeps its support read the support columns alone
+  int splits;               // row splits of the A_k U launch (0 and 1: none).  Above 1, Ginv holds the Gram of every
+                            // split (q x splits x r x r) and bound its part (q x splits): this kernel adds and inverts
 };
 
 struct AUArgs {
@@ -88,7 +90,20 @@ struct AUArgs {
   const float* table;       // Philox form: normal table (kNormalTable FP32)
   int waves;                // waves per workgroup: 8 (at most 512 columns) or 4 (0 reads as 4)
   float* bound;             // optional q: receives an upper bound of the column norms of A_k
+  int splits;               // workgroups per column, each with its own rows (0 and 1: one); above 1 as in ColArgs
 };
+
+// Rows of a split of the A_k U launch: whole 4-row chunks.
+__host__ __device__ inline int au_split_rows(int m, int splits) {
+  return splits > 1 ? 4 * (((m + 3) / 4 + splits - 1) / splits) : m;
+}
+
+// Orders one wave's LDS accesses: they complete in program order, so only the
+// compiler has to keep them there.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
 
 // ---------------------------------------------------------------- wave reductions
 // Butterfly sums: every lane ends with the same, bitwise identical total.
@@ -344,53 +359,60 @@ __device__ __forceinline__ float get4(float4 v, int e) {
   return e == 0 ? v.x : (e == 1 ? v.y : (e == 2 ? v.z : v.w));
 }
 
-// G^{-1} of an SPD r x r FP64 matrix G (row-major, r <= 16) by Gauss-Jordan
-// elimination without pivoting (an SPD matrix has positive pivots and needs
-// none), by one wave with no barriers: the wave's LDS accesses complete in
-// order, and each step reads every entry it needs before it writes.  W (LDS,
-// 2 r^2 doubles) holds [G | I]; step k scales row k by 1 / W[k][k] and takes
-// W[i][k] times it from every other row; the right half ends as G^{-1}, copied
-// to Ginv.  Returns false, with the identity in Ginv, when a pivot is not
-// positive (or not a number); the result is the same on every lane.  One
-// reciprocal per step and a chain of r steps, with the other waves idle: the
-// A_k U launch at n = q = 1000, m = 400, r = 10 went from 0.269 to 0.262 ms
-// against a workgroup-wide Cholesky with two triangular solves (which chain r
-// square roots and 3r divisions under barriers).
+// 1 / x for positive normal x: the hardware estimate and two Newton steps.
+__device__ __forceinline__ double fast_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(y, fma(-x, y, 1.0), y);
+  return fma(y, fma(-x, y, 1.0), y);
+}
+
+// G^{-1} of an SPD r x r FP64 matrix G (LDS, row-major, r <= 16) by in-place
+// Gauss-Jordan elimination without pivoting (an SPD matrix has positive pivots and
+// needs none), by one wave.  A lane keeps up to 4 entries; step k exchanges row and
+// column k through W (LDS, 4 r doubles, two sets in turn), so a step is one LDS
+// round trip, one reciprocal and one multiply-add deep.  Ginv (LDS) may be G.  Returns
+// false, with the identity in Ginv, when a pivot is not positive (or not a number);
+// the result is the same on every lane.  The other waves idle meanwhile: against
+// [G | I] in LDS, with a division a step, 2 us less of the column kernel at r = 10.
 __device__ inline bool wave_spd_inverse(const double* G, double* W, double* Ginv, int r) {
-  const int lane = threadIdx.x & 63, w2 = 2 * r, ne = r * w2;   // ne <= 512: at most 8 entries per lane
-  for (int e = lane; e < ne; e += 64) {
-    const int i = e / w2, c = e - i * w2;
-    W[e] = c < r ? G[i * r + c] : (c - r == i ? 1.0 : 0.0);
+  const int lane = threadIdx.x & 63, rr = r * r;
+  int ri[4], ci[4];
+  double v[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int e = lane + 64 * t;
+    ri[t] = e < rr ? e / r : r;
+    ci[t] = e < rr ? e - ri[t] * r : r;
+    v[t] = e < rr ? G[e] : 0.0;
   }
   bool ok = true;
-  for (int k = 0; k < r && ok; ++k) {
-    const double piv = W[k * w2 + k];
+  for (int k = 0; k < r; ++k) {
+    double* row = W + (k & 1) * 2 * r;
+    double* col = row + r;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (ri[t] == k) row[ci[t]] = v[t];
+      if (ci[t] == k) col[ri[t]] = v[t];
+    }
+    wave_lds_fence();
+    const double piv = row[k];
     if (!(piv > 0.0)) {
       ok = false;
       break;
     }
-    const double inv = 1.0 / piv;
-    double nv[8];
+    const double inv = fast_rcp(piv);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int e = lane + 64 * t;
-      nv[t] = 0.0;
-      if (e < ne) {
-        const int i = e / w2, c = e - i * w2;
-        const double rk = W[k * w2 + c] * inv;   // the new row k
-        nv[t] = i == k ? rk : fma(-W[i * w2 + k], rk, W[e]);
+    for (int t = 0; t < 4; ++t) {
+      if (ri[t] < r) {
+        const double rk = ci[t] == k ? inv : row[ci[t]] * inv, c = col[ri[t]];
+        v[t] = ri[t] == k ? rk : fma(-c, rk, ci[t] == k ? 0.0 : v[t]);
       }
     }
+  }
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int e = lane + 64 * t;
-      if (e < ne) W[e] = nv[t];
-    }
-  }
-  for (int e = lane; e < r * r; e += 64) {
-    const int i = e / r, c = e - i * r;
-    Ginv[e] = ok ? W[i * w2 + r + c] : (i == c ? 1.0 : 0.0);
-  }
+  for (int t = 0; t < 4; ++t)
+    if (ri[t] < r) Ginv[ri[t] * r + ci[t]] = ok ? v[t] : (ri[t] == ci[t] ? 1.0 : 0.0);
+  wave_lds_fence();
   return ok;
 }
 
@@ -446,7 +468,7 @@ struct AULayout {
     P = o;     o = align16(o + (pb > ust ? pb : ust));
     gpart = o; o = align16(o + 4 * 8 * (size_t)kThreads);
     G = o;     o = align16(o + 8 * (size_t)r * r);
-    W = o;     o = align16(o + 16 * (size_t)r * r);   // [G | I], r x 2r, for the inverse
+    W = o;     o = align16(o + 16 * (size_t)r * r);   // scratch of the inverse
     Gi = o;    o = align16(o + 8 * (size_t)r * r);
     tab = o;   o = align16(o + (philox ? 4 * (size_t)kNormalTable : 0));
     total = o;

@@ -622,19 +622,41 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     }
   }
 
+  const bool split = a.project && a.splits > 1;
+  if (split && wave == 0) {   // G_k from the row splits; its inverse below, beside the other waves' loads
+    const double* Gk = a.Ginv + (long long)k * a.splits * r * r;
+    double g[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) g[t] = lane + 64 * t < r * r ? Gk[lane + 64 * t] : 0.0;
+    for (int s = 1; s < a.splits; ++s)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) g[t] += lane + 64 * t < r * r ? Gk[s * r * r + lane + 64 * t] : 0.0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (lane + 64 * t < r * r) Gi[lane + 64 * t] = g[t];
+  }
   for (int j = tid; j < n; j += kT) sd[j] = 0.f;
   for (int w = tid; w < nwords; w += kT) inT[w] = 0u;
   if (a.project) {
     const float* Pk = a.P + (long long)k * m * r;
     if (lay.p_in_lds) {   // consecutive threads take consecutive columns of a row: coalesced, spread over the banks
       const int mq = lay.mq;
-      for (int t = tid; t < mq * r; t += kT) {
+      const int first = split ? 64 : 0;
+      for (int t = tid - first; t < mq * r; t += kT - first) {
+        if (t < 0) break;
         const int i = t / r, c = t - i * r;
         Pl[c * mq + i] = i < m ? Pk[t] : 0.f;
       }
     }
-    const double* Gk = a.Ginv + (long long)k * r * r;
-    for (int t = tid; t < r * r; t += kT) Gi[t] = Gk[t];
+    if (a.splits <= 1) {
+      const double* Gk = a.Ginv + (long long)k * r * r;
+      for (int t = tid; t < r * r; t += kT) Gi[t] = Gk[t];
+    } else if (wave == 0) {
+      wave_lds_fence();
+      // its scratch in wpart (32 r bytes; splits take m > 256, so there are at least 4 KiB)
+      const bool spd = wave_spd_inverse(Gi, reinterpret_cast<double*>(wpart), Gi, r);
+      if (!spd && lane == 0 && a.flags) atomicOr(&a.flags[k], 2);
+    }
   }
   __syncthreads();
   // A start support must hold rho distinct in-range indices in ascending order
@@ -689,7 +711,15 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   // mixed form, and at q = 125 from 0.173 to 0.105.  Above rho = n / 4 the support
   // columns are no longer a small part of a pass, and their list needs 2 rho words
   // of g's LDS.
-  const float bnd = a.bound && a.project && 4 * rho <= n ? a.bound[k] : 0.f;
+  float bnd = 0.f;
+  if (a.bound && a.project && 4 * rho <= n) {
+    if (a.splits <= 1) {
+      bnd = a.bound[k];
+    } else {
+      for (int s = 0; s < a.splits; ++s) bnd += a.bound[k * a.splits + s];
+      bnd = kBoundSlack * sqrtf(bnd);
+    }
+  }
   const bool screen = bnd > 0.f && isfinite(bnd);
   int* list = reinterpret_cast<int*>(gl);   // rho entries, then the rho values of g on T (2 rho <= n)
   float* gT = gl + rho;
@@ -906,7 +936,50 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(col_min_
 
 // ---------------------------------------------------------------- k_au
 
-// One column k of A_k U by a workgroup of W waves.  Waves split the 256-row
+// G = P^T P in FP64 over m rows into Gl (r x r), by the first 256 threads of a
+// workgroup; pval(i, c) reads P.  Thread (blk, part) accumulates the 2 x 2 block
+// (2ba .. 2ba+1) x (2bb .. 2bb+1), ba <= bb, over rows part, part + parts, ...;
+// the parts are then added in order.  Columns beyond r read as zero.
+template <class PV>
+__device__ __forceinline__ void au_gram(PV pval, int m, int r, double* gpart, double* Gl) {
+  const int tid = threadIdx.x;
+  const int RB = (r + 1) >> 1;
+  const int nb = RB * (RB + 1) / 2;
+  const int parts = kThreads / nb;
+  if (tid < kThreads) {
+    const int blk = tid % nb, part = tid / nb;
+    int ba = 0, base = 0;
+    while (blk >= base + (RB - ba)) { base += RB - ba; ++ba; }
+    const int bb = ba + (blk - base);
+    const int c0 = 2 * ba, c1 = 2 * ba + 1, d0 = 2 * bb, d1 = 2 * bb + 1;
+    double g00 = 0.0, g01 = 0.0, g10 = 0.0, g11 = 0.0;
+    if (part < parts)
+      for (int i = part; i < m; i += parts) {
+        const double x0 = pval(i, c0), x1 = c1 < r ? pval(i, c1) : 0.0;
+        const double y0 = pval(i, d0), y1 = d1 < r ? pval(i, d1) : 0.0;
+        g00 = fma(x0, y0, g00); g01 = fma(x0, y1, g01);
+        g10 = fma(x1, y0, g10); g11 = fma(x1, y1, g11);
+      }
+    gpart[4 * tid] = g00; gpart[4 * tid + 1] = g01; gpart[4 * tid + 2] = g10; gpart[4 * tid + 3] = g11;
+  }
+  __syncthreads();
+  if (tid < 4 * nb) {
+    const int blk = tid >> 2, w = tid & 3;
+    int ba = 0, base = 0;
+    while (blk >= base + (RB - ba)) { base += RB - ba; ++ba; }
+    const int bb = ba + (blk - base);
+    const int ra = 2 * ba + (w >> 1), rb = 2 * bb + (w & 1);
+    double t = 0.0;
+    for (int p = 0; p < parts; ++p) t += gpart[4 * (p * nb + blk) + w];
+    if (ra < r && rb < r) {
+      Gl[ra * r + rb] = t;
+      Gl[rb * r + ra] = t;
+    }
+  }
+  __syncthreads();
+}
+
+// Column k of A_k U (or the rows of one of its splits) by a workgroup of W waves.  Waves split the 256-row
 // chunks of A_k first and the columns j second: with nch = ceil(m / 256) chunks,
 // wave w takes chunk w / js and columns j = w % js, w % js + js, ... where
 // js = max(1, W / nch); each lane holds 4 rows x R accumulators.  Partial P_k of
@@ -915,12 +988,17 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(col_min_
 // problem (8 waves up to 512 columns), the same in a solo and a batched launch.
 // The Gram and the inverse use the first 4 waves whatever W.
 template <int FMT, int R, int AUD, int POL = POL_STREAM, int W = kWaves>
-__device__ __forceinline__ void au_body(const AUArgs& a, int k, unsigned char* smem) {
+__device__ __forceinline__ void au_body(const AUArgs& a, int blk, unsigned char* smem) {
   constexpr int kT = 64 * W;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-  const int n = a.n, m = a.m, r = a.r;
-  const AULayout lay(m, r, FMT == FMT_PHILOX, W);
-  float* Pk = a.P + (long long)k * m * r;
+  const int n = a.n, r = a.r;
+  const int splits = W > kWaves && a.splits > 1 ? a.splits : 1;
+  const int k = splits > 1 ? blk / splits : blk;
+  // this workgroup's rows: row0 .. row0 + m - 1
+  const int srows = au_split_rows(a.m, splits), row0 = (blk - k * splits) * srows;
+  const int m = a.m - row0 < srows ? (a.m > row0 ? a.m - row0 : 0) : srows;
+  const AULayout lay(srows, r, FMT == FMT_PHILOX, W);
+  float* Pk = a.P + ((long long)k * a.m + row0) * r;
   float* Pp = lay.p_in_lds ? reinterpret_cast<float*>(smem + lay.P) : Pk;
   double* gpart = reinterpret_cast<double*>(smem + lay.gpart);
   double* Gl = reinterpret_cast<double*>(smem + lay.G);
@@ -937,9 +1015,9 @@ __device__ __forceinline__ void au_body(const AUArgs& a, int k, unsigned char* s
   const int js = W / nch > 1 ? W / nch : 1;
   const int cs = wave / js, jw = wave % js;
   const bool active = cs < nch;
-  const int ch = lane + 64 * cs;
-  const int chmax = (m - 1) >> 2;
-  const int chc = ch < chmax ? ch : chmax;
+  const int ch = lane + 64 * cs;   // chunk of this workgroup's rows
+  const int chmax = (row0 + m - 1) >> 2;
+  const int chc = (row0 >> 2) + ch < chmax ? (row0 >> 2) + ch : chmax;   // this workgroup's rows: always a legal address
   const int nvr = m - 4 * ch;
   const int nv = nvr < 0 ? 0 : (nvr > 4 ? 4 : nvr);
 
@@ -1050,7 +1128,7 @@ __device__ __forceinline__ void au_body(const AUArgs& a, int k, unsigned char* s
       s += mx;
     }
     s = wave_sum(s);
-    if (lane == 0) a.bound[k] = kBoundSlack * sqrtf(s);
+    if (lane == 0) a.bound[blk] = splits > 1 ? s : kBoundSlack * sqrtf(s);
   }
 
   // partial P of the waves sharing a chunk, added in column-split order.  In
@@ -1093,43 +1171,13 @@ __device__ __forceinline__ void au_body(const AUArgs& a, int k, unsigned char* s
     return (double)(lay.p_in_lds ? Pp[c * mp + i] : Pp[i * r + c]);
   };
 
-  // G = P^T P in FP64.  Thread (blk, part) accumulates the 2 x 2 block
-  // (2ba .. 2ba+1) x (2bb .. 2bb+1), ba <= bb, over rows part, part + parts, ...;
-  // the parts are then added in order.  Columns beyond r read as zero.
-  const int RB = (r + 1) >> 1;
-  const int nb = RB * (RB + 1) / 2;
-  const int parts = kThreads / nb;
-  if (tid < kThreads) {
-    const int blk = tid % nb, part = tid / nb;
-    int ba = 0, base = 0;
-    while (blk >= base + (RB - ba)) { base += RB - ba; ++ba; }
-    const int bb = ba + (blk - base);
-    const int c0 = 2 * ba, c1 = 2 * ba + 1, d0 = 2 * bb, d1 = 2 * bb + 1;
-    double g00 = 0.0, g01 = 0.0, g10 = 0.0, g11 = 0.0;
-    if (part < parts)
-      for (int i = part; i < m; i += parts) {
-        const double x0 = pval(i, c0), x1 = c1 < r ? pval(i, c1) : 0.0;
-        const double y0 = pval(i, d0), y1 = d1 < r ? pval(i, d1) : 0.0;
-        g00 = fma(x0, y0, g00); g01 = fma(x0, y1, g01);
-        g10 = fma(x1, y0, g10); g11 = fma(x1, y1, g11);
-      }
-    gpart[4 * tid] = g00; gpart[4 * tid + 1] = g01; gpart[4 * tid + 2] = g10; gpart[4 * tid + 3] = g11;
+  au_gram(pval, m, r, gpart, Gl);
+  if (splits > 1) {   // the column kernel, or k_gram, adds the splits' Grams
+    if (!a.Ginv) return;
+    double* Gk = a.Ginv + (long long)blk * r * r;
+    for (int t = tid; t < r * r; t += kT) Gk[t] = Gl[t];
+    return;
   }
-  __syncthreads();
-  if (tid < 4 * nb) {
-    const int blk = tid >> 2, w = tid & 3;
-    int ba = 0, base = 0;
-    while (blk >= base + (RB - ba)) { base += RB - ba; ++ba; }
-    const int bb = ba + (blk - base);
-    const int ra = 2 * ba + (w >> 1), rb = 2 * bb + (w & 1);
-    double t = 0.0;
-    for (int p = 0; p < parts; ++p) t += gpart[4 * (p * nb + blk) + w];
-    if (ra < r && rb < r) {
-      Gl[ra * r + rb] = t;
-      Gl[rb * r + ra] = t;
-    }
-  }
-  __syncthreads();
   // G^{-1} by wave 0 (tid 0, which raises the flag, is in it)
   if (wave == 0) {
     const bool spd = wave_spd_inverse(Gl, Wl, Gil, r);
@@ -1161,6 +1209,10 @@ constexpr int default_aud(int R, int FMT = FMT_F32) {
 // default depths keep more waves resident.  The depth only moves loads: the
 // arithmetic, and so every bit, is the same.
 constexpr int deep_aud(int R, int = FMT_F32) { return R <= 4 ? 4 : 3; }
+// 8-wave workgroups: six loads in flight up to R = 10 (one workgroup per CU: 1.13 against 1.16 ms
+// at n = 16384, q = 100, m = 1000 in two splits; above, the registers do not hold them).
+// The Philox form has no loads: three keep its loop short (0.17 against 0.20 ms at n = 777, q = 333, m = 301, r = 7).
+constexpr int wide_aud(int R, int fmt) { return R <= 10 && fmt != FMT_PHILOX ? 6 : (R <= 4 ? 4 : 3); }
 constexpr int kDeepAuColumns = 256;
 
 template <int FMT, int R, int AUD = default_aud(R, FMT), int POL = POL_STREAM, int W = kWaves>
@@ -1242,15 +1294,15 @@ static const au_fn kAUDeep[3][kRMax / 2] = {AUD_ROW(FMT_F32), AUD_ROW(FMT_BF16X2
 static const aug_fn kAUGrpDeep[3][kRMax / 2] = {AUGD_ROW(FMT_F32), AUGD_ROW(FMT_BF16X2), AUGD_ROW(FMT_BF16HI)};
 // 8-wave workgroups (problems of at most 512 columns, with the deep depths; every
 // format, so that the width, and with it the bits, do not depend on how A is held)
-#define AU8_ROW(F) {k_au<F, 2, deep_aud(2), POL_STREAM, 8>, k_au<F, 4, deep_aud(4), POL_STREAM, 8>,     \
-                    k_au<F, 6, deep_aud(6), POL_STREAM, 8>, k_au<F, 8, deep_aud(8), POL_STREAM, 8>,     \
-                    k_au<F, 10, deep_aud(10), POL_STREAM, 8>, k_au<F, 12, deep_aud(12), POL_STREAM, 8>, \
-                    k_au<F, 14, deep_aud(14), POL_STREAM, 8>, k_au<F, 16, deep_aud(16), POL_STREAM, 8>}
+#define AU8_ROW(F) {k_au<F, 2, wide_aud(2, F), POL_STREAM, 8>, k_au<F, 4, wide_aud(4, F), POL_STREAM, 8>,     \
+                    k_au<F, 6, wide_aud(6, F), POL_STREAM, 8>, k_au<F, 8, wide_aud(8, F), POL_STREAM, 8>,     \
+                    k_au<F, 10, wide_aud(10, F), POL_STREAM, 8>, k_au<F, 12, wide_aud(12, F), POL_STREAM, 8>, \
+                    k_au<F, 14, wide_aud(14, F), POL_STREAM, 8>, k_au<F, 16, wide_aud(16, F), POL_STREAM, 8>}
 static const au_fn kAU8[4][kRMax / 2] = {AU8_ROW(FMT_F32), AU8_ROW(FMT_BF16X2), AU8_ROW(FMT_BF16HI), AU8_ROW(FMT_PHILOX)};
-#define AUG8_ROW(F) {k_au_grp<F, 2, POL_STREAM, deep_aud(2), 8>, k_au_grp<F, 4, POL_STREAM, deep_aud(4), 8>,     \
-                     k_au_grp<F, 6, POL_STREAM, deep_aud(6), 8>, k_au_grp<F, 8, POL_STREAM, deep_aud(8), 8>,     \
-                     k_au_grp<F, 10, POL_STREAM, deep_aud(10), 8>, k_au_grp<F, 12, POL_STREAM, deep_aud(12), 8>, \
-                     k_au_grp<F, 14, POL_STREAM, deep_aud(14), 8>, k_au_grp<F, 16, POL_STREAM, deep_aud(16), 8>}
+#define AUG8_ROW(F) {k_au_grp<F, 2, POL_STREAM, wide_aud(2, F), 8>, k_au_grp<F, 4, POL_STREAM, wide_aud(4, F), 8>,     \
+                     k_au_grp<F, 6, POL_STREAM, wide_aud(6, F), 8>, k_au_grp<F, 8, POL_STREAM, wide_aud(8, F), 8>,     \
+                     k_au_grp<F, 10, POL_STREAM, wide_aud(10, F), 8>, k_au_grp<F, 12, POL_STREAM, wide_aud(12, F), 8>, \
+                     k_au_grp<F, 14, POL_STREAM, wide_aud(14, F), 8>, k_au_grp<F, 16, POL_STREAM, wide_aud(16, F), 8>}
 static const aug_fn kAUGrp8[4][kRMax / 2] = {AUG8_ROW(FMT_F32), AUG8_ROW(FMT_BF16X2), AUG8_ROW(FMT_BF16HI),
                                              AUG8_ROW(FMT_PHILOX)};
 
@@ -1285,11 +1337,12 @@ hipError_t launch_au(int fmt, const AUArgs& a, hipStream_t st, int pol) {
     if (e != hipErrorNotSupported) return e;
   }
   const int ri = (a.r + 1) / 2 - 1, w = au_width(a.waves);
-  const AULayout lay(a.m, a.r, fmt == FMT_PHILOX, w);
+  const int splits = w == 8 && a.splits > 1 ? a.splits : 1;
+  const AULayout lay(au_split_rows(a.m, splits), a.r, fmt == FMT_PHILOX, w);
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
   const au_fn f = w == 8 ? kAU8[fmt][ri]
                          : ((fmt != FMT_PHILOX && a.q <= kDeepAuColumns) ? kAUDeep[fmt][ri] : kAUTable[fmt][ri]);
-  hipLaunchKernelGGL(f, dim3(a.q), dim3(64 * w), lay.total, st, a);
+  hipLaunchKernelGGL(f, dim3(a.q * splits), dim3(64 * w), lay.total, st, a);
   return hipGetLastError();
 }
 
@@ -1324,6 +1377,33 @@ hipError_t launch_au_grp(int fmt, int rmax, int waves, const AUArgs* tab, const 
                           : ((fmt != FMT_PHILOX && blocks <= kDeepAuColumns) ? kAUGrpDeep[fmt][ri]
                                                                               : kAUGrpTable[fmt][ri]);
   hipLaunchKernelGGL(f, dim3(blocks), dim3(64 * w), lds, st, tab, map);
+  return hipGetLastError();
+}
+
+// G_k of a split A_k U launch from P_k alone, split by split in the column kernel's order, and
+// its inverse: for the step-level entry point, whose caller has no room for the splits'
+// Grams.
+__global__ __launch_bounds__(kThreads) void k_gram(AUArgs a) {
+  __shared__ double gpart[4 * kThreads], G[kRMax * kRMax], sum[kRMax * kRMax], Wl[4 * kRMax];
+  const int tid = threadIdx.x, k = blockIdx.x, r = a.r, rows = au_split_rows(a.m, a.splits);
+  for (int s = 0; s < a.splits; ++s) {
+    const int row0 = s * rows, m = a.m - row0 < rows ? (a.m > row0 ? a.m - row0 : 0) : rows;
+    const float* P = a.P + ((long long)k * a.m + row0) * r;
+    au_gram([&](int i, int c) -> double { return (double)P[(long long)i * r + c]; }, m, r, gpart, G);
+    for (int t = tid; t < r * r; t += kThreads) sum[t] = s == 0 ? G[t] : sum[t] + G[t];
+    __syncthreads();
+  }
+  if (tid < 64) {
+    const bool spd = wave_spd_inverse(sum, Wl, sum, r);
+    if (!spd && tid == 0 && a.flags) a.flags[k] |= 2;
+  }
+  __syncthreads();
+  for (int t = tid; t < r * r; t += kThreads) a.Ginv[(long long)k * r * r + t] = sum[t];
+}
+
+hipError_t launch_gram(const AUArgs& a, hipStream_t st) {
+  (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
+  hipLaunchKernelGGL(k_gram, dim3(a.q), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1545,15 +1625,15 @@ static const aug_fn3 kAUGrpCached[2][3][kRMax / 2] = {
     {AUGC_F(FMT_F32, default_aud), AUGC_F(FMT_BF16X2, default_aud), AUGC_F(FMT_BF16HI, default_aud)},
     {AUGC_F(FMT_F32, deep_aud), AUGC_F(FMT_BF16X2, deep_aud), AUGC_F(FMT_BF16HI, deep_aud)}};
 // 8-wave workgroups (deep depths), as in the streaming tables
-#define AUC8_F(F) {k_au<F, 2, deep_aud(2), POL_CACHED, 8>, k_au<F, 4, deep_aud(4), POL_CACHED, 8>,     \
-                   k_au<F, 6, deep_aud(6), POL_CACHED, 8>, k_au<F, 8, deep_aud(8), POL_CACHED, 8>,     \
-                   k_au<F, 10, deep_aud(10), POL_CACHED, 8>, k_au<F, 12, deep_aud(12), POL_CACHED, 8>, \
-                   k_au<F, 14, deep_aud(14), POL_CACHED, 8>, k_au<F, 16, deep_aud(16), POL_CACHED, 8>}
+#define AUC8_F(F) {k_au<F, 2, wide_aud(2, F), POL_CACHED, 8>, k_au<F, 4, wide_aud(4, F), POL_CACHED, 8>,     \
+                   k_au<F, 6, wide_aud(6, F), POL_CACHED, 8>, k_au<F, 8, wide_aud(8, F), POL_CACHED, 8>,     \
+                   k_au<F, 10, wide_aud(10, F), POL_CACHED, 8>, k_au<F, 12, wide_aud(12, F), POL_CACHED, 8>, \
+                   k_au<F, 14, wide_aud(14, F), POL_CACHED, 8>, k_au<F, 16, wide_aud(16, F), POL_CACHED, 8>}
 static const au_fn3 kAUCached8[3][kRMax / 2] = {AUC8_F(FMT_F32), AUC8_F(FMT_BF16X2), AUC8_F(FMT_BF16HI)};
-#define AUGC8_F(F) {k_au_grp<F, 2, POL_CACHED, deep_aud(2), 8>, k_au_grp<F, 4, POL_CACHED, deep_aud(4), 8>,     \
-                    k_au_grp<F, 6, POL_CACHED, deep_aud(6), 8>, k_au_grp<F, 8, POL_CACHED, deep_aud(8), 8>,     \
-                    k_au_grp<F, 10, POL_CACHED, deep_aud(10), 8>, k_au_grp<F, 12, POL_CACHED, deep_aud(12), 8>, \
-                    k_au_grp<F, 14, POL_CACHED, deep_aud(14), 8>, k_au_grp<F, 16, POL_CACHED, deep_aud(16), 8>}
+#define AUGC8_F(F) {k_au_grp<F, 2, POL_CACHED, wide_aud(2, F), 8>, k_au_grp<F, 4, POL_CACHED, wide_aud(4, F), 8>,     \
+                    k_au_grp<F, 6, POL_CACHED, wide_aud(6, F), 8>, k_au_grp<F, 8, POL_CACHED, wide_aud(8, F), 8>,     \
+                    k_au_grp<F, 10, POL_CACHED, wide_aud(10, F), 8>, k_au_grp<F, 12, POL_CACHED, wide_aud(12, F), 8>, \
+                    k_au_grp<F, 14, POL_CACHED, wide_aud(14, F), 8>, k_au_grp<F, 16, POL_CACHED, wide_aud(16, F), 8>}
 static const aug_fn3 kAUGrpCached8[3][kRMax / 2] = {AUGC8_F(FMT_F32), AUGC8_F(FMT_BF16X2), AUGC8_F(FMT_BF16HI)};
 
 static int cached_width_row(int waves) { return waves == 8 ? 1 : (waves == 0 || waves == kWaves ? 0 : -1); }
@@ -1608,10 +1688,11 @@ hipError_t launch_col_grp_cached(int fmt, int nc, int waves, const ColArgs* tab,
 hipError_t launch_au_cached(int fmt, const AUArgs& a, hipStream_t st) {
   if (fmt < FMT_F32 || fmt > FMT_BF16HI) return hipErrorNotSupported;
   const int ri = (a.r + 1) / 2 - 1, w = a.waves == 8 ? 8 : kWaves;
-  const AULayout lay(a.m, a.r, 0, w);
+  const int splits = w == 8 && a.splits > 1 ? a.splits : 1;
+  const AULayout lay(au_split_rows(a.m, splits), a.r, 0, w);
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
   const au_fn3 f = w == 8 ? kAUCached8[fmt][ri] : kAUCached[a.q <= kDeepAuColumns][fmt][ri];
-  hipLaunchKernelGGL(f, dim3(a.q), dim3(64 * w), lay.total, st, a);
+  hipLaunchKernelGGL(f, dim3(a.q * splits), dim3(64 * w), lay.total, st, a);
   return hipGetLastError();
 }
 

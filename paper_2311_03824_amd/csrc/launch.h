@@ -53,6 +53,7 @@ hipError_t launch_col(int fmt, const ColArgs& a, hipStream_t st, int pol = 0);
 hipError_t launch_col_tuned(int fmt, int ju, const ColArgs& a, hipStream_t st);
 hipError_t launch_au_tuned(int fmt, int aud, const AUArgs& a, hipStream_t st);
 hipError_t launch_au(int fmt, const AUArgs& a, hipStream_t st, int pol = 0);
+hipError_t launch_gram(const AUArgs& a, hipStream_t st);   // Ginv of a split A_k U launch from its P
 bool au_supported(int m, int r);
 hipError_t launch_col_grp(int fmt, int nc, int waves, const ColArgs* tab, const int2* map, int blocks, size_t lds,
                           hipStream_t st, int pol = 0);
@@ -79,7 +80,7 @@ size_t col_lds_accept(int n, int m, int r, int rho, int philox);   // against kC
 hipError_t col_allow_big_lds();
 hipError_t col_allow_big_lds_tuned();    // the autotuned and wide variants
 hipError_t col_allow_big_lds_cached();   // the cached-load variants
-size_t au_lds_bytes(int m, int r, int philox, int waves = kWaves);
+size_t au_lds_bytes(int m, int r, int philox, int waves);
 hipError_t launch_philox_fill(unsigned long long seed, const float* table, int q, int n, int m, long long lda, float* A,
                               hipStream_t st);
 size_t select_lds_bytes(int n, int rho);

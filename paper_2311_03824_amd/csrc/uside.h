@@ -45,19 +45,7 @@ __device__ __forceinline__ int sum_groups(int threads, int cnt, int count) {
   return g > 0 ? g : 1;
 }
 
-// Orders one wave's LDS accesses: they complete in program order, so only the
-// compiler has to keep them there.
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// 1 / x and 1 / sqrt(x) for positive normal x: the hardware estimate and two Newton steps.
-__device__ __forceinline__ double fast_rcp(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(y, fma(-x, y, 1.0), y);
-  return fma(y, fma(-x, y, 1.0), y);
-}
+// 1 / sqrt(x) for positive normal x: the hardware estimate and two Newton steps.
 __device__ __forceinline__ double fast_rsqrt(double x) {
   double y = __builtin_amdgcn_rsq(x);
   y = fma(y, fma(-0.5 * x * y, y, 0.5), y);
