@@ -912,8 +912,20 @@ constexpr int col_min_waves(int fmt, int nc, int ju) {
 }
 
 // Wider workgroups: W / 4 waves per SIMD at least (the workgroup must fit).
+// 8-wave workgroups of two row chunks with 4 columns in flight are for one workgroup per CU: two
+// waves per SIMD.
+constexpr int kColDeepJU = 4;
 constexpr int col_min_waves_w(int fmt, int nc, int ju, int w) {
+  if (w == 8 && nc == 2 && ju == kColDeepJU && fmt != FMT_PHILOX) return 2;
   return col_min_waves(fmt, nc, ju) > w / 4 ? col_min_waves(fmt, nc, ju) : w / 4;
+}
+
+// Launches that give a CU one 8-wave workgroup (at most 256 of them, or LDS for one) of two row
+// chunks take the deep variant: the 128 registers of four waves per SIMD cost 31 spills there, and
+// twice the columns in flight fit (n = 1000, m = 400, r = 10, FP32: 79 -> 74 us at q = 125,
+// 98 -> 91 at 200, 111 -> 104 at 256).
+static inline bool col_deep(int fmt, int nc, const ColArgs& a, size_t lds) {
+  return nc == 2 && a.waves == 8 && fmt <= FMT_BF16HI && (a.q <= 256 || lds > 80 * 1024);
 }
 
 template <int FMT, int NC, int JU = default_ju(NC, kWaves, FMT), int W = kWaves, int POL = POL_STREAM>
@@ -1512,6 +1524,9 @@ static const colg_fn2 kColGrpWide[2][5][kNCMax] = {
      COLGW_F(FMT_BF16MIX, 8)},
     {COLGW16_F(FMT_F32), COLGW16_F(FMT_BF16X2), COLGW16_F(FMT_BF16HI), COLGW16_F(FMT_PHILOX), COLGW16_F(FMT_BF16MIX)}};
 
+static const col_fn2 kColDeep[3] = {k_col<FMT_F32, 2, kColDeepJU, 8>, k_col<FMT_BF16X2, 2, kColDeepJU, 8>,
+                                    k_col<FMT_BF16HI, 2, kColDeepJU, 8>};
+
 bool col_wide_built(int waves, int nc) { return waves == 8 || (waves == 16 && nc <= 2); }
 
 hipError_t launch_col_wide(int fmt, const ColArgs& a, hipStream_t st) {
@@ -1525,7 +1540,8 @@ hipError_t launch_col_wide(int fmt, const ColArgs& a, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  hipLaunchKernelGGL(kColWide[wi][fmt][nc - 1], dim3(a.q), dim3(64 * a.waves), lay.total, st, a);
+  hipLaunchKernelGGL(col_deep(fmt, nc, a, lay.total) ? kColDeep[fmt] : kColWide[wi][fmt][nc - 1], dim3(a.q),
+                     dim3(64 * a.waves), lay.total, st, a);
   return hipGetLastError();
 }
 
@@ -1557,6 +1573,7 @@ static hipError_t raise_lds(const F* fns, size_t count) {
 hipError_t col_allow_big_lds_tuned() {
   hipError_t e = raise_lds(&kColTuned[0][0][0], sizeof(kColTuned) / sizeof(kColTuned[0][0][0]));
   if (e == hipSuccess) e = raise_lds(&kColWide[0][0][0], sizeof(kColWide) / sizeof(kColWide[0][0][0]));
+  if (e == hipSuccess) e = raise_lds(kColDeep, sizeof(kColDeep) / sizeof(kColDeep[0]));
   if (e == hipSuccess) e = raise_lds(&kColGrpWide[0][0][0], sizeof(kColGrpWide) / sizeof(kColGrpWide[0][0][0]));
   return e;
 }
@@ -1605,6 +1622,9 @@ typedef void (*aug_fn3)(const AUArgs*, const int2*);
 static const col_fn3 kColCached[2][5][kNCMax] = {
     {COLC_F(FMT_F32, 4), COLC_F(FMT_BF16X2, 4), COLC_F(FMT_BF16HI, 4), COLC_NONE, COLC_F(FMT_BF16MIX, 4)},
     {COLC_F(FMT_F32, 8), COLC_F(FMT_BF16X2, 8), COLC_F(FMT_BF16HI, 8), COLC_NONE, COLC_F(FMT_BF16MIX, 8)}};
+static const col_fn3 kColCachedDeep[3] = {k_col<FMT_F32, 2, kColDeepJU, 8, POL_CACHED>,
+                                          k_col<FMT_BF16X2, 2, kColDeepJU, 8, POL_CACHED>,
+                                          k_col<FMT_BF16HI, 2, kColDeepJU, 8, POL_CACHED>};
 #define COLGC_F(F, W) {k_col_grp<F, 1, W, POL_CACHED>, k_col_grp<F, 2, W, POL_CACHED>, \
                        k_col_grp<F, 3, W, POL_CACHED>, k_col_grp<F, 4, W, POL_CACHED>}
 static const colg_fn3 kColGrpCached[2][5][kNCMax] = {
@@ -1639,6 +1659,11 @@ static const aug_fn3 kAUGrpCached8[3][kRMax / 2] = {AUGC8_F(FMT_F32), AUGC8_F(FM
 static int cached_width_row(int waves) { return waves == 8 ? 1 : (waves == 0 || waves == kWaves ? 0 : -1); }
 
 hipError_t col_allow_big_lds_cached() {
+  for (const col_fn3 f : kColCachedDeep) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(f),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kColLdsMax);
+    if (e != hipSuccess) return e;
+  }
   for (size_t i = 0; i < sizeof(kColCached) / sizeof(kColCached[0][0][0]); ++i) {
     const col_fn3 f = (&kColCached[0][0][0])[i];
     if (!f) continue;
@@ -1667,7 +1692,8 @@ hipError_t launch_col_cached(int fmt, const ColArgs& a, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  hipLaunchKernelGGL(kColCached[wi][fmt][nc - 1], dim3(a.q), dim3(64 * w), lay.total, st, a);
+  hipLaunchKernelGGL(col_deep(fmt, nc, a, lay.total) ? kColCachedDeep[fmt] : kColCached[wi][fmt][nc - 1], dim3(a.q),
+                     dim3(64 * w), lay.total, st, a);
   return hipGetLastError();
 }
 
