@@ -111,13 +111,12 @@ RankShape rank_shape_complex(int n, int q, int m) {
 }
 
 // Scratch of the automatic rank: the block U and Z = L_0 L_0^T U (n x b), T = L_0^T U
-// (q x b), the FP64 Gram and R^{-1} (b x b), R^{-1} in FP32, the K values, r, a flag.
+// (q x b), the FP64 Gram (b x b), R^{-1} in FP32, the K values, r, a flag.
 struct RankScratch {
   float* Ub;
   float* Z;
   float* T;
   double* W;
-  double* Xinv;
   float* Xf;
   double* sv;
   int* r;
@@ -133,7 +132,6 @@ RankScratch rank_scratch(void* base, const RankShape& sh) {
   s.Z = c.take<float>((size_t)n * b);
   s.T = c.take<float>((size_t)q * b);
   s.W = c.take<double>(b * b);
-  s.Xinv = c.take<double>(b * b);
   s.Xf = c.take<float>(b * b);
   s.sv = c.take<double>(K);
   s.r = c.take<int>(1);
@@ -158,7 +156,7 @@ hipError_t enqueue_rank(const float* L0t, const RankShape& sh, double energy, in
     if (e == hipSuccess) e = launch_rank_mm(true, L0t, n, s.T, b, Z, b, n, b, q, st);   // Z = L_0 T
     for (int pass = 0; pass < 2 && e == hipSuccess; ++pass) {                     // CholeskyQR2: Z -> U -> Z
       e = launch_rank_gram(Z, n, b, s.W, st);
-      if (e == hipSuccess) e = launch_rank_chol(s.W, b, s.Xinv, s.Xf, s.flag, st);
+      if (e == hipSuccess) e = launch_rank_chol(s.W, b, s.Xf, s.flag, st);
       if (e == hipSuccess) e = launch_rank_mm(false, Z, b, s.Xf, b, U, b, n, b, b, st);
       std::swap(U, Z);
     }

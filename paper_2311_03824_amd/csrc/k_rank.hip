@@ -21,92 +21,145 @@ namespace altg {
 
 namespace {
 
-constexpr int kTile = 32;       // output tile of k_rank_mm (kTile x kTile), 256 threads x 4 outputs
-constexpr int kKc = 32;         // contraction chunk staged in LDS
+constexpr int kTile = 32;       // output tile of k_rank_mm (kTile x kTile)
+constexpr int kKc = 64;         // contraction chunk staged in LDS
 constexpr int kGT = 16;         // tile of k_rank_gram (kGT x kGT entries, one per thread)
 constexpr int kGRows = 64;      // rows per LDS stage of k_rank_gram
 
 // C (M x N, row-major, ldc) = A' B with A' = A (M x K, row-major lda) or, with
 // TRANS, A' = A^T where A is K x M row-major (lda); B is K x N row-major (ldb).
-// Each thread accumulates 4 outputs of its column in FP32 over the chunks in order.
+// Four groups of 256 threads take a quarter of every 64-term chunk each, a thread 4 outputs
+// of its column in FP32; the next chunk is loaded meanwhile and the groups' sums are added in
+// order.  At these sizes a launch has a few workgroups and is bound by the latency of
+// its loads and LDS reads (n = 300, q = 200, b = 20: 13 -> 6 us).
 template <bool TRANS>
-__global__ __launch_bounds__(256) void k_rank_mm(const float* __restrict__ A, long long lda,
-                                                 const float* __restrict__ B, long long ldb, float* __restrict__ C,
-                                                 long long ldc, int M, int N, int K) {
-  __shared__ float sa[kKc][kTile + 1];   // sa[kk][i] = A'(i0 + i, k0 + kk)
-  __shared__ float sb[kKc][kTile + 1];   // sb[kk][c] = B(k0 + kk, c0 + c)
-  const int tid = threadIdx.x;
+__global__ __launch_bounds__(1024) void k_rank_mm(const float* __restrict__ A, long long lda,
+                                                  const float* __restrict__ B, long long ldb, float* __restrict__ C,
+                                                  long long ldc, int M, int N, int K) {
+  __shared__ __attribute__((aligned(16))) float sa[kKc][kTile + 4];   // sa[kk][i] = A'(i0 + i, k0 + kk)
+  __shared__ float sb[kKc][kTile + 1];                                // sb[kk][c] = B(k0 + kk, c0 + c)
+  constexpr int kPer = kKc * kTile / 1024, kQ = kKc / 4;
+  const int tid = threadIdx.x, grp = tid >> 8, t8 = tid & 255;
   const int i0 = blockIdx.y * kTile, c0 = blockIdx.x * kTile;
-  const int tc = tid & (kTile - 1), ti = (tid >> 5) * 4;   // this thread: column tc, rows ti .. ti + 3
+  const int tc = t8 & (kTile - 1), ti = (t8 >> 5) * 4;   // this thread: column tc, rows ti .. ti + 3
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < K; k0 += kKc) {
-    for (int e = tid; e < kKc * kTile; e += 256) {
-      const int kk = e / kTile, x = e % kTile;
+  float va[kPer], vb[kPer];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      const int e = tid + 1024 * t;
       // A' tile: consecutive threads read consecutive addresses (along k for A, along i for A^T)
-      const int ii = TRANS ? x : e / kKc;
-      const int kx = TRANS ? kk : e % kKc;
+      const int ii = TRANS ? e % kTile : e / kKc, kx = TRANS ? e / kTile : e % kKc;
       const int gi = i0 + ii, gk = k0 + kx;
-      float v = 0.f;
-      if (gi < M && gk < K) v = TRANS ? A[(long long)gk * lda + gi] : A[(long long)gi * lda + gk];
-      sa[kx][ii] = v;
-      const int bk = k0 + kk, bc = c0 + x;
-      sb[kk][x] = (bk < K && bc < N) ? B[(long long)bk * ldb + bc] : 0.f;
+      va[t] = gi < M && gk < K ? (TRANS ? A[(long long)gk * lda + gi] : A[(long long)gi * lda + gk]) : 0.f;
+      const int bk = k0 + e / kTile, bc = c0 + e % kTile;
+      vb[t] = bk < K && bc < N ? B[(long long)bk * ldb + bc] : 0.f;
+    }
+  };
+  load(0);
+  for (int k0 = 0; k0 < K; k0 += kKc) {
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      const int e = tid + 1024 * t;
+      const int ii = TRANS ? e % kTile : e / kKc, kx = TRANS ? e / kTile : e % kKc;
+      sa[kx][ii] = va[t];
+      sb[e / kTile][e % kTile] = vb[t];
     }
     __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < kKc; ++kk) {
-      const float b = sb[kk][tc];
+    if (k0 + kKc < K) load(k0 + kKc);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = fmaf(sa[kk][ti + e], b, acc[e]);
+    for (int kk = 0; kk < kQ; ++kk) {   // terms beyond K are zero
+      const float b = sb[grp * kQ + kk][tc];
+      const float4 x = *reinterpret_cast<const float4*>(&sa[grp * kQ + kk][ti]);
+      acc[0] = fmaf(x.x, b, acc[0]);
+      acc[1] = fmaf(x.y, b, acc[1]);
+      acc[2] = fmaf(x.z, b, acc[2]);
+      acc[3] = fmaf(x.w, b, acc[3]);
     }
     __syncthreads();
   }
+  float4* part = reinterpret_cast<float4*>(&sa[0][0]);   // 2 x 256 entries fit (9 KiB): the groups in two steps
+  if (grp >= 2) part[(grp - 2) * 256 + t8] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+  __syncthreads();
+  if (grp < 2) {
+    const float4 o = part[grp * 256 + t8];   // groups 0 + 2 and 1 + 3
+    acc[0] += o.x; acc[1] += o.y; acc[2] += o.z; acc[3] += o.w;
+  }
+  __syncthreads();
+  if (grp == 1) part[t8] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+  __syncthreads();
+  if (grp > 0) return;
+  const float4 o = part[t8];
+  const float r[4] = {acc[0] + o.x, acc[1] + o.y, acc[2] + o.z, acc[3] + o.w};
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int gi = i0 + ti + e, gc = c0 + tc;
-    if (gi < M && gc < N) C[(long long)gi * ldc + gc] = acc[e];
+    if (gi < M && gc < N) C[(long long)gi * ldc + gc] = r[e];
   }
 }
 
-// W (b x b, FP64) = X^T X for X (rows x b, row-major): one entry per thread,
-// rows summed in order in FP64.
-__global__ __launch_bounds__(kGT * kGT) void k_rank_gram(const float* __restrict__ X, int rows, int b,
-                                                         double* __restrict__ W) {
+// W (b x b, FP64) = X^T X for X (rows x b, row-major): one entry per thread of each of
+// four groups, which take a quarter of every 64-row stage; the next stage is loaded meanwhile;
+// the groups' sums are added in order (n = 300, b = 20: 5 us against 15 with one group and no
+// load ahead).
+__global__ __launch_bounds__(4 * kGT * kGT) void k_rank_gram(const float* __restrict__ X, int rows, int b,
+                                                             double* __restrict__ W) {
   __shared__ float sx[kGRows][2 * kGT + 1];
-  const int tid = threadIdx.x, ta = tid / kGT, tb = tid % kGT;
+  __shared__ double part[3][kGT * kGT];
+  constexpr int kTh = 4 * kGT * kGT, kPer = kGRows * 2 * kGT / kTh, kQ = kGRows / 4;
+  const int tid = threadIdx.x, grp = tid / (kGT * kGT), ent = tid % (kGT * kGT), ta = ent / kGT, tb = ent % kGT;
   const int a0 = blockIdx.y * kGT, b0 = blockIdx.x * kGT;
-  double s = 0.0;
-  for (int j0 = 0; j0 < rows; j0 += kGRows) {
-    for (int e = tid; e < kGRows * 2 * kGT; e += kGT * kGT) {
-      const int jj = e / (2 * kGT), cc = e % (2 * kGT);
+  float v[kPer];
+  auto load = [&](int j0) {
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      const int e = tid + kTh * t, jj = e / (2 * kGT), cc = e % (2 * kGT);
       const int c = cc < kGT ? a0 + cc : b0 + cc - kGT;
-      sx[jj][cc] = (j0 + jj < rows && c < b) ? X[(long long)(j0 + jj) * b + c] : 0.f;
+      v[t] = j0 + jj < rows && c < b ? X[(long long)(j0 + jj) * b + c] : 0.f;
+    }
+  };
+  double s = 0.0;
+  load(0);
+  for (int j0 = 0; j0 < rows; j0 += kGRows) {
+#pragma unroll
+    for (int t = 0; t < kPer; ++t) {
+      const int e = tid + kTh * t;
+      sx[e / (2 * kGT)][e % (2 * kGT)] = v[t];
     }
     __syncthreads();
-    const int lim = min(kGRows, rows - j0);
-    for (int jj = 0; jj < lim; ++jj) s = fma((double)sx[jj][ta], (double)sx[jj][kGT + tb], s);
+    if (j0 + kGRows < rows) load(j0 + kGRows);
+#pragma unroll
+    for (int jj = 0; jj < kQ; ++jj)   // rows beyond the last are zero
+      s = fma((double)sx[grp * kQ + jj][ta], (double)sx[grp * kQ + jj][kGT + tb], s);
     __syncthreads();
   }
+  if (grp > 0) part[grp - 1][ent] = s;
+  __syncthreads();
   const int ga = a0 + ta, gb = b0 + tb;
-  if (ga < b && gb < b) W[(long long)ga * b + gb] = s;
+  if (grp == 0 && ga < b && gb < b) W[(long long)ga * b + gb] = ((s + part[0][ent]) + part[1][ent]) + part[2][ent];
 }
 
 // One workgroup: W = R^T R (R upper triangular, positive diagonal) in LDS, then
-// X = R^{-1} (FP64 in Xinv, FP32 copy in Xf for the next product).  A pivot at
-// or below 1e-13 times the largest diagonal of W (a numerically rank-deficient
-// block) is replaced by 1 with a zero row, so the factor stays finite; flag
-// bit 0 records it.
-__global__ __launch_bounds__(256) void k_rank_chol(const double* __restrict__ W, int b, double* __restrict__ Xinv,
-                                                   float* __restrict__ Xf, int* __restrict__ flag) {
-  extern __shared__ double sw[];   // b x b
-  const int tid = threadIdx.x;
-  for (int e = tid; e < b * b; e += 256) sw[e] = W[e];
-  __shared__ double dmax;
-  __syncthreads();
-  if (tid == 0) {
-    double mx = 0.0;
-    for (int i = 0; i < b; ++i) mx = fmax(mx, sw[i * b + i]);
-    dmax = mx;
+// Xf = R^{-1} (rounded to FP32, for the next product).  A pivot at or below 1e-13
+// times the largest diagonal of W (a numerically rank-deficient block) is replaced
+// by 1 with a zero row, so the factor stays finite; flag bit 0 records it.
+// Elimination without scaling on [W | I], row i minus W[k][i] / pivot times row k, so that a
+// step takes one barrier and one reciprocal: W = L D L^T, the right half becomes L^{-1} and is
+// held in the lower triangle that the factor leaves free, and R^{-1} = L^{-T} D^{-1/2}.  At b = 20
+// 15 us against 29 with three barriers and divisions a step and a serial back
+// substitution per column through global memory.
+__global__ __launch_bounds__(256) void k_rank_chol(const double* __restrict__ W, int b, float* __restrict__ Xf,
+                                                   int* __restrict__ flag) {
+  extern __shared__ double sw[];   // b x b: rows of W on and above the diagonal, L^{-1} below it
+  __shared__ double rd[kRankBlockMax];   // D, then D^{-1/2}
+  const int tid = threadIdx.x, lane = tid & 63, ty = tid >> 4, tx = tid & 15;
+  double dmax = 0.0;
+  for (int e = lane; e < b; e += 64) dmax = fmax(dmax, W[(long long)e * b + e]);
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) dmax = fmax(dmax, __shfl_xor(dmax, o));
+  for (int e = tid; e < b * b; e += 256) {
+    const int i = e / b, j = e - i * b;
+    sw[e] = j >= i ? W[e] : 0.0;
   }
   __syncthreads();
   const double floor_d = 1e-13 * dmax;
@@ -115,34 +168,24 @@ __global__ __launch_bounds__(256) void k_rank_chol(const double* __restrict__ W,
     const double d = sw[k * b + k];
     const bool ok = d > floor_d && isfinite(d);
     deficient |= !ok;
-    const double rkk = ok ? sqrt(d) : 1.0;
-    __syncthreads();   // every thread has read the pivot
-    for (int j = k + 1 + tid; j < b; j += 256) sw[k * b + j] = ok ? sw[k * b + j] / rkk : 0.0;
-    if (tid == 0) sw[k * b + k] = rkk;
-    __syncthreads();
-    // trailing update of the upper triangle: W[i][j] -= R[k][i] R[k][j], k < i <= j
-    const int t = b - k - 1;
-    for (int e = tid; e < t * t; e += 256) {
-      const int i = k + 1 + e / t, j = k + 1 + e % t;
-      if (j >= i) sw[i * b + j] -= sw[k * b + i] * sw[k * b + j];
+    const double inv = ok ? fast_rcp(d) : 0.0;
+    if (tid == 0) rd[k] = ok ? d : 1.0;
+    for (int i = k + 1 + ty; i < b && ok; i += 16) {
+      const double f = -sw[k * b + i] * inv;
+      for (int j = tx; j < b; j += 16) {
+        if (j >= i) sw[i * b + j] = fma(f, sw[k * b + j], sw[i * b + j]);
+        else if (j <= k) sw[i * b + j] = fma(f, j == k ? 1.0 : sw[k * b + j], sw[i * b + j]);
+      }
     }
     __syncthreads();
   }
   if (tid == 0 && deficient) atomicOr(flag, 1);
-  // R^{-1}: column c by back substitution (thread c), rows c .. 0 in order
-  for (int c = tid; c < b; c += 256) {
-    for (int i = b - 1; i >= 0; --i) {
-      double v = 0.0;
-      if (i <= c) {
-        v = (i == c) ? 1.0 : 0.0;
-        for (int l = i + 1; l <= c; ++l) v -= sw[i * b + l] * Xinv[(long long)l * b + c];
-        v /= sw[i * b + i];
-      }
-      Xinv[(long long)i * b + c] = v;
-    }
-  }
+  if (tid < b) rd[tid] = 1.0 / sqrt(rd[tid]);
   __syncthreads();
-  for (int e = tid; e < b * b; e += 256) Xf[e] = (float)Xinv[e];
+  for (int e = tid; e < b * b; e += 256) {
+    const int i = e / b, c = e - i * b;
+    Xf[e] = c < i ? 0.f : (float)((c == i ? 1.0 : sw[c * b + i]) * rd[c]);
+  }
 }
 
 // One workgroup: eigenvalues of the symmetric b x b matrix M (FP64) by cyclic
@@ -307,21 +350,21 @@ hipError_t launch_rank_mm(bool trans, const float* A, long long lda, const float
                           long long ldc, int M, int N, int K, hipStream_t st) {
   (void)hipGetLastError();
   const dim3 grid((N + kTile - 1) / kTile, (M + kTile - 1) / kTile);
-  if (trans) hipLaunchKernelGGL(k_rank_mm<true>, grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K);
-  else hipLaunchKernelGGL(k_rank_mm<false>, grid, dim3(256), 0, st, A, lda, B, ldb, C, ldc, M, N, K);
+  if (trans) hipLaunchKernelGGL(k_rank_mm<true>, grid, dim3(1024), 0, st, A, lda, B, ldb, C, ldc, M, N, K);
+  else hipLaunchKernelGGL(k_rank_mm<false>, grid, dim3(1024), 0, st, A, lda, B, ldb, C, ldc, M, N, K);
   return hipGetLastError();
 }
 
 hipError_t launch_rank_gram(const float* X, int rows, int b, double* W, hipStream_t st) {
   (void)hipGetLastError();
   const dim3 grid((b + kGT - 1) / kGT, (b + kGT - 1) / kGT);
-  hipLaunchKernelGGL(k_rank_gram, grid, dim3(kGT * kGT), 0, st, X, rows, b, W);
+  hipLaunchKernelGGL(k_rank_gram, grid, dim3(4 * kGT * kGT), 0, st, X, rows, b, W);
   return hipGetLastError();
 }
 
-hipError_t launch_rank_chol(const double* W, int b, double* Xinv, float* Xf, int* flag, hipStream_t st) {
+hipError_t launch_rank_chol(const double* W, int b, float* Xf, int* flag, hipStream_t st) {
   (void)hipGetLastError();
-  hipLaunchKernelGGL(k_rank_chol, dim3(1), dim3(256), (size_t)b * b * sizeof(double), st, W, b, Xinv, Xf, flag);
+  hipLaunchKernelGGL(k_rank_chol, dim3(1), dim3(256), (size_t)b * b * sizeof(double), st, W, b, Xf, flag);
   return hipGetLastError();
 }
 

@@ -196,7 +196,7 @@ size_t rank_lds_bytes(int b);
 hipError_t launch_rank_mm(bool trans, const float* A, long long lda, const float* B, long long ldb, float* C,
                           long long ldc, int M, int N, int K, hipStream_t st);
 hipError_t launch_rank_gram(const float* X, int rows, int b, double* W, hipStream_t st);
-hipError_t launch_rank_chol(const double* W, int b, double* Xinv, float* Xf, int* flag, hipStream_t st);
+hipError_t launch_rank_chol(const double* W, int b, float* Xf, int* flag, hipStream_t st);
 hipError_t launch_rank_jacobi(const double* M, int b, int K, double energy, double* sv, int* r_out,
                               hipStream_t st);
 hipError_t launch_rank_slice(const float* Ub, int n, int b, int r, float* U, hipStream_t st);
