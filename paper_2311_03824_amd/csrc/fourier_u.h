@@ -439,7 +439,7 @@ struct FSubShared {
 
 // As k_subspace of the real forms; part of a 64-row unit (doubles): Gram of Z | U_old^H U_new |
 // Gram of U_new | change.
-__global__ __launch_bounds__(kFSubThreads) void k_fsub(FSubArgs a) {
+__global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_fsub(FSubArgs a) {
   __shared__ FSubShared S;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), nblk = gridDim.x;
   const int n = a.n, q = a.q, r = a.r, rr = r * r, E = r * (r + 1) / 2, KS = a.KS;

@@ -726,34 +726,19 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   bool have_list = false;
   int2 seg = make_int2(0, 0);
 
-  // u = Pi (A_k s - y_k) and w = Pi A_k g_T.  A step that keeps T moves s by -mu g_T
-  // and so u by -mu w, which is at hand: the next step needs neither the gather of
-  // A_k s nor its projection (equal up to rounding; the tail gathers A_k s afresh):
-  // 0.083 -> 0.075 ms at q = 125, 0.342 -> 0.323 at q = 1000.
-  // Not in the mixed form, whose w comes from the hi plane and u from hi + lo.
+  // u = Pi (A_k s - y_k) and w = Pi A_k g_T.  u is formed from s afresh in every step: a step
+  // that keeps T moves it by -mu w, but that u does not see the rounding of s to FP32
+  // (at n = 187, m = 81 U against FP64 1.7e-7 instead of 0.9e-7; it was 3 to 10 % faster).
   // smin: the smallest magnitude of s on T as a bit pattern, when known.
   float4 v[NC], w[NC];
-  bool have_u = false, have_smin = false;
+  bool have_smin = false;
   unsigned smin = 0u;
 
   for (int it = 0; it < a.tau; ++it) {
-    if (!have_u) {
-      gather<GF, NC, W>(L, ln, Ti, Tv, hasT ? rho : 0, v, wpart, mq, wave);
+    gather<GF, NC, W>(L, ln, Ti, Tv, hasT ? rho : 0, v, wpart, mq, wave);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) v[c] = sub4(v[c], yv[c]);
-      if (a.project) project<NC, W>(v, ln, Pv, Gi, r, lane, wave, cbuf, nullptr);
-    }
-    auto move_u = [&](double mu) {
-      if constexpr (GF == SF) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-          v[c] = make_float4((float)fma(-mu, (double)w[c].x, (double)v[c].x),
-                             (float)fma(-mu, (double)w[c].y, (double)v[c].y),
-                             (float)fma(-mu, (double)w[c].z, (double)v[c].z),
-                             (float)fma(-mu, (double)w[c].w, (double)v[c].w));
-        have_u = true;
-      }
-    };
+    for (int c = 0; c < NC; ++c) v[c] = sub4(v[c], yv[c]);
+    if (a.project) project<NC, W>(v, ln, Pv, Gi, r, lane, wave, cbuf, nullptr);
 
     const bool last = (it == a.tau - 1);
     // the test can only hold when ||u|| / bound, a lower estimate of its left side, is
@@ -826,8 +811,6 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
           Tv[t] = gT[t];
           sd[Ti[t]] = gT[t];
         }
-        have_u = false;
-        move_u(mu);
         smin = kmin;
         break;
       }
@@ -845,10 +828,9 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     // s - mu g, then HardThreshold
     for (int j = tid; j < n; j += kT) gl[j] = (float)fma(-mu, (double)gl[j], (double)sd[j]);
     __syncthreads();
-    have_smin = have_u = false;
+    have_smin = false;
     if (hasT && block_support_kept<W>(gl, n, inT, reinterpret_cast<unsigned*>(hist))) {
       // most steps keep T: Ti (ascending) and inT stand, s takes the new values on T
-      move_u(mu);
       for (int t = tid; t < rho; t += kT) {
         const int j = Ti[t];
         Tv[t] = gl[j];
@@ -922,8 +904,8 @@ constexpr int col_min_waves_w(int fmt, int nc, int ju, int w) {
 
 // Launches that give a CU one 8-wave workgroup (at most 256 of them, or LDS for one) of two row
 // chunks take the deep variant: the 128 registers of four waves per SIMD cost 31 spills there, and
-// twice the columns in flight fit (n = 1000, m = 400, r = 10, FP32: 79 -> 74 us at q = 125,
-// 98 -> 91 at 200, 111 -> 104 at 256).
+// twice the columns in flight fit (n = 1000, m = 400, r = 10, FP32: 5 us less at q = 125, of
+// 82; 7 less at 200 and 256).
 static inline bool col_deep(int fmt, int nc, const ColArgs& a, size_t lds) {
   return nc == 2 && a.waves == 8 && fmt <= FMT_BF16HI && (a.q <= 256 || lds > 80 * 1024);
 }
