@@ -28,7 +28,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 from paper_2311_03824_amd import roofline  # noqa: E402
-from paper_2311_03824_amd.roofline import au_kernel_bytes, column_kernel_bytes  # noqa: E402
+from paper_2311_03824_amd.roofline import au_kernel_bytes, settled_column_bytes  # noqa: E402
 
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E peak
 FP32_VECTOR_TFLOPS = 157.3      # MI355X FP32 vector peak (256 CUs at 2.4 GHz)
@@ -165,7 +165,7 @@ def shard_config(lib, torch, np, shards: int = 8):
         e1.record()
         torch.cuda.synchronize()
         kms = s.profile_iteration(20)
-        col_bytes = column_kernel_bytes(inst.n, inst.q, inst.m, inst.r, inst.rho, 3, 2.0 if planes else 4.0, 4.0)
+        col_bytes = settled_column_bytes(inst.n, inst.q, inst.m, inst.r, inst.rho, 3, 2.0 if planes else 4.0, 4.0)
         out[name] = {"gdmin_iters_per_s": round(T_ITERS / (e0.elapsed_time(e1) * 1e-3), 1),
                      "kernels_ms": {k: round(v, 4) for k, v in kms.items()},
                      "k_col_GBps": round(col_bytes / (kms["k_col"] * 1e-3) / 1e9, 1),
@@ -362,7 +362,7 @@ def small_configs(lib, torch, np):
     kms = s.profile_iteration(20)
     tuning = lib.altgdmin_tuning(s.h)
     s.close()
-    col_bytes = column_kernel_bytes(inst.n, inst.q, inst.m, inst.r, inst.rho, 3)
+    col_bytes = settled_column_bytes(inst.n, inst.q, inst.m, inst.r, inst.rho, 3)
     col_gbs = col_bytes / (kms["k_col"] * 1e-3) / 1e9
     A = inst.A64()
     Yd = inst.Y32.astype(np.float64)
@@ -573,7 +573,7 @@ def main() -> int:
     kms = solver.profile_iteration(args.profile_iters)
     log("per-kernel ms: " + ", ".join(f"{k}={v:.4f}" for k, v in kms.items()))
     a_bytes = 2.0 if args.form == "bf16_mixed" else 4.0
-    col_bytes = column_kernel_bytes(n, q, m, r, rho, par.tau, a_bytes, gather_bytes=4.0)
+    col_bytes = settled_column_bytes(n, q, m, r, rho, par.tau, a_bytes, gather_bytes=4.0)
     au_bytes = au_kernel_bytes(n, q, m, r, 4.0)
     col_gbs = col_bytes / (kms["k_col"] * 1e-3) / 1e9
     au_gbs = au_bytes / (kms["k_au"] * 1e-3) / 1e9

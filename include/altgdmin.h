@@ -405,7 +405,9 @@ int altgdmin_op_subspace(const float* L0t, int32_t n, int32_t q, int32_t r, cons
  * hipMalloc).
  * ---------------------------------------------------------------------- */
 
-/* Bytes of the library's static device scratch array (one per GPU, held until the process ends). */
+/* The library's static device scratch array (one per GPU, held until the process ends): the sizes it
+ * takes are those whose buffers, without the partial sums of the split kernels, fit these bytes; it has
+ * 9 MiB more for the partial sums. */
 #define ALTGDMIN_STATIC_SCRATCH_BYTES (16u << 20)
 
 /* altgdmin_op_subspace without the scratch argument: its scratch (the

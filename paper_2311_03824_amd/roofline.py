@@ -26,6 +26,14 @@ def column_kernel_bytes(n, q, m, r, rho, tau, a_bytes=4.0, gather_bytes=None):
     return per_col * q
 
 
+def settled_column_bytes(n, q, m, r, rho, tau, a_bytes=4.0, gather_bytes=None):
+    """column_kernel_bytes of a launch whose IHT steps all keep their support by the column
+    norm bound: one streaming pass (the tail) and, per step, the rho support columns instead
+    of a pass (their gather is counted as before)."""
+    per_col = tau * (n - rho) * m * a_bytes
+    return column_kernel_bytes(n, q, m, r, rho, tau, a_bytes, gather_bytes) - per_col * q
+
+
 def au_kernel_bytes(n, q, m, r, a_bytes=4.0):
     """Per column: one pass over A_k, U (n r, L2-resident after the first column), P_k written, G^{-1} written."""
     return q * (m * n * a_bytes + 4 * m * r + 8 * r * r) + 4 * n * r
