@@ -212,6 +212,8 @@ struct altgdmin_handle {
   void* rank_ws = nullptr; // r = 0 (automatic rank): scratch of the rank estimate
   float* rank_embed = nullptr;  // Fourier form, r = 0: the real embedding of L_0 (2q x 2n)
   int col_waves = kWaves;  // waves of the column workgroup (a property of the problem, see choose_col_waves)
+  int au_waves = kWaves;   // waves of the A_k U workgroup and its row splits, taken once, at init (Ginv and
+  int au_splits = 1;       // colbound hold a value per split)
   int col_unroll = 0;      // autotuned JU of the column kernel (0: the default instantiation)
   int au_depth = 0;        // autotuned AUD of the A_k U kernel (0: the default instantiation)
   int colfmt = 0;          // format of the column kernel: fmt, or the mixed BF16 form
@@ -281,8 +283,8 @@ int au_waves(const altgdmin_problem& p) {
 // against 0.179 and q = 400 0.342 against 0.316; n = 4000, m = 1000, q = 64: four 0.667, three
 // 0.700, two 0.727, one 0.897.  It sets the order of the sums of P_k and G_k: a property of the
 // problem, like the width.
-int au_splits(const altgdmin_problem& p) {
-  if (p.a_format == ALTGDMIN_A_PFOURIER || p.m <= 256 || au_waves(p) != 8) return 1;
+int au_splits(const altgdmin_problem& p, int waves) {
+  if (p.a_format == ALTGDMIN_A_PFOURIER || p.m <= 256 || waves != 8) return 1;
   return std::max(1, std::min((p.m + 255) / 256, 256 / p.q));
 }
 
@@ -294,7 +296,7 @@ size_t carve(altgdmin_handle* h, void* base) {
   Carver c(base);
   h->ctl = c.take<Ctl>(1);
   h->P = c.take<float>(q * m * r);
-  const size_t asp = au_splits(p);
+  const size_t asp = au_splits(p, 8);   // room for the splits of either width: the size is the problem's alone
   h->Ginv = c.take<double>(q * asp * r * r);
   h->Tidx = c.take<int>(q * rho);
   h->Tval = c.take<float>(q * rho);
@@ -431,7 +433,7 @@ ColArgs gd_col_args(const altgdmin_handle* h) {
   ColArgs a = col_args(h);
   a.tau = h->par.tau; a.project = 1; a.has_support = 1; a.tail = TAIL_LSGRAD;
   a.bound = h->colbound;
-  a.splits = au_splits(h->prob);
+  a.splits = h->au_splits;
   return a;
 }
 
@@ -444,9 +446,9 @@ AUArgs gd_au_args(const altgdmin_handle* h, const float* U) {
   a.A = p.A; a.Alo = p.A_lo; a.lda = p.lda; a.sA = p.a_stride_k;
   a.U = U; a.P = h->P; a.Ginv = h->Ginv; a.flags = h->colflags;
   a.seed = p.a_seed; a.table = p.normal_table;
-  a.waves = au_waves(p);
+  a.waves = h->au_waves;
   a.bound = h->colbound;
-  a.splits = au_splits(p);
+  a.splits = h->au_splits;
   return a;
 }
 
@@ -564,7 +566,7 @@ int autotune(altgdmin_handle* h, hipStream_t st) {
     if (ju == 8 && p.m > 512) ju = 4;   // JU = 8 is built for at most two row chunks
     // the unrolls are built for 4-wave workgroups; -1 (the cached default) for every width
     h->col_unroll = ju < 0 || h->col_waves == kWaves ? ju : 0;
-    h->au_depth = aud < 0 || au_waves(h->prob) == kWaves ? aud : 0;
+    h->au_depth = aud < 0 || h->au_waves == kWaves ? aud : 0;
     return ALTGDMIN_OK;
   }
   const std::string arch = device_arch();
@@ -776,6 +778,8 @@ int altgdmin_init(const altgdmin_problem* prob, const altgdmin_params* par, void
   h->auto_rank = prob->r == 0;
   if (h->fmt != FMT_PFOURIER) {
     h->col_waves = choose_col_waves(h->prob, h->colfmt == FMT_BF16MIX);
+    h->au_waves = au_waves(h->prob);
+    h->au_splits = au_splits(h->prob, h->au_waves);
     // a GDmin iteration's column workgroup (with P_k) may need more LDS than the
     // initialisation's: raise the kernels' limit now, before any graph capture
     if (col_lds_bytes(prob->n, prob->m, r_eff(*prob), prob->rho, 1, prob->a_format == ALTGDMIN_A_PHILOX,
@@ -1298,7 +1302,7 @@ int plan_group(altgdmin_handle* const* hs, int count, GroupPlan& g) {
     g.upd.push_back(ua);
     const int f = h->fmt, cf = h->colfmt, phx = f == FMT_PHILOX;
     const int nc = (p.m + 255) / 256, rr = (p.r + 1) / 2 * 2, cw = h->col_waves;
-    const int aw = au_waves(p);
+    const int aw = h->au_waves;
     Bucket& ab = g.au_b[(f * 64 + rr) * 32 + aw];   // and with others of their A_k U width
     Bucket& cb = g.col_b[(cf * 64 + nc) * 32 + cw];   // problems batch with others of their column width
     ab.fmt = f;
@@ -1467,7 +1471,7 @@ int altgdmin_op_au(const altgdmin_problem* prob, const float* U, float* P, doubl
   au.gate = nullptr; au.gate_want = 0;
   au.seed = prob->a_seed; au.table = prob->normal_table;
   au.waves = au_waves(*prob);   // the width the solver takes for this problem
-  au.splits = au_splits(*prob);   // and the row splits, so the same bits
+  au.splits = au_splits(*prob, au.waves);   // and the row splits, so the same bits
   if (au.splits > 1) {
     AUArgs rows = au;
     rows.Ginv = nullptr;
