@@ -394,7 +394,10 @@ int altgdmin_op_rank(const float* L0t, int32_t n, int32_t q, int32_t m, double e
 /* Top-r left singular subspace of L0 (n x q, given as L0t q x n) by subspace
  * iteration from U_start (n x r), at most `iters` iterations or until the
  * change drops to tol.  U_out: n x r orthonormal.  iters_out (optional, device
- * int32) gets the count used. */
+ * int32) gets the count used.  One launch, whose workgroups wait for each other; it
+ * finishes with however many of them the device holds at once (it gives the others
+ * 2 ms to come; ALTGDMIN_START_GRACE_US forces that wait, for tests), with the same
+ * bits. */
 int altgdmin_op_subspace(const float* L0t, int32_t n, int32_t q, int32_t r, const float* U_start,
                          int32_t iters, double tol, float* U_out, int32_t* iters_out,
                          void* scratch, size_t scratch_bytes, void* stream);

@@ -855,7 +855,7 @@ int altgdmin_init(const altgdmin_problem* prob, const altgdmin_params* par, void
     sa.L0t = CF2(h->H); sa.start = F2(h->Utmp); sa.U = F2(h->U); sa.V = F2(h->Utmp); sa.T = F2(h->Tpow);
     sa.gpart = F2(h->gpart); sa.part = h->upart; sa.n = p.n; sa.q = p.q; sa.r = p.r; sa.KS = h->KS;
     sa.iters = par->power_iters; sa.tol = par->power_tol;
-    sa.ctl = h->ctl; sa.bar = &h->ctl->bar; sa.stuck = &h->ctl->stuck;
+    sa.ctl = h->ctl;
     if ((e = launch_fsub(sa, st)) != hipSuccess) return bail(e, "subspace");
     if ((e = launch_reset_ctl(h->ctl, 0, st)) != hipSuccess) return bail(e, "reset eta");
     *out = h;
@@ -899,7 +899,7 @@ int altgdmin_init(const altgdmin_problem* prob, const altgdmin_params* par, void
     std::memset(&sa, 0, sizeof(sa));
     sa.L0t = h->H; sa.start = h->Utmp; sa.U = h->U; sa.V = h->Utmp; sa.T = h->Tpow; sa.gpart = h->gpart;
     sa.part = h->upart; sa.n = p.n; sa.q = p.q; sa.r = p.r; sa.iters = par->power_iters;
-    sa.tol = par->power_tol; sa.ctl = h->ctl; sa.bar = &h->ctl->bar; sa.stuck = &h->ctl->stuck;
+    sa.tol = par->power_tol; sa.ctl = h->ctl;
     if ((e = launch_subspace(sa, h->KS, st)) != hipSuccess) return bail(e, "subspace");
   }
   if ((e = launch_reset_ctl(h->ctl, 0, st)) != hipSuccess) return bail(e, "reset eta");
@@ -1680,7 +1680,7 @@ static int subspace_body(const float* L0t, int32_t n, int32_t q, int32_t r, cons
   std::memset(&a, 0, sizeof(a));
   a.L0t = L0t; a.start = s.Utmp; a.U = U_out; a.V = s.Utmp; a.T = s.T; a.gpart = s.gpart; a.part = s.part;
   a.n = n; a.q = q; a.r = r; a.iters = iters; a.tol = tol;
-  a.ctl = s.ctl; a.bar = &s.ctl->bar; a.stuck = &s.ctl->stuck;
+  a.ctl = s.ctl;
   HIPCHK(launch_subspace(a, s.KS, st));
   if (iters_out) HIPCHK(hipMemcpyAsync(iters_out, &s.ctl->power_it, sizeof(int), hipMemcpyDeviceToDevice, st));
   return ALTGDMIN_OK;

@@ -38,8 +38,9 @@ struct Ctl {
   int refine_t;      // first iteration with phase 1 (-1 before)
   int done;          // batched stepping: the residual reached tol_resid; the problem is not advanced further
   int bar;           // subspace iteration: meeting counter of its workgroups
-  int stuck;         // subspace iteration: a workgroup gave up waiting
-  int pad[2];
+  int roll;          // subspace iteration: workgroups that have arrived, and whether the roll is closed
+  int members;       // subspace iteration: workgroups on the closed roll (0 before)
+  int pad;
   double prev_resid; // residual of the previous iteration (stall test of the hi-only phase)
 };
 

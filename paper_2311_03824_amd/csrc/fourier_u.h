@@ -6,7 +6,7 @@
 //            the block's part of the FP64 Gram X^H X of X = U - eta grad;
 //  k_fapply: a row per thread: every workgroup adds the parts in order and factors the
 //            Gram, then U = X R^{-1}; one more workgroup does the bookkeeping;
-//  k_fsub  : start block, subspace iteration and stop rule with resident workgroups.
+//  k_fsub  : start block, subspace iteration and stop rule in one launch (meet.h).
 //
 // None is bound by bytes: 64-row blocks are latency of q loads per wave, the rest is the
 // serial factorisation.  Measured (launch to launch): k_frows 10 us at n = 9216, q = 64, r = 6
@@ -16,6 +16,7 @@
 // n = 400: 0.4 ms, in eight launches a step 2.8 ms.
 #pragma once
 #include "launch.h"
+#include "meet.h"
 #include "uside.h"
 
 namespace altg {
@@ -25,8 +26,7 @@ namespace {
 constexpr int kFRowsWaves = 16;
 constexpr int kFApplyRows = 256;
 constexpr int kFSubThreads = 256, kFSubWaves = kFSubThreads / 64;
-constexpr int kFSubBlocksMax = 96;          // as kSubBlocksMax of the real forms: four launches at once fit
-constexpr int kFSpinMax = 1 << 26;          // polls before a wait gives up (tens of seconds)
+constexpr int kFSubBlocksMax = 96;
 
 __device__ __forceinline__ double2 c_fma(double2 a, double2 b, double2 c) {   // a b + c
   return make_double2(fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y)));
@@ -433,6 +433,7 @@ struct FSubShared {
   double rdiag[kFRMax];
   double val[2];
   int flag;
+  int2 roll;
 };
 
 }  // namespace
@@ -441,39 +442,16 @@ struct FSubShared {
 // Gram of U_new | change.
 __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_fsub(FSubArgs a) {
   __shared__ FSubShared S;
-  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), nblk = gridDim.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
   const int n = a.n, q = a.q, r = a.r, rr = r * r, E = r * (r + 1) / 2, KS = a.KS;
   const int units = (n + 63) / 64, ps = 2 * (2 * E + rr) + 1;
   const long long nr = (long long)n * r;
-  int target = 0;
-  bool dead = false;
-
-  auto meet = [&]() {
-    __syncthreads();
-    if (nblk > 1) {
-      target += nblk;
-      if (tid == 0) {
-        int give_up = 0;
-        __hip_atomic_fetch_add(a.bar, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        for (int spin = 0; __hip_atomic_load(a.bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target; ++spin) {
-          if (spin >= kFSpinMax || __hip_atomic_load(a.stuck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-            __hip_atomic_store(a.stuck, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            give_up = 1;
-            break;
-          }
-          __builtin_amdgcn_s_sleep(1);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        S.flag = give_up;
-      }
-      __syncthreads();
-      dead = dead || S.flag != 0;
-      __syncthreads();
-    }
-  };
+  Meeting meet(a.ctl);
+  if (!meet.join(a.grace, &S.roll)) return;
+  const int me = meet.id, nblk = meet.count;
 
   auto orth = [&](float2* z, int splits, float2* dst, const float2* old) -> bool {
-    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+    for (int ru = me; ru < units; ru += nblk) {
       __syncthreads();
       const long long base = (long long)ru * 64 * r;
       for (int i = tid; i < 64 * r; i += kFSubThreads) {
@@ -493,7 +471,6 @@ __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2,
       rows_gram64_c<kFSubWaves>(S.rows.X, S.rows.X, r, true, reinterpret_cast<double2*>(a.part + (long long)ru * (ps + 1)));
     }
     meet();
-    if (dead) return false;
     for (int pass = 0; pass < 2; ++pass) {
       sum_parts_c<kFSubThreads>(a.part, ps + 1, pass == 0 ? 0 : 2 * (E + rr), 2 * E, units, S.sum,
                                 reinterpret_cast<double*>(S.tri));
@@ -508,7 +485,7 @@ __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2,
       if (mode == 0) return false;
       const bool again = pass == 0 && mode == 2;   // ill-conditioned: once more on the rounded rows
       const float2* src = pass == 0 ? z : dst;
-      for (int ru = blockIdx.x; ru < units; ru += nblk) {
+      for (int ru = me; ru < units; ru += nblk) {
         const int j = ru * 64 + tid;
         const long long o = (long long)j * r;
         __syncthreads();
@@ -541,7 +518,6 @@ __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2,
         __syncthreads();
       }
       meet();
-      if (dead) return false;
       if (!again) break;
     }
     return true;
@@ -552,7 +528,7 @@ __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2,
     sum_parts_c<kFSubThreads>(a.part, ps + 1, ps - 1, 1, units, S.sum, S.val);
     const double sd = sqrt(S.val[0]);
     const bool conv = sd <= a.tol || (sd <= 1e-3 && prev > 0.0 && sd >= 0.99 * prev);
-    if (blockIdx.x == 0 && tid == 0) {
+    if (me == 0 && tid == 0) {
       a.ctl->power_sd = sd;
       a.ctl->power_it += 1;
       if (conv) a.ctl->conv = 1;
@@ -568,7 +544,7 @@ __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2,
   const int WK = n > 2048 ? kFSubWaves : 1;        // waves that share a column
   for (int p = 0; ok && p < a.iters; ++p) {
     // T[k][c] = sum_j h_k[j] conj(U[j][c]) in FP64
-    for (int k0 = blockIdx.x * (kFSubWaves / WK); k0 < q; k0 += nblk * (kFSubWaves / WK)) {
+    for (int k0 = me * (kFSubWaves / WK); k0 < q; k0 += nblk * (kFSubWaves / WK)) {
       const int k = k0 + (WK == 1 ? wave : 0), kc = k < q ? k : q - 1;
       const float2* row = a.L0t + (long long)kc * n;
       double2 acc[kFRMax];
@@ -606,13 +582,12 @@ __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2,
       }
     }
     meet();
-    if (dead) break;
     if (pending) {
       pending = false;
       if (decide()) break;
     }
     // Z[j][c] = sum_k h_k[j] conj(T[k][c]) by 64-row units and column splits
-    for (int w = blockIdx.x; w < units * KS; w += nblk) {
+    for (int w = me; w < units * KS; w += nblk) {
       const int ru = KS == 1 ? w : w / KS, ks = w - ru * KS;
       const int k0 = (int)((long long)q * ks / KS), k1 = (int)((long long)q * (ks + 1) / KS);
       const long long base = (long long)ru * 64 * r;
@@ -621,16 +596,13 @@ __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2,
         if (base + i < nr) a.gpart[ks * nr + base + i] = g;
       });
     }
-    if (KS > 1) {
-      meet();
-      if (dead) break;
-    }
+    if (KS > 1) meet();
     __syncthreads();
     ok = orth(a.gpart, KS, nxt, cur);
     if (!ok) break;
     // the change ||U_new - U_old W||_F of this workgroup's rows, W = U_old^H U_new
     sum_parts_c<kFSubThreads>(a.part, ps + 1, 2 * E, 2 * rr, units, S.sum, reinterpret_cast<double*>(S.M));
-    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+    for (int ru = me; ru < units; ru += nblk) {
       if (wave == 0) {
         const int j = ru * 64 + lane;
         const long long o = (long long)j * r;
@@ -662,13 +634,13 @@ __global__ __launch_bounds__(kFSubThreads) __attribute__((amdgpu_waves_per_eu(2,
     cur = nxt;
     nxt = x;
   }
-  if (!dead && pending) {   // the step limit: record the last change
+  if (pending) {   // the step limit: record the last change
     meet();
-    if (!dead) decide();
+    decide();
   }
-  if ((dead || !ok) && blockIdx.x == 0 && tid == 0) atomicOr(&a.ctl->err, 2);
+  if (!ok && me == 0 && tid == 0) atomicOr(&a.ctl->err, 2);
   if (cur != a.U)           // this workgroup's rows, read by no other one any more
-    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+    for (int ru = me; ru < units; ru += nblk) {
       const long long base = (long long)ru * 64 * r;
       for (int i = tid; i < 64 * r; i += kFSubThreads)
         if (base + i < nr) a.U[base + i] = cur[base + i];
@@ -698,7 +670,9 @@ hipError_t launch_fapply(const FUpdArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_fsub(const FSubArgs& a, hipStream_t st) {
+hipError_t launch_fsub(const FSubArgs& a_in, hipStream_t st) {
+  FSubArgs a = a_in;
+  a.grace = roll_grace();
   const int per = a.n > 2048 ? 1 : kFSubWaves;     // columns of a workgroup's round
   const int cols = (a.q + per - 1) / per, rows = (a.n + 63) / 64 * a.KS;
   const int b = cols > rows ? cols : rows;

@@ -38,7 +38,8 @@ __global__ void k_reset_ctl(Ctl* ctl, int full) {
     ctl->prev_resid = 0.0;
     ctl->done = 0;
     ctl->bar = 0;
-    ctl->stuck = 0;
+    ctl->roll = 0;
+    ctl->members = 0;
     if (full) {
       ctl->power_sd = 0.0;
       ctl->ynorm2 = 0.0;

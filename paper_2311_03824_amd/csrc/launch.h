@@ -38,9 +38,8 @@ struct SubArgs {
   double* part;            // sub_part_doubles
   int n, q, r, KS, iters;  // KS: set by launch_subspace; iters = 0: the orthonormal block only
   double tol;
-  Ctl* ctl;                // power_sd, power_it, conv, err
-  int* bar;                // meeting counter and the give-up flag: zero at launch (launch_reset_ctl)
-  int* stuck;
+  Ctl* ctl;                // power_sd, power_it, conv, err; bar, roll and members (zero at launch)
+  int grace;               // roll call: wait for late workgroups (set by the launcher)
 };
 
 constexpr int kGradWaves = 16;             // waves of a k_urows workgroup
@@ -90,6 +89,7 @@ hipError_t launch_sum_partials(const float* gpart, int KS, long long nr, float* 
 size_t upd_part_doubles(int n, int r);
 int uapply_blocks(int n);
 size_t sub_part_doubles(int n, int r);
+int roll_grace();   // the spectral starts' wait for late workgroups, in wall clock ticks
 hipError_t launch_subspace(const SubArgs& a, int max_splits, hipStream_t st);
 hipError_t launch_urows(const UpdArgs& a, hipStream_t st);
 hipError_t launch_uapply(const UpdArgs& a, hipStream_t st);
@@ -172,8 +172,7 @@ struct FSubArgs {
   int n, q, r, KS, iters;
   double tol;
   Ctl* ctl;
-  int* bar;
-  int* stuck;
+  int grace;
 };
 
 size_t fcol_lds_bytes(int rho, int r, int n, int m, int n1, int n2);

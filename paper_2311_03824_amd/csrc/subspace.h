@@ -7,18 +7,18 @@
 // to 100 steps took three (55 us a step at n = q = 1000, r = 10, most of it the one
 // workgroup that orthonormalised), and the ones after the stop still cost their launches
 // (1.7 us each, at the host's 4.6 us): 1400 us for 6 steps.  Here sub_blocks() workgroups
-// stay resident and meet at a counter between the pieces (2.6 us for 32 workgroups, 3.3
+// stay and meet at a counter between the pieces (2.6 us for 32 workgroups, 3.3
 // for 64), and the loop ends when the rule fires: 59 us a step, 360 us in all; 20 us a
 // step at n = q = 100.
 //
-// Residency: at most kSubBlocksMax workgroups of 4 waves and about 240 registers, two to a
-// CU: 512 fit the chip, so four launches at once (a process has four hardware queues)
-// all become resident as soon as other kernels drain; none can hold what another waits
-// for.  A wait is bounded all the same: a workgroup that gives up raises *stuck, which
-// ends every other one too (error bit 1).  Rows are dealt to workgroups in a fixed way
-// and every sum runs in a fixed order, so results do not depend on timing.
+// The workgroups need not all be resident (meet.h).  Rows are dealt to workgroups in units and
+// every sum runs in a fixed order, so results depend neither on timing nor on how many
+// workgroups take part.
 #pragma once
+#include <cstdlib>
+
 #include "launch.h"
+#include "meet.h"
 #include "uside.h"
 
 namespace altg {
@@ -27,7 +27,6 @@ namespace {
 
 constexpr int kSubThreads = 256, kSubWaves = kSubThreads / 64;
 constexpr int kSubBlocksMax = 96;
-constexpr int kSpinMax = 1 << 26;           // polls before a wait gives up (tens of seconds)
 
 struct SubShared {
   union {
@@ -41,6 +40,7 @@ struct SubShared {
   double rdiag[kRMax];
   double val[2];
   int flag;
+  int2 roll;
 };
 
 // Part layout of a 64-row unit (doubles): Gram of Z | U_old^T U_new | Gram of U_new | change
@@ -71,43 +71,19 @@ __device__ __forceinline__ void sum_parts(const SubArgs& a, int off, int cnt, Su
 __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_subspace(SubArgs a) {
   __shared__ SubShared S;
   __shared__ double tri[kRMax * (kRMax + 1) / 2];
-  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), nblk = gridDim.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
   const int n = a.n, q = a.q, r = a.r, rr = r * r, E = r * (r + 1) / 2, KS = a.KS;
   const int units = (n + 63) / 64, ps = part_stride(r);
   const long long nr = (long long)n * r;
-  int target = 0;
-  bool dead = false;
-
-  // every workgroup's earlier writes are visible to all after it
-  auto meet = [&]() {
-    __syncthreads();
-    if (nblk > 1) {
-      target += nblk;
-      if (tid == 0) {
-        int give_up = 0;
-        __hip_atomic_fetch_add(a.bar, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        for (int spin = 0; __hip_atomic_load(a.bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target; ++spin) {
-          if (spin >= kSpinMax || __hip_atomic_load(a.stuck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-            __hip_atomic_store(a.stuck, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            give_up = 1;
-            break;
-          }
-          __builtin_amdgcn_s_sleep(1);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        S.flag = give_up;
-      }
-      __syncthreads();
-      dead = dead || S.flag != 0;
-      __syncthreads();
-    }
-  };
+  Meeting meet(a.ctl);
+  if (!meet.join(a.grace, &S.roll)) return;
+  const int me = meet.id, nblk = meet.count;
 
   // dst = Q of the thin QR of z (rows of z already in place: summed over `splits` splits,
   // which end in split 0); with old, also the parts of old^T dst.  False if z is rank
   // deficient.  Ends with every workgroup's rows of dst and parts visible.
   auto orth = [&](float* z, int splits, float* dst, const float* old) -> bool {
-    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+    for (int ru = me; ru < units; ru += nblk) {
       __syncthreads();
       const long long base = (long long)ru * 64 * r;
       for (int i = tid; i < 64 * r; i += kSubThreads) {
@@ -123,7 +99,6 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
       rows_gram64<kSubWaves>(S.rows.X, S.rows.X, r, true, a.part + (long long)ru * ps);
     }
     meet();
-    if (dead) return false;
     for (int pass = 0; pass < 2; ++pass) {
       sum_parts(a, pass == 0 ? 0 : E + rr, E, S, tri, units);
       if (wave == 0) {
@@ -137,7 +112,7 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
       if (mode == 0) return false;
       const bool again = pass == 0 && mode == 2;   // ill-conditioned: once more on the rounded rows
       const float* src = pass == 0 ? z : dst;
-      for (int ru = blockIdx.x; ru < units; ru += nblk) {
+      for (int ru = me; ru < units; ru += nblk) {
         const int j = ru * 64 + tid;
         const long long o = (long long)j * r;
         if (tid < 64) {
@@ -164,7 +139,6 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
         __syncthreads();
       }
       meet();
-      if (dead) return false;
       if (!again) break;
     }
     return true;
@@ -179,7 +153,7 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
     // than 1 % in a step): the FP32 iterate's rounding floor.  A change that still
     // shrinks by a steady factor above 0.9 is a slow iteration, not the floor.
     const bool conv = sd <= a.tol || (sd <= 1e-3 && prev > 0.0 && sd >= 0.99 * prev);
-    if (blockIdx.x == 0 && tid == 0) {
+    if (me == 0 && tid == 0) {
       a.ctl->power_sd = sd;
       a.ctl->power_it += 1;
       if (conv) a.ctl->conv = 1;
@@ -196,7 +170,7 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
     // T = L_0^T U on the matrix cores, 16 columns k by r per workgroup, the rows j split
     // over its waves 16 at a time: lane (i, p) holds 4 rows of column i, and the four
     // products of a group take row 4 p + e of it, e = 0..3, for both operands.
-    for (int k0 = blockIdx.x * 16; k0 < q; k0 += nblk * 16) {
+    for (int k0 = me * 16; k0 < q; k0 += nblk * 16) {
       typedef float f32x4 __attribute__((ext_vector_type(4)));
       const int i = lane & 15, p4 = 4 * (lane >> 4);
       const float* row = a.L0t + (long long)(k0 + i < q ? k0 + i : q - 1) * n;
@@ -244,13 +218,12 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
       }
     }
     meet();
-    if (dead) break;
     if (pending) {
       pending = false;
       if (decide()) break;
     }
     // Z = L_0 T by 64-row units and column splits
-    for (int w = blockIdx.x; w < units * KS; w += nblk) {
+    for (int w = me; w < units * KS; w += nblk) {
       const int ru = KS == 1 ? w : w / KS, ks = w - ru * KS;
       const int k0 = (int)((long long)q * ks / KS), k1 = (int)((long long)q * (ks + 1) / KS);
       const long long base = (long long)ru * 64 * r;
@@ -259,17 +232,14 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
         if (base + i < nr) a.gpart[ks * nr + base + i] = g;
       });
     }
-    if (KS > 1) {
-      meet();
-      if (dead) break;
-    }
+    if (KS > 1) meet();
     __syncthreads();
     ok = orth(a.gpart, KS, nxt, cur);
     if (!ok) break;
     // the change ||U_new - U_old W||_F of this workgroup's rows, W = U_old^T U_new,
     // summed directly from the residual entries; decided after the next meeting
     sum_parts(a, E, rr, S, S.M, units);
-    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+    for (int ru = me; ru < units; ru += nblk) {
       if (wave == 0) {
         const int j = ru * 64 + lane;
         const long long o = (long long)j * r;
@@ -301,13 +271,13 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
     cur = nxt;
     nxt = x;
   }
-  if (!dead && pending) {   // the step limit: record the last change (after a failed step, the one before)
+  if (pending) {   // the step limit: record the last change (after a failed step, the one before)
     meet();
-    if (!dead) decide();
+    decide();
   }
-  if ((dead || !ok) && blockIdx.x == 0 && tid == 0) atomicOr(&a.ctl->err, 2);
+  if (!ok && me == 0 && tid == 0) atomicOr(&a.ctl->err, 2);
   if (cur != a.U)           // this workgroup's rows, read by no other one any more
-    for (int ru = blockIdx.x; ru < units; ru += nblk) {
+    for (int ru = me; ru < units; ru += nblk) {
       const long long base = (long long)ru * 64 * r;
       for (int i = tid; i < 64 * r; i += kSubThreads)
         if (base + i < nr) a.U[base + i] = cur[base + i];
@@ -335,8 +305,18 @@ static int sub_splits(int n, int q, int max_splits) {
   return ks < 1 ? 1 : ks;
 }
 
+// ALTGDMIN_START_GRACE_US forces the wait for late workgroups (tests: 0 closes the roll at once).
+int roll_grace() {
+  if (const char* f = std::getenv("ALTGDMIN_START_GRACE_US")) {
+    const int us = std::atoi(f);
+    if (us >= 0 && us <= 1000000) return 100 * us;
+  }
+  return kRollGrace;
+}
+
 hipError_t launch_subspace(const SubArgs& a_in, int max_splits, hipStream_t st) {
   SubArgs a = a_in;
+  a.grace = roll_grace();
   a.KS = sub_splits(a.n, a.q, max_splits);
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
   hipLaunchKernelGGL(k_subspace, dim3(sub_blocks(a.n, a.q)), dim3(kSubThreads), 0, st, a);
