@@ -204,7 +204,12 @@ template <int FMT, int POL = POL_STREAM> struct ALoader;
 // The column norm bound is raised by 1 %: it then also covers the FP32 rounding of
 // the squares it is summed from and of the products A_j^T u it is used to bound
 // (worst case m 2^-24 of ||A_j|| ||u||, 6e-5 at m = 1024).
+// In the underflow range the rounding is absolute: at most 2^-150 for each of the m squares and for
+// each product of A_j^T u, so kBoundFloor is added to a sum of squares and kDotFloor to a
+// bound of |A_j^T u|.
 constexpr float kBoundSlack = 1.01f;
+constexpr float kBoundFloor = 0x1p-138f;
+constexpr double kDotFloor = 0x1p-138;
 
 template <int POL> struct ALoader<FMT_F32, POL> {
   const float* base;

@@ -717,7 +717,7 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
       bnd = a.bound[k];
     } else {
       for (int s = 0; s < a.splits; ++s) bnd += a.bound[k * a.splits + s];
-      bnd = kBoundSlack * sqrtf(bnd);
+      bnd = kBoundSlack * sqrtf(bnd + kBoundFloor);
     }
   }
   const bool screen = bnd > 0.f && isfinite(bnd);
@@ -805,7 +805,8 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
       __syncthreads();
 #pragma unroll
       for (int q = 0; q < W; ++q) kmin = min(kmin, slot[q]);
-      kept = mu * (double)bnd * un < (double)__uint_as_float(kmin);
+      // (a normal number: the slack covers the rounding of mu g there)
+      kept = kmin >= 0x00800000u && mu * ((double)bnd * un + kDotFloor) < (double)__uint_as_float(kmin);
       if (kept) {
         for (int t = tid; t < rho; t += kT) {   // the entries this thread wrote above
           Tv[t] = gT[t];
@@ -1122,7 +1123,7 @@ __device__ __forceinline__ void au_body(const AUArgs& a, int blk, unsigned char*
       s += mx;
     }
     s = wave_sum(s);
-    if (lane == 0) a.bound[blk] = splits > 1 ? s : kBoundSlack * sqrtf(s);
+    if (lane == 0) a.bound[blk] = splits > 1 ? s : kBoundSlack * sqrtf(s + kBoundFloor);
   }
 
   // partial P of the waves sharing a chunk, added in column-split order.  In
