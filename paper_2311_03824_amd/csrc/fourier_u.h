@@ -281,6 +281,7 @@ __global__ __launch_bounds__(kFApplyRows) void k_fapply(FUpdArgs a) {
   constexpr int kPE = kFRMax * (kFRMax + 1) + kFRMax * kFRMax;   // complex values of a part
   __shared__ double tmp[2 * kPE];
   __shared__ double2 W[kPE], A[2 * kFRMax * kFRMax];
+  __shared__ __attribute__((aligned(16))) float2 rows[kFApplyRows][kFRMax + 1];   // second pass: rounded rows
   __shared__ double rdiag[kFRMax], eta_s;
   __shared__ int mode_s;
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), jb = blockIdx.x;
@@ -330,41 +331,49 @@ __global__ __launch_bounds__(kFApplyRows) void k_fapply(FUpdArgs a) {
       x[c] = make_double2(fma(-eta, (double)g[c].x, (double)u[c].x), fma(-eta, (double)g[c].y, (double)u[c].y));
     solve_row_c(x, A, rdiag, r);
   };
-  if (mode_s == 2) {   // an ill-conditioned X: once more on the rounded rows
-    for (int e = 0; e < E; ++e) {
-      int ra, rb;
-      tri_entry(e, r, ra, rb);
-      double sr = 0.0, si = 0.0;
-      for (int i = tid; i < n; i += kFApplyRows) {
-        float2 u[kFRMax], g[kFRMax];
+  const bool has_rows = jb * kFApplyRows < n;   // the last workgroup has none
+  if (mode_s == 2 && has_rows) {   // an ill-conditioned X: once more on the rounded rows, each solved once
+    const int grps = kFApplyRows / E, en = tid % E, gr = tid / E;   // a thread: an entry over every grps-th row
+    int ra, rb;
+    tri_entry(en, r, ra, rb);
+    double sr = 0.0, si = 0.0;
+    for (int i0 = 0; i0 < n; i0 += kFApplyRows) {
+      const int i = i0 + tid;
+      float2 u[kFRMax], g[kFRMax];   // rows at or beyond n are zero
 #pragma unroll
-        for (int c = 0; c < kFRMax; ++c) {
-          u[c] = c < r ? a.Uprev[(long long)i * r + c] : make_float2(0.f, 0.f);
-          g[c] = c < r ? a.G[(long long)i * r + c] : make_float2(0.f, 0.f);
-        }
-        row_x(u, g);
-        float2 xa = make_float2(0.f, 0.f), xb = xa;
+      for (int c = 0; c < kFRMax; ++c) {
+        u[c] = c < r && i < n ? a.Uprev[(long long)i * r + c] : make_float2(0.f, 0.f);
+        g[c] = c < r && i < n ? a.G[(long long)i * r + c] : make_float2(0.f, 0.f);
+      }
+      row_x(u, g);
 #pragma unroll
-        for (int c = 0; c < kFRMax; ++c) {
-          if (c == ra) xa = make_float2((float)x[c].x, (float)x[c].y);
-          if (c == rb) xb = make_float2((float)x[c].x, (float)x[c].y);
-        }
-        sr = fma((double)xa.x, (double)xb.x, fma((double)xa.y, (double)xb.y, sr));
-        si = fma((double)xa.x, (double)xb.y, fma(-(double)xa.y, (double)xb.x, si));
-      }
-      sr = wave_sum_dpp(sr);
-      si = wave_sum_dpp(si);
-      if (lane == 0) {
-        tmp[2 * wave] = sr;
-        tmp[2 * wave + 1] = si;
-      }
+      for (int c = 0; c < kFRMax; ++c)
+        if (c < r) rows[tid][c] = make_float2((float)x[c].x, (float)x[c].y);
       __syncthreads();
-      if (tid == 0) W[e] = make_double2((tmp[0] + tmp[2]) + (tmp[4] + tmp[6]), (tmp[1] + tmp[3]) + (tmp[5] + tmp[7]));
+      if (gr < grps) {
+#pragma unroll 8
+        for (int k = gr; k < kFApplyRows; k += grps) {
+          const float2 xa = rows[k][ra], xb = rows[k][rb];
+          sr = fma((double)xa.x, (double)xb.x, fma((double)xa.y, (double)xb.y, sr));
+          si = fma((double)xa.x, (double)xb.y, fma(-(double)xa.y, (double)xb.x, si));
+        }
+      }
       __syncthreads();
     }
+    double2* sum = reinterpret_cast<double2*>(&rows[0][0]);   // 4 KiB of 18
+    sum[tid] = make_double2(sr, si);
+    __syncthreads();
+    if (tid < E) {
+      for (int g = 1; g < grps; ++g) {
+        sr += sum[g * E + tid].x;
+        si += sum[g * E + tid].y;
+      }
+      W[tid] = make_double2(sr, si);
+    }
+    __syncthreads();
   }
   if (ok && j < n) row_x(ru, rg);
-  if (mode_s == 2) {
+  if (mode_s == 2 && has_rows) {
     __syncthreads();   // the first factor has been used
     if (wave == 0) {
       if (lane < rr) A[lane] = herm_entry(W, lane / r, lane % r, r);
@@ -384,7 +393,10 @@ __global__ __launch_bounds__(kFApplyRows) void k_fapply(FUpdArgs a) {
 #pragma unroll
     for (int c = 0; c < kFRMax; ++c)
       if (c < r) a.U[o + c] = make_float2((float)x[c].x, (float)x[c].y);
-  if (jb * kFApplyRows < n) return;
+  if (has_rows) {
+    if (!ok && jb == 0 && tid == 0) atomicOr(&a.ctl->err, 2);
+    return;
+  }
   // the last workgroup (no rows): eta, the residual of the iteration and the counters
   double s = 0.0;
   int fl = 0;
@@ -398,7 +410,6 @@ __global__ __launch_bounds__(kFApplyRows) void k_fapply(FUpdArgs a) {
   if (lane == 0) tmp[wave] = s;
   __syncthreads();
   if (tid == 0) {
-    if (!ok) atomicOr(&a.ctl->err, 2);
     if (first) {
       a.ctl->eta = eta;
       a.ctl->eta_set = 1;

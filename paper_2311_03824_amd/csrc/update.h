@@ -21,7 +21,7 @@
 // The factor comes from the FP64 Gram of the unrounded X, so one CholeskyQR pass gives
 // Q to FP32 rounding whenever cond(X)^2 2^-53 is far below it: a second pass is taken
 // only when the pivots span more than kPivotSpan (each workgroup then forms the Gram of
-// all the rounded rows itself: slow, and only for steps that nearly cancel U).
+// all the rounded rows itself, 256 rows at a time through LDS).
 #pragma once
 #include "launch.h"
 #include "uside.h"
@@ -130,6 +130,7 @@ struct UApplyShared {
   double sum[kUPartMax > kUApplyRows ? kUPartMax : kUApplyRows];
   double W[kUPartMax];
   double A[2 * kRMax * kRMax];              // the matrix to factor (L afterwards), scratch
+  __attribute__((aligned(16))) float rows[kUApplyRows][kRMax + 1];   // second pass: rounded rows
   double rdiag[kRMax];
   double eta;
   int mode;                                 // 0: the Gram is not positive definite, 1 or 2 passes
@@ -193,6 +194,7 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
   }
   __syncthreads();
   const double eta = S.eta;
+  const bool rows = jb * kUApplyRows < n;   // the last workgroup has none
   bool ok = S.mode != 0;
   double x[kRMax];
   if (ok && j < n) {
@@ -201,32 +203,44 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
       if (c < r) x[c] = fma(-eta, (double)rg[c], (double)ru[c]);
     solve_row(x, M, S.rdiag, r);
   }
-  if (S.mode == 2) {   // an ill-conditioned X: once more on the rounded rows
-    for (int e = 0; e < E; ++e) {
-      int ra, rb;
-      tri_entry(e, r, ra, rb);
-      double s = 0.0;
-      for (int i = tid; i < n; i += kUApplyRows) {
-        const long long oi = (long long)i * r;
-        double y[kRMax];
+  if (S.mode == 2 && rows) {   // an ill-conditioned X: once more on the rounded rows, each solved once
+    // their Gram by FP64 matrix products, four rows each: lane l holds column l % 16 of row l / 16 for both
+    // operands, and column l % 16 of rows l / 16 + 4 v of the result
+    typedef double f64x4 __attribute__((ext_vector_type(4)));
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+    for (int i0 = 0; i0 < n; i0 += kUApplyRows) {
+      const int i = i0 + tid;
+      double y[kRMax];
+      if (i != j) {
 #pragma unroll
         for (int c = 0; c < kRMax; ++c)
-          if (c < r) y[c] = fma(-eta, (double)a.gpart[oi + c], (double)a.Uprev[oi + c]);
+          y[c] = c < r && i < n ? fma(-eta, (double)a.gpart[(long long)i * r + c], (double)a.Uprev[(long long)i * r + c]) : 0.0;
         solve_row(y, M, S.rdiag, r);
-        double ya = 0.0, yb = 0.0;
+      } else {   // this workgroup's rows are in x
 #pragma unroll
-        for (int c = 0; c < kRMax; ++c) {
-          if (c == ra) ya = (double)(float)y[c];
-          if (c == rb) yb = (double)(float)y[c];
-        }
-        s = fma(ya, yb, s);
+        for (int c = 0; c < kRMax; ++c) y[c] = x[c];
       }
-      s = wave_sum_dpp(s);
-      if (lane == 0) S.sum[wave] = s;
+#pragma unroll
+      for (int c = 0; c < kRMax; ++c) S.rows[tid][c] = c < r && i < n ? (float)y[c] : 0.f;
       __syncthreads();
-      if (tid == 0) S.W[e] = (S.sum[0] + S.sum[1]) + (S.sum[2] + S.sum[3]);
+      float v[16];
+#pragma unroll
+      for (int s = 0; s < 16; ++s) v[s] = S.rows[64 * wave + 4 * s + (lane >> 4)][lane & 15];
+#pragma unroll
+      for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[s], (double)v[s], acc, 0, 0, 0);
       __syncthreads();
     }
+    double* sum = reinterpret_cast<double*>(&S.rows[0][0]);   // 4 x 256 of the waves
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sum[wave * 256 + ((lane >> 4) + 4 * v) * 16 + (lane & 15)] = acc[v];
+    __syncthreads();
+    if (tid < E) {
+      int ra, rb;
+      tri_entry(tid, r, ra, rb);
+      const int e = ra * 16 + rb;
+      S.W[tid] = (sum[e] + sum[256 + e]) + (sum[512 + e] + sum[768 + e]);
+    }
+    __syncthreads();
     if (wave == 0) {
       for (int e = lane; e < rr; e += 64) M[e] = S.W[tri_index(e / r, e % r, r)];
       double lo, hi;
@@ -246,7 +260,10 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
 #pragma unroll
     for (int c = 0; c < kRMax; ++c)
       if (c < r) a.U[o + c] = (float)x[c];
-  if (jb * kUApplyRows < n) return;
+  if (rows) {
+    if (!ok && jb == 0 && tid == 0 && a.ctl) atomicOr(&a.ctl->err, 2);
+    return;
+  }
   // the last workgroup (no rows): eta, then the residual of the iteration and the
   // counters, recorded whether or not the factorisation failed
   if (!a.ctl) {
@@ -265,7 +282,6 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
   if (lane == 0) S.sum[wave] = s;
   __syncthreads();
   if (tid == 0) {
-    if (!ok) atomicOr(&a.ctl->err, 2);
     if (first) {
       a.ctl->eta = eta;
       a.ctl->eta_set = 1;
