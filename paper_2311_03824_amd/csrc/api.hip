@@ -304,7 +304,7 @@ size_t carve(altgdmin_handle* h, void* base) {
   h->H = c.take<float>(q * n);
   h->colrr = c.take<double>(q);
   h->colflags = c.take<int>(q);
-  h->KS = grad_splits(p.q);
+  h->KS = sub_splits(p.n, p.q);
   h->KSu = upd_splits(p.n, p.q);
   h->gpart = c.take<float>((size_t)std::max(h->KS, h->KSu) * n * r);
   h->U = c.take<float>(n * r);
@@ -1601,7 +1601,8 @@ struct OpScratch {
   float* T;
   double* part;
   int* upd;
-  int KS;
+  float* zpart;
+  int KS, KSz;
   size_t base, bytes;
 };
 
@@ -1616,6 +1617,9 @@ static OpScratch op_scratch(void* base, int n, int q, int r) {
   s.base = c.off;
   s.part = c.take<double>(std::max(upd_part_doubles(n, r), sub_part_doubles(n, r)));
   s.upd = c.take<int>(1);
+  s.KSz = sub_splits(n, q);
+  s.zpart = c.take<float>(s.KSz > s.KS ? (size_t)s.KSz * n * r : 0);
+  if (s.KSz <= s.KS) s.zpart = s.gpart;
   s.bytes = c.off;
   return s;
 }
@@ -1678,10 +1682,10 @@ static int subspace_body(const float* L0t, int32_t n, int32_t q, int32_t r, cons
   else HIPCHK(launch_fill_basis(s.Utmp, n, r, st));
   SubArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.L0t = L0t; a.start = s.Utmp; a.U = U_out; a.V = s.Utmp; a.T = s.T; a.gpart = s.gpart; a.part = s.part;
+  a.L0t = L0t; a.start = s.Utmp; a.U = U_out; a.V = s.Utmp; a.T = s.T; a.gpart = s.zpart; a.part = s.part;
   a.n = n; a.q = q; a.r = r; a.iters = iters; a.tol = tol;
   a.ctl = s.ctl;
-  HIPCHK(launch_subspace(a, s.KS, st));
+  HIPCHK(launch_subspace(a, s.KSz, st));
   if (iters_out) HIPCHK(hipMemcpyAsync(iters_out, &s.ctl->power_it, sizeof(int), hipMemcpyDeviceToDevice, st));
   return ALTGDMIN_OK;
 }
@@ -1745,7 +1749,7 @@ int altgdmin_op_rank(const float* L0t, int32_t n, int32_t q, int32_t m, double e
 
 // kStaticParts: room for the parts (beyond OpScratch::base) of any sizes whose base fits
 // in ALTGDMIN_STATIC_SCRATCH_BYTES: n r <= 2^21 there, so at most 8 (n / 64 + 1) (2 r^2 +
-// r + 1) <= 8.7e6 bytes (r = 16).
+// r + 1) <= 8.7e6 bytes (r = 16); splits of L_0 T have 1.1e6 more, at n <= 8192 only.
 
 constexpr size_t kStaticParts = 9u << 20;
 static __device__ __align__(256) unsigned char scratch[ALTGDMIN_STATIC_SCRATCH_BYTES + kStaticParts];

@@ -89,6 +89,7 @@ hipError_t launch_sum_partials(const float* gpart, int KS, long long nr, float* 
 size_t upd_part_doubles(int n, int r);
 int uapply_blocks(int n);
 size_t sub_part_doubles(int n, int r);
+int sub_splits(int n, int q);   // column splits of L_0 T (planes of SubArgs::gpart)
 int roll_grace();   // the spectral starts' wait for late workgroups, in wall clock ticks
 hipError_t launch_subspace(const SubArgs& a, int max_splits, hipStream_t st);
 hipError_t launch_urows(const UpdArgs& a, hipStream_t st);

@@ -15,6 +15,7 @@
 // every sum runs in a fixed order, so results depend neither on timing nor on how many
 // workgroups take part.
 #pragma once
+#include <algorithm>
 #include <cstdlib>
 
 #include "launch.h"
@@ -26,7 +27,8 @@ namespace altg {
 namespace {
 
 constexpr int kSubThreads = 256, kSubWaves = kSubThreads / 64;
-constexpr int kSubBlocksMax = 96;
+constexpr int kSubBlocksMax = 256;
+constexpr int kSubSplitCols = 32, kSubSplitsMax = 32;
 
 struct SubShared {
   union {
@@ -78,6 +80,7 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
   Meeting meet(a.ctl);
   if (!meet.join(a.grace, &S.roll)) return;
   const int me = meet.id, nblk = meet.count;
+  const int CG = max(1, min(4, (q + 16 * nblk - 1) / (16 * nblk)));   // 16-column blocks a workgroup takes at once
 
   // dst = Q of the thin QR of z (rows of z already in place: summed over `splits` splits,
   // which end in split 0); with old, also the parts of old^T dst.  False if z is rank
@@ -90,7 +93,15 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
         float x = 0.f;
         if (base + i < nr) {
           x = z[base + i];
-          for (int s = 1; s < splits; ++s) x += z[s * nr + base + i];
+          int s = 1;
+          for (; s + 8 <= splits; s += 8) {   // in order, the loads eight at a time
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = z[(s + u) * nr + base + i];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x += v[u];
+          }
+          for (; s < splits; ++s) x += z[s * nr + base + i];
           if (splits > 1) z[base + i] = x;
         }
         S.rows.X[i] = (double)x;
@@ -167,54 +178,60 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
   bool ok = orth(a.start, 1, cur, nullptr);
   bool pending = false;
   for (int p = 0; ok && p < a.iters; ++p) {
-    // T = L_0^T U on the matrix cores, 16 columns k by r per workgroup, the rows j split
-    // over its waves 16 at a time: lane (i, p) holds 4 rows of column i, and the four
-    // products of a group take row 4 p + e of it, e = 0..3, for both operands.
-    for (int k0 = me * 16; k0 < q; k0 += nblk * 16) {
+    // T = L_0^T U on the matrix cores, 16 columns k by r at a time, the rows j split over the
+    // workgroup's waves 16 at a time: lane (i, p) holds 4 rows of column i, and the four
+    // products of a group take row 4 p + e of it, e = 0..3, for both operands.  Up to four such blocks of
+    // columns go through LDS together, where each workgroup has that many.
+    for (int kb = me * 16 * CG; kb < q; kb += nblk * 16 * CG) {
       typedef float f32x4 __attribute__((ext_vector_type(4)));
       const int i = lane & 15, p4 = 4 * (lane >> 4);
-      const float* row = a.L0t + (long long)(k0 + i < q ? k0 + i : q - 1) * n;
-      constexpr int SU = 4;   // 16-row groups in flight per wave
-      // eight sums of n / 32 terms per wave, added as a tree: one chain of n / 4 products rounds worse than
-      // the sums over lanes it replaced (U against FP64 at n = q = 1000: 1.3e-7 where those gave 0.93e-7 and these
-      // 0.96e-7; 12 us of 415)
-      f32x4 acc[2][4];
+      __syncthreads();
+      for (int cg = 0; cg < CG && kb + 16 * cg < q; ++cg) {
+        const int k = kb + 16 * cg + i;
+        const float* row = a.L0t + (long long)(k < q ? k : q - 1) * n;
+        constexpr int SU = 4;   // 16-row groups in flight per wave
+        // eight sums of n / 32 terms per wave, added as a tree: one chain of n / 4 products rounds worse than
+        // the sums over lanes it replaced (U against FP64 at n = q = 1000: 1.3e-7 where those gave 0.93e-7 and these
+        // 0.96e-7; 12 us of 415)
+        f32x4 acc[2][4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[0][e] = acc[1][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      for (int s0 = wave * 16; s0 < n; s0 += kSubWaves * 16 * SU) {
-        float x[SU][4], u[SU][4];
+        for (int e = 0; e < 4; ++e) acc[0][e] = acc[1][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int s0 = wave * 16; s0 < n; s0 += kSubWaves * 16 * SU) {
+          float x[SU][4], u[SU][4];
 #pragma unroll
-        for (int g = 0; g < SU; ++g) {
-          const int j = s0 + g * kSubWaves * 16 + p4;
-          if (j + 4 <= n) {
-            const f32x4_u v = *reinterpret_cast<const f32x4_u*>(row + j);
-            x[g][0] = v.x; x[g][1] = v.y; x[g][2] = v.z; x[g][3] = v.w;
-          } else {
+          for (int g = 0; g < SU; ++g) {
+            const int j = s0 + g * kSubWaves * 16 + p4;
+            if (j + 4 <= n) {
+              const f32x4_u v = *reinterpret_cast<const f32x4_u*>(row + j);
+              x[g][0] = v.x; x[g][1] = v.y; x[g][2] = v.z; x[g][3] = v.w;
+            } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[g][e] = j + e < n ? row[j + e] : 0.f;
+              for (int e = 0; e < 4; ++e) x[g][e] = j + e < n ? row[j + e] : 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) u[g][e] = i < r && j + e < n ? cur[(long long)(j + e) * r + i] : 0.f;
           }
 #pragma unroll
-          for (int e = 0; e < 4; ++e) u[g][e] = i < r && j + e < n ? cur[(long long)(j + e) * r + i] : 0.f;
+          for (int g = 0; g < SU; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              acc[g & 1][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[g][e], u[g][e], acc[g & 1][e], 0, 0, 0);
         }
+        const f32x4 sum = ((acc[0][0] + acc[1][0]) + (acc[0][1] + acc[1][1])) +
+                          ((acc[0][2] + acc[1][2]) + (acc[0][3] + acc[1][3]));
+        // lane (i, p) holds column i of rows 4 p .. 4 p + 3 of the 16 x 16 result
 #pragma unroll
-        for (int g = 0; g < SU; ++g)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            acc[g & 1][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[g][e], u[g][e], acc[g & 1][e], 0, 0, 0);
+        for (int e = 0; e < 4; ++e) S.red[wave][16 * cg + p4 + e][i] = sum[e];
       }
-      const f32x4 sum = ((acc[0][0] + acc[1][0]) + (acc[0][1] + acc[1][1])) +
-                        ((acc[0][2] + acc[1][2]) + (acc[0][3] + acc[1][3]));
-      // lane (i, p) holds column i of rows 4 p .. 4 p + 3 of the 16 x 16 result
       __syncthreads();
-#pragma unroll
-      for (int e = 0; e < 4; ++e) S.red[wave][p4 + e][i] = sum[e];
-      __syncthreads();
-      for (int t = tid; t < 16 * r; t += kSubThreads) {
+      for (int t = tid; t < 16 * CG * r; t += kSubThreads) {
         const int kk = t / r, c = t - kk * r;
-        float v = S.red[0][kk][c];
+        if (kb + kk < q) {
+          float v = S.red[0][kk][c];
 #pragma unroll
-        for (int w = 1; w < kSubWaves; ++w) v += S.red[w][kk][c];
-        if (k0 + kk < q) a.T[(long long)(k0 + kk) * r + c] = v;
+          for (int w = 1; w < kSubWaves; ++w) v += S.red[w][kk][c];
+          a.T[(long long)(kb + kk) * r + c] = v;
+        }
       }
     }
     meet();
@@ -296,12 +313,12 @@ static int sub_blocks(int n, int q) {
   return b < kSubBlocksMax ? b : kSubBlocksMax;
 }
 
-// Column splits of Z: a 64-row unit per workgroup with at least 32 columns each, at most
-// max_splits (the buffers).
-static int sub_splits(int n, int q, int max_splits) {
+// Column splits of Z: a 64-row unit per workgroup with at least kSubSplitCols columns each, at
+// most kSubSplitsMax.
+int sub_splits(int n, int q) {
   int ks = sub_blocks(n, q) / ((n + 63) / 64);
-  if (ks > q / 32) ks = q / 32;
-  if (ks > max_splits) ks = max_splits;
+  if (ks > q / kSubSplitCols) ks = q / kSubSplitCols;
+  if (ks > kSubSplitsMax) ks = kSubSplitsMax;
   return ks < 1 ? 1 : ks;
 }
 
@@ -317,7 +334,7 @@ int roll_grace() {
 hipError_t launch_subspace(const SubArgs& a_in, int max_splits, hipStream_t st) {
   SubArgs a = a_in;
   a.grace = roll_grace();
-  a.KS = sub_splits(a.n, a.q, max_splits);
+  a.KS = std::min(sub_splits(a.n, a.q), max_splits);
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
   hipLaunchKernelGGL(k_subspace, dim3(sub_blocks(a.n, a.q)), dim3(kSubThreads), 0, st, a);
   return hipGetLastError();
