@@ -1204,8 +1204,12 @@ constexpr int default_aud(int R, int FMT = FMT_F32) {
 // default depths keep more waves resident.  The depth only moves loads: the
 // arithmetic, and so every bit, is the same.
 constexpr int deep_aud(int R, int = FMT_F32) { return R <= 4 ? 4 : 3; }
-// 8-wave workgroups: six loads in flight up to R = 10 (one workgroup per CU: 1.13 against 1.16 ms
-// at n = 16384, q = 100, m = 1000 in two splits; above, the registers do not hold them).
+// 8-wave workgroups, with at most kDeepAuColumns of them (one per CU): six loads in flight up to R = 10
+// (1.13 against 1.16 ms at n = 16384, q = 100, m = 1000 in two splits, 0.196 against 0.238 at n = 2000, q = 200,
+// m = 520, r = 8; at n = 300 the two are within 1.5 us; above R = 10 the registers do not hold them).  Above 256
+// workgroups their registers leave room for one per CU, and the depths of the deep variants win: n = 300,
+// m = 100, r = 7 26 against 39 us at q = 260, n = 1000, m = 400, r = 10 124 against 148, n = 2000, m = 520,
+// r = 8 298 against 382.
 // The Philox form has no loads: three keep its loop short (0.17 against 0.20 ms at n = 777, q = 333, m = 301, r = 7).
 constexpr int wide_aud(int R, int fmt) { return R <= 10 && fmt != FMT_PHILOX ? 6 : (R <= 4 ? 4 : 3); }
 constexpr int kDeepAuColumns = 256;
@@ -1287,19 +1291,22 @@ static const au_fn kAUDeep[3][kRMax / 2] = {AUD_ROW(FMT_F32), AUD_ROW(FMT_BF16X2
                      k_au_grp<F, 10, POL_STREAM, deep_aud(10)>, k_au_grp<F, 12, POL_STREAM, deep_aud(12)>, \
                      k_au_grp<F, 14, POL_STREAM, deep_aud(14)>, k_au_grp<F, 16, POL_STREAM, deep_aud(16)>}
 static const aug_fn kAUGrpDeep[3][kRMax / 2] = {AUGD_ROW(FMT_F32), AUGD_ROW(FMT_BF16X2), AUGD_ROW(FMT_BF16HI)};
-// 8-wave workgroups (problems of at most 512 columns, with the deep depths; every
+// 8-wave workgroups (problems of at most 512 columns, with the deep or wide depths; every
 // format, so that the width, and with it the bits, do not depend on how A is held)
-#define AU8_ROW(F) {k_au<F, 2, wide_aud(2, F), POL_STREAM, 8>, k_au<F, 4, wide_aud(4, F), POL_STREAM, 8>,     \
-                    k_au<F, 6, wide_aud(6, F), POL_STREAM, 8>, k_au<F, 8, wide_aud(8, F), POL_STREAM, 8>,     \
-                    k_au<F, 10, wide_aud(10, F), POL_STREAM, 8>, k_au<F, 12, wide_aud(12, F), POL_STREAM, 8>, \
-                    k_au<F, 14, wide_aud(14, F), POL_STREAM, 8>, k_au<F, 16, wide_aud(16, F), POL_STREAM, 8>}
-static const au_fn kAU8[4][kRMax / 2] = {AU8_ROW(FMT_F32), AU8_ROW(FMT_BF16X2), AU8_ROW(FMT_BF16HI), AU8_ROW(FMT_PHILOX)};
-#define AUG8_ROW(F) {k_au_grp<F, 2, POL_STREAM, wide_aud(2, F), 8>, k_au_grp<F, 4, POL_STREAM, wide_aud(4, F), 8>,     \
-                     k_au_grp<F, 6, POL_STREAM, wide_aud(6, F), 8>, k_au_grp<F, 8, POL_STREAM, wide_aud(8, F), 8>,     \
-                     k_au_grp<F, 10, POL_STREAM, wide_aud(10, F), 8>, k_au_grp<F, 12, POL_STREAM, wide_aud(12, F), 8>, \
-                     k_au_grp<F, 14, POL_STREAM, wide_aud(14, F), 8>, k_au_grp<F, 16, POL_STREAM, wide_aud(16, F), 8>}
-static const aug_fn kAUGrp8[4][kRMax / 2] = {AUG8_ROW(FMT_F32), AUG8_ROW(FMT_BF16X2), AUG8_ROW(FMT_BF16HI),
-                                             AUG8_ROW(FMT_PHILOX)};
+#define AU8_ROW(F, D) {k_au<F, 2, D(2, F), POL_STREAM, 8>, k_au<F, 4, D(4, F), POL_STREAM, 8>, \
+                    k_au<F, 6, D(6, F), POL_STREAM, 8>, k_au<F, 8, D(8, F), POL_STREAM, 8>, \
+                    k_au<F, 10, D(10, F), POL_STREAM, 8>, k_au<F, 12, D(12, F), POL_STREAM, 8>, \
+                    k_au<F, 14, D(14, F), POL_STREAM, 8>, k_au<F, 16, D(16, F), POL_STREAM, 8>}
+static const au_fn kAU8[2][4][kRMax / 2] = {   // [at most kDeepAuColumns workgroups]
+    {AU8_ROW(FMT_F32, deep_aud), AU8_ROW(FMT_BF16X2, deep_aud), AU8_ROW(FMT_BF16HI, deep_aud), AU8_ROW(FMT_PHILOX, deep_aud)},
+    {AU8_ROW(FMT_F32, wide_aud), AU8_ROW(FMT_BF16X2, wide_aud), AU8_ROW(FMT_BF16HI, wide_aud), AU8_ROW(FMT_PHILOX, wide_aud)}};
+#define AUG8_ROW(F, D) {k_au_grp<F, 2, POL_STREAM, D(2, F), 8>, k_au_grp<F, 4, POL_STREAM, D(4, F), 8>, \
+                     k_au_grp<F, 6, POL_STREAM, D(6, F), 8>, k_au_grp<F, 8, POL_STREAM, D(8, F), 8>, \
+                     k_au_grp<F, 10, POL_STREAM, D(10, F), 8>, k_au_grp<F, 12, POL_STREAM, D(12, F), 8>, \
+                     k_au_grp<F, 14, POL_STREAM, D(14, F), 8>, k_au_grp<F, 16, POL_STREAM, D(16, F), 8>}
+static const aug_fn kAUGrp8[2][4][kRMax / 2] = {
+    {AUG8_ROW(FMT_F32, deep_aud), AUG8_ROW(FMT_BF16X2, deep_aud), AUG8_ROW(FMT_BF16HI, deep_aud), AUG8_ROW(FMT_PHILOX, deep_aud)},
+    {AUG8_ROW(FMT_F32, wide_aud), AUG8_ROW(FMT_BF16X2, wide_aud), AUG8_ROW(FMT_BF16HI, wide_aud), AUG8_ROW(FMT_PHILOX, wide_aud)}};
 
 // the workgroup width of the A_k U kernels for a launch: 8 waves when asked for, else 4
 static inline int au_width(int waves) { return waves == 8 ? 8 : kWaves; }
@@ -1335,7 +1342,7 @@ hipError_t launch_au(int fmt, const AUArgs& a, hipStream_t st, int pol) {
   const int splits = w == 8 && a.splits > 1 ? a.splits : 1;
   const AULayout lay(au_split_rows(a.m, splits), a.r, fmt == FMT_PHILOX, w);
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  const au_fn f = w == 8 ? kAU8[fmt][ri]
+  const au_fn f = w == 8 ? kAU8[a.q * splits <= kDeepAuColumns][fmt][ri]
                          : ((fmt != FMT_PHILOX && a.q <= kDeepAuColumns) ? kAUDeep[fmt][ri] : kAUTable[fmt][ri]);
   hipLaunchKernelGGL(f, dim3(a.q * splits), dim3(64 * w), lay.total, st, a);
   return hipGetLastError();
@@ -1368,7 +1375,7 @@ hipError_t launch_au_grp(int fmt, int rmax, int waves, const AUArgs* tab, const 
   }
   const int ri = (rmax + 1) / 2 - 1, w = au_width(waves);
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  const aug_fn f = w == 8 ? kAUGrp8[fmt][ri]
+  const aug_fn f = w == 8 ? kAUGrp8[blocks <= kDeepAuColumns][fmt][ri]
                           : ((fmt != FMT_PHILOX && blocks <= kDeepAuColumns) ? kAUGrpDeep[fmt][ri]
                                                                               : kAUGrpTable[fmt][ri]);
   hipLaunchKernelGGL(f, dim3(blocks), dim3(64 * w), lds, st, tab, map);
@@ -1627,17 +1634,21 @@ static const au_fn3 kAUCached[2][3][kRMax / 2] = {
 static const aug_fn3 kAUGrpCached[2][3][kRMax / 2] = {
     {AUGC_F(FMT_F32, default_aud), AUGC_F(FMT_BF16X2, default_aud), AUGC_F(FMT_BF16HI, default_aud)},
     {AUGC_F(FMT_F32, deep_aud), AUGC_F(FMT_BF16X2, deep_aud), AUGC_F(FMT_BF16HI, deep_aud)}};
-// 8-wave workgroups (deep depths), as in the streaming tables
-#define AUC8_F(F) {k_au<F, 2, wide_aud(2, F), POL_CACHED, 8>, k_au<F, 4, wide_aud(4, F), POL_CACHED, 8>,     \
-                   k_au<F, 6, wide_aud(6, F), POL_CACHED, 8>, k_au<F, 8, wide_aud(8, F), POL_CACHED, 8>,     \
-                   k_au<F, 10, wide_aud(10, F), POL_CACHED, 8>, k_au<F, 12, wide_aud(12, F), POL_CACHED, 8>, \
-                   k_au<F, 14, wide_aud(14, F), POL_CACHED, 8>, k_au<F, 16, wide_aud(16, F), POL_CACHED, 8>}
-static const au_fn3 kAUCached8[3][kRMax / 2] = {AUC8_F(FMT_F32), AUC8_F(FMT_BF16X2), AUC8_F(FMT_BF16HI)};
-#define AUGC8_F(F) {k_au_grp<F, 2, POL_CACHED, wide_aud(2, F), 8>, k_au_grp<F, 4, POL_CACHED, wide_aud(4, F), 8>,     \
-                    k_au_grp<F, 6, POL_CACHED, wide_aud(6, F), 8>, k_au_grp<F, 8, POL_CACHED, wide_aud(8, F), 8>,     \
-                    k_au_grp<F, 10, POL_CACHED, wide_aud(10, F), 8>, k_au_grp<F, 12, POL_CACHED, wide_aud(12, F), 8>, \
-                    k_au_grp<F, 14, POL_CACHED, wide_aud(14, F), 8>, k_au_grp<F, 16, POL_CACHED, wide_aud(16, F), 8>}
-static const aug_fn3 kAUGrpCached8[3][kRMax / 2] = {AUGC8_F(FMT_F32), AUGC8_F(FMT_BF16X2), AUGC8_F(FMT_BF16HI)};
+// 8-wave workgroups, as in the streaming tables
+#define AUC8_F(F, D) {k_au<F, 2, D(2, F), POL_CACHED, 8>, k_au<F, 4, D(4, F), POL_CACHED, 8>, \
+                   k_au<F, 6, D(6, F), POL_CACHED, 8>, k_au<F, 8, D(8, F), POL_CACHED, 8>, \
+                   k_au<F, 10, D(10, F), POL_CACHED, 8>, k_au<F, 12, D(12, F), POL_CACHED, 8>, \
+                   k_au<F, 14, D(14, F), POL_CACHED, 8>, k_au<F, 16, D(16, F), POL_CACHED, 8>}
+static const au_fn3 kAUCached8[2][3][kRMax / 2] = {
+    {AUC8_F(FMT_F32, deep_aud), AUC8_F(FMT_BF16X2, deep_aud), AUC8_F(FMT_BF16HI, deep_aud)},
+    {AUC8_F(FMT_F32, wide_aud), AUC8_F(FMT_BF16X2, wide_aud), AUC8_F(FMT_BF16HI, wide_aud)}};
+#define AUGC8_F(F, D) {k_au_grp<F, 2, POL_CACHED, D(2, F), 8>, k_au_grp<F, 4, POL_CACHED, D(4, F), 8>, \
+                    k_au_grp<F, 6, POL_CACHED, D(6, F), 8>, k_au_grp<F, 8, POL_CACHED, D(8, F), 8>, \
+                    k_au_grp<F, 10, POL_CACHED, D(10, F), 8>, k_au_grp<F, 12, POL_CACHED, D(12, F), 8>, \
+                    k_au_grp<F, 14, POL_CACHED, D(14, F), 8>, k_au_grp<F, 16, POL_CACHED, D(16, F), 8>}
+static const aug_fn3 kAUGrpCached8[2][3][kRMax / 2] = {
+    {AUGC8_F(FMT_F32, deep_aud), AUGC8_F(FMT_BF16X2, deep_aud), AUGC8_F(FMT_BF16HI, deep_aud)},
+    {AUGC8_F(FMT_F32, wide_aud), AUGC8_F(FMT_BF16X2, wide_aud), AUGC8_F(FMT_BF16HI, wide_aud)}};
 
 static int cached_width_row(int waves) { return waves == 8 ? 1 : (waves == 0 || waves == kWaves ? 0 : -1); }
 
@@ -1700,7 +1711,7 @@ hipError_t launch_au_cached(int fmt, const AUArgs& a, hipStream_t st) {
   const int splits = w == 8 && a.splits > 1 ? a.splits : 1;
   const AULayout lay(au_split_rows(a.m, splits), a.r, 0, w);
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  const au_fn3 f = w == 8 ? kAUCached8[fmt][ri] : kAUCached[a.q <= kDeepAuColumns][fmt][ri];
+  const au_fn3 f = w == 8 ? kAUCached8[a.q * splits <= kDeepAuColumns][fmt][ri] : kAUCached[a.q <= kDeepAuColumns][fmt][ri];
   hipLaunchKernelGGL(f, dim3(a.q * splits), dim3(64 * w), lay.total, st, a);
   return hipGetLastError();
 }
@@ -1710,7 +1721,7 @@ hipError_t launch_au_grp_cached(int fmt, int rmax, int waves, const AUArgs* tab,
   if (fmt < FMT_F32 || fmt > FMT_BF16HI) return hipErrorNotSupported;
   const int ri = (rmax + 1) / 2 - 1, w = waves == 8 ? 8 : kWaves;
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  const aug_fn3 f = w == 8 ? kAUGrpCached8[fmt][ri] : kAUGrpCached[blocks <= kDeepAuColumns][fmt][ri];
+  const aug_fn3 f = w == 8 ? kAUGrpCached8[blocks <= kDeepAuColumns][fmt][ri] : kAUGrpCached[blocks <= kDeepAuColumns][fmt][ri];
   hipLaunchKernelGGL(f, dim3(blocks), dim3(64 * w), lds, st, tab, map);
   return hipGetLastError();
 }
