@@ -193,6 +193,7 @@ struct altgdmin_handle {
   double* colrr;
   int* colflags;
   float* colbound;
+  float* colstep;          // step lengths of the columns' last IHT steps
   float* gpart;
   int KS;                  // column splits of the subspace iteration
   int KSu;                 // column splits of the gradient
@@ -314,6 +315,7 @@ size_t carve(altgdmin_handle* h, void* base) {
   h->rlog_len = h->par.t_max > 0 ? h->par.t_max : 1;
   h->rlog = c.take<double>(h->rlog_len);
   h->colbound = c.take<float>(q * asp);
+  h->colstep = c.take<float>(q);
   h->upart = c.take<double>(std::max(upd_part_doubles(p.n, (int)r), sub_part_doubles(p.n, (int)r)));
   h->upd = c.take<int>(1);
   if (p.r == 0) h->rank_ws = c.take<unsigned char>(rank_scratch(nullptr, rank_shape(p.n, p.q, p.m)).bytes);
@@ -422,6 +424,7 @@ ColArgs col_args(const altgdmin_handle* h) {
   a.P = h->P; a.Ginv = h->Ginv; a.Tidx = h->Tidx; a.Tval = h->Tval;
   a.H = h->H; a.Bt = h->Bt; a.rr = h->colrr; a.flags = h->colflags;
   a.seed = p.a_seed; a.table = p.normal_table;
+  a.step = h->colstep;   // the initialisation's launch writes it first
   a.waves = h->col_waves;
   return a;
 }

@@ -72,6 +72,7 @@ struct ColArgs {
   int waves;                // waves of the column workgroup: 4 (also for 0), 8 or 16
   const float* bound;       // optional q: an upper bound of every ||(A_k)_j|| (A_k U kernel); lets a step that
                             // provably keeps its support read the support columns alone
+  float* step;              // optional q, in/out: the step length of the column's last IHT step (0: not known)
   int splits;               // row splits of the A_k U launch (0 and 1: none).  Above 1, Ginv holds the Gram of every
                             // split (q x splits x r x r) and bound its part (q x splits): this kernel adds and inverts
 };

@@ -721,6 +721,7 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     }
   }
   const bool screen = bnd > 0.f && isfinite(bnd);
+  float mu_last = screen && a.step ? a.step[k] : 0.f;
   int* list = reinterpret_cast<int*>(gl);   // rho entries, then the rho values of g on T (2 rho <= n)
   float* gT = gl + rho;
   bool have_list = false;
@@ -741,8 +742,10 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     if (a.project) project<NC, W>(v, ln, Pv, Gi, r, lane, wave, cbuf, nullptr);
 
     const bool last = (it == a.tau - 1);
-    // the test can only hold when ||u|| / bound, a lower estimate of its left side, is
-    // below the smallest magnitude of s
+    // the support columns are read first where the test would hold with a quarter of the step length of the
+    // last step (with none, of 1 / bound^2), so that a test that keeps failing, as with one long column in A_k,
+    // is not paid for in every step: up to rho / n of a pass.  Step lengths vary by a small factor from step to
+    // step when rho is small (the whole of it gave 1 % at n = q = 100, rho = 2).
     bool on_T = false;
     double un = 0.0;
     if (screen && hasT && !(last && a.G_out)) {
@@ -754,7 +757,7 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
         for (int o = 32; o > 0; o >>= 1) smin = min(smin, (unsigned)__shfl_xor((int)smin, o));
         have_smin = true;
       }
-      on_T = un < (double)bnd * (double)__uint_as_float(smin);
+      on_T = (mu_last > 0.f ? 0.25 * (double)mu_last * (double)bnd * un : un / (double)bnd) < (double)__uint_as_float(smin);
     }
 
     // g = A_k^T u; w = A_k g_T on the current support; mu.  A step whose test holds
@@ -789,6 +792,7 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
       if (a.project) project<NC, W>(w, ln, Pv, Gi, r, lane, wave, cbuf, nullptr);
       const double ww = sumsq<NC>(w);
       mu = (ww > 0.0 && isfinite(ww) && isfinite(gT2)) ? gT2 / ww : 0.0;
+      mu_last = (float)mu;
       if (!on_T) break;
       // s - mu g on T, its smallest magnitude (0 if one is NaN) against the bound off T
       unsigned* slot = reinterpret_cast<unsigned*>(hist);
@@ -852,6 +856,7 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     hasT = true;
   }
 
+  if (a.step && tid == 0) a.step[k] = mu_last;
   if (a.tail != TAIL_NONE) {
     gather<GF, NC, W>(L, ln, Ti, Tv, hasT ? rho : 0, v, wpart, mq, wave);
 #pragma unroll
