@@ -42,18 +42,20 @@ union URowsShared {
 };
 
 // One column split of the gradient: rows of block jb over the columns of split ks.
+template <int WV>
 __device__ __forceinline__ void ugrad_body(const UpdArgs& a, int jb, int ks, float (*red)[64][kRMax + 1]) {
   if (a.gate_done && a.ctl->done) return;
   const int k0 = (int)((long long)a.q * ks / a.KS), k1 = (int)((long long)a.q * (ks + 1) / a.KS);
   const long long nr = (long long)a.n * a.r, base = (long long)jb * 64 * a.r;
-  urows_grad_r<kUGradWaves>(a.H, a.B, a.n, a.r, jb, k0, k1, red, [&](int i, float g) {
+  urows_grad_r<WV>(a.H, a.B, a.n, a.r, jb, k0, k1, red, [&](int i, float g) {
     if (base + i < nr) a.gpart[ks * nr + base + i] = g;
   });
 }
 
-__global__ __launch_bounds__(64 * kUGradWaves) void k_ugrad(UpdArgs a) {
-  __shared__ float red[kUGradWaves][64][kRMax + 1];
-  ugrad_body(a, blockIdx.x, blockIdx.y, red);
+template <int WV>
+__global__ __launch_bounds__(64 * WV) void k_ugrad(UpdArgs a) {
+  __shared__ float red[WV > 8 ? 8 : WV][64][kRMax + 1];
+  ugrad_body<WV>(a, blockIdx.x, blockIdx.y, red);
 }
 
 // Several problems in one launch: block b is (problem, row block, split) = map[b].
@@ -61,7 +63,7 @@ __global__ __launch_bounds__(64 * kUGradWaves) void k_ugrad_grp(const UpdArgs* t
   __shared__ float red[kUGradWaves][64][kRMax + 1];
   const int4 mp = map[blockIdx.x];
   const UpdArgs a = tab[mp.x];
-  ugrad_body(a, mp.y, mp.z, red);
+  ugrad_body<kUGradWaves>(a, mp.y, mp.z, red);
 }
 
 __device__ __forceinline__ void urows_body(const UpdArgs& a, int jb, URowsShared& S) {
@@ -272,7 +274,22 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
   }
   double s = 0.0;
   int fl = 0;
-  for (int k = tid; k < a.q; k += kUApplyRows) {
+  int k = tid;
+  for (; k + 7 * kUApplyRows < a.q; k += 8 * kUApplyRows) {   // in order, the loads eight at a time
+    double v[8];
+    int f[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      v[u] = a.colrr[k + u * kUApplyRows];
+      f[u] = a.colflags[k + u * kUApplyRows];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      s += v[u];
+      fl |= f[u];
+    }
+  }
+  for (; k < a.q; k += kUApplyRows) {
     s += a.colrr[k];
     fl |= a.colflags[k];
   }
@@ -309,7 +326,14 @@ int uapply_blocks(int n) { return (n + kUApplyRows - 1) / kUApplyRows + 1; }
 
 hipError_t launch_ugrad(const UpdArgs& a, hipStream_t st) {
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  hipLaunchKernelGGL(k_ugrad, dim3((a.n + 63) / 64, a.KS), dim3(64 * kUGradWaves), 0, st, a);
+  const dim3 grid((a.n + 63) / 64, a.KS);
+  // A GDmin iteration takes 4 waves whatever the launch, so that its sums do not depend on it.  The entry point has few
+  // splits (the scratch); where they leave CUs idle, 16 waves: n = 100, q = 20,000, r = 4 53 against 104 us,
+  // n = q = 2000, r = 8 (128 workgroups) 14.3 against 20, n = q = 1000, r = 10 14 against 15.4.
+  if (!a.ctl && grid.x * grid.y <= 128)
+    hipLaunchKernelGGL(k_ugrad<kGradWaves>, grid, dim3(64 * kGradWaves), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_ugrad<kUGradWaves>, grid, dim3(64 * kUGradWaves), 0, st, a);
   return hipGetLastError();
 }
 
