@@ -1595,8 +1595,9 @@ int altgdmin_op_measure(const altgdmin_problem* prob, const double* Xt, float* Y
   return ALTGDMIN_OK;
 }
 
-// scratch layout of the U-side entry points: Ctl | gpart (KS n r) | Utmp (n r) | T (q r),
-// (base), then the parts of the U update and the subspace iteration
+// scratch layout of the U-side entry points: Ctl | gpart (KS n r) | Utmp (n r) | T (q r)
+// (base, with which every one of them runs), then what the faster forms take: the parts of the U update and
+// the subspace iteration, and the latter's column splits
 struct OpScratch {
   Ctl* ctl;
   float* gpart;
@@ -1655,7 +1656,8 @@ int altgdmin_op_qr_step(const float* U, const float* grad, int32_t n, int32_t r,
     return fail(ALTGDMIN_EINVAL, "bad qr arguments");
   NEED_STREAM(stream);
   OpScratch s = op_scratch(scratch, n, 1, r);
-  if (scratch_bytes < s.bytes) return fail(ALTGDMIN_ENOWS, "scratch too small");
+  if (scratch_bytes < s.base) return fail(ALTGDMIN_ENOWS, "scratch too small");
+  const bool room = scratch_bytes >= s.bytes;
   hipStream_t st = static_cast<hipStream_t>(stream);
   HIPCHK(launch_copy_f(U_out, U, (long long)n * r, st));
   UpdArgs a;
@@ -1663,7 +1665,8 @@ int altgdmin_op_qr_step(const float* U, const float* grad, int32_t n, int32_t r,
   a.n = n; a.r = r; a.KS = 1;
   a.gpart = const_cast<float*>(grad);   // read only with KS = 1
   a.U = U_out; a.Uprev = s.Utmp;
-  a.part = s.part; a.upd = s.upd;
+  a.part = room ? s.part : nullptr;
+  a.upd = room ? s.upd : &s.ctl->bar;
   a.eta_c = eta_c; a.eta_io = eta_io;
   HIPCHK(launch_urows(a, st));
   HIPCHK(launch_uapply(a, st));
@@ -1678,17 +1681,19 @@ static int subspace_body(const float* L0t, int32_t n, int32_t q, int32_t r, cons
                          double tol, float* U_out, int32_t* iters_out, void* scratch, size_t scratch_bytes,
                          void* stream) {
   OpScratch s = op_scratch(scratch, n, q, r);
-  if (scratch_bytes < s.bytes) return fail(ALTGDMIN_ENOWS, "scratch too small");
+  if (scratch_bytes < s.base) return fail(ALTGDMIN_ENOWS, "scratch too small");
+  const bool room = scratch_bytes >= s.bytes;
   hipStream_t st = static_cast<hipStream_t>(stream);
   HIPCHK(launch_reset_ctl(s.ctl, 1, st));
   if (U_start) HIPCHK(launch_copy_f(s.Utmp, U_start, (long long)n * r, st));
   else HIPCHK(launch_fill_basis(s.Utmp, n, r, st));
   SubArgs a;
   std::memset(&a, 0, sizeof(a));
-  a.L0t = L0t; a.start = s.Utmp; a.U = U_out; a.V = s.Utmp; a.T = s.T; a.gpart = s.zpart; a.part = s.part;
+  a.L0t = L0t; a.start = s.Utmp; a.U = U_out; a.V = s.Utmp; a.T = s.T;
+  a.gpart = room ? s.zpart : s.gpart; a.part = room ? s.part : nullptr;
   a.n = n; a.q = q; a.r = r; a.iters = iters; a.tol = tol;
   a.ctl = s.ctl;
-  HIPCHK(launch_subspace(a, s.KSz, st));
+  HIPCHK(launch_subspace(a, room ? s.KSz : s.KS, st));
   if (iters_out) HIPCHK(hipMemcpyAsync(iters_out, &s.ctl->power_it, sizeof(int), hipMemcpyDeviceToDevice, st));
   return ALTGDMIN_OK;
 }

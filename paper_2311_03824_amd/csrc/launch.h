@@ -12,7 +12,7 @@ struct UpdArgs {
   float* gpart;            // n x r: grad; with KS > 1 the KS x n x r column splits, split 0 ends as grad
   float* U;                // n x r, in/out
   float* Uprev;            // n x r: receives the U the step started from
-  double* part;            // upd_part_doubles: Gram parts of the 64-row blocks
+  double* part;            // upd_part_doubles: Gram parts of the 64-row blocks; null: none (grad given, ctl null)
   int* upd;                // what k_uapply is to do (set by k_urows)
   Ctl* ctl;                // null: the entry point, with eta in eta_io (<= 0 on entry: computed)
   double* eta_io;
@@ -35,7 +35,7 @@ struct SubArgs {
   float* V;                // n x r scratch (the other iterate; may be start)
   float* T;                // q x r scratch
   float* gpart;            // KS x n x r scratch
-  double* part;            // sub_part_doubles
+  double* part;            // sub_part_doubles; null: every workgroup sums over all rows itself
   int n, q, r, KS, iters;  // KS: set by launch_subspace; iters = 0: the orthonormal block only
   double tol;
   Ctl* ctl;                // power_sd, power_it, conv, err; bar, roll and members (zero at launch)

@@ -67,8 +67,34 @@ __device__ __forceinline__ void sum_parts(const SubArgs& a, int off, int cnt, Su
   __syncthreads();
 }
 
+// dst (LDS) = X^T Y over all n rows, as rows_gram64 lays it out; for launches without parts.
+__device__ __forceinline__ void gram_all(const float* X, const float* Y, int n, int r, bool sym, SubShared& S, double* dst) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id(), E = sym ? r * (r + 1) / 2 : r * r;
+  const long long nr = (long long)n * r;
+  for (int j0 = 0; j0 < n; j0 += 64) {
+    __syncthreads();
+    for (int i = tid; i < 64 * r; i += kSubThreads) {
+      const long long o = (long long)j0 * r + i;
+      S.rows.X[i] = o < nr ? (double)X[o] : 0.0;
+      S.rows.Y[i] = o < nr ? (double)Y[o] : 0.0;
+    }
+    __syncthreads();
+    for (int e = wave; e < E; e += kSubWaves) {
+      int p = 0, c = 0;
+      if (sym) tri_entry(e, r, p, c);
+      else { p = e / r; c = e - p * r; }
+      const double s = wave_sum_dpp(S.rows.X[lane * r + p] * S.rows.Y[lane * r + c]);
+      if (lane == 0) dst[e] = j0 == 0 ? s : dst[e] + s;
+    }
+  }
+  __syncthreads();
+}
+
 }  // namespace
 
+// PARTS: Gram parts of the row units in a.part, each computed once; without (a scratch that has no room for
+// them), every workgroup forms what it needs over all rows.
+template <bool PARTS>
 __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_subspace(SubArgs a) {
   __shared__ SubShared S;
   __shared__ double tri[kRMax * (kRMax + 1) / 2];
@@ -106,11 +132,14 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
         S.rows.X[i] = (double)x;
       }
       __syncthreads();
-      rows_gram64<kSubWaves>(S.rows.X, S.rows.X, r, true, a.part + (long long)ru * ps);
+      if constexpr (PARTS) rows_gram64<kSubWaves>(S.rows.X, S.rows.X, r, true, a.part + (long long)ru * ps);
     }
     meet();
     for (int pass = 0; pass < 2; ++pass) {
-      sum_parts(a, pass == 0 ? 0 : E + rr, E, S, tri, units);
+      const float* src = pass == 0 ? z : dst;
+      if constexpr (PARTS) sum_parts(a, pass == 0 ? 0 : E + rr, E, S, tri, units);
+      else gram_all(src, src, n, r, true, S, tri);
+      if (!PARTS) meet();   // dst may be z: every workgroup has read it
       if (wave == 0) {
         for (int e = lane; e < rr; e += 64) S.M[e] = tri[tri_index(e / r, e % r, r)];
         double lo, hi;
@@ -121,7 +150,6 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
       const int mode = S.flag;
       if (mode == 0) return false;
       const bool again = pass == 0 && mode == 2;   // ill-conditioned: once more on the rounded rows
-      const float* src = pass == 0 ? z : dst;
       for (int ru = me; ru < units; ru += nblk) {
         const int j = ru * 64 + tid;
         const long long o = (long long)j * r;
@@ -143,10 +171,12 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
           for (int i = tid; i < 64 * r; i += kSubThreads)
             S.rows.Y[i] = (long long)ru * 64 * r + i < nr ? (double)old[(long long)ru * 64 * r + i] : 0.0;
         __syncthreads();
-        double* pt = a.part + (long long)ru * ps;
-        if (again) rows_gram64<kSubWaves>(S.rows.X, S.rows.X, r, true, pt + E + rr);
-        else if (old) rows_gram64<kSubWaves>(S.rows.Y, S.rows.X, r, false, pt + E);
-        __syncthreads();
+        if constexpr (PARTS) {
+          double* pt = a.part + (long long)ru * ps;
+          if (again) rows_gram64<kSubWaves>(S.rows.X, S.rows.X, r, true, pt + E + rr);
+          else if (old) rows_gram64<kSubWaves>(S.rows.Y, S.rows.X, r, false, pt + E);
+          __syncthreads();
+        }
       }
       meet();
       if (!again) break;
@@ -157,7 +187,7 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
   // the change of the last step, from the units' parts in order, and the stop rule
   double prev = 0.0;
   auto decide = [&]() -> bool {
-    sum_parts(a, ps - 1, 1, S, S.val, units);
+    if constexpr (PARTS) sum_parts(a, ps - 1, 1, S, S.val, units);
     const double sd = sqrt(S.val[0]);
     // converged at tol, or once the change has stopped shrinking below 1e-3 (by less
     // than 1 % in a step): the FP32 iterate's rounding floor.  A change that still
@@ -254,8 +284,10 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
     if (!ok) break;
     // the change ||U_new - U_old W||_F of this workgroup's rows, W = U_old^T U_new,
     // summed directly from the residual entries; decided after the next meeting
-    sum_parts(a, E, rr, S, S.M, units);
-    for (int ru = me; ru < units; ru += nblk) {
+    if constexpr (PARTS) sum_parts(a, E, rr, S, S.M, units);
+    else gram_all(cur, nxt, n, r, false, S, S.M);
+    double all = 0.0;   // without parts: the units of all workgroups, in order
+    for (int ru = PARTS ? me : 0; ru < units; ru += PARTS ? nblk : 1) {
       if (wave == 0) {
         const int j = ru * 64 + lane;
         const long long o = (long long)j * r;
@@ -278,9 +310,14 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
             }
         }
         acc = wave_sum_dpp(acc);
-        if (lane == 0) a.part[(long long)ru * ps + ps - 1] = acc;
+        if constexpr (PARTS) {
+          if (lane == 0) a.part[(long long)ru * ps + ps - 1] = acc;
+        } else {
+          all += acc;
+        }
       }
     }
+    if (!PARTS && tid == 0) S.val[0] = all;
     __syncthreads();
     pending = true;
     float* x = cur;
@@ -337,7 +374,7 @@ hipError_t launch_subspace(const SubArgs& a_in, int max_splits, hipStream_t st) 
   a.grace = roll_grace();
   a.KS = std::min(sub_splits(a.n, a.q), max_splits);
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  hipLaunchKernelGGL(k_subspace, dim3(sub_blocks(a.n, a.q)), dim3(kSubThreads), 0, st, a);
+  hipLaunchKernelGGL(a.part ? k_subspace<true> : k_subspace<false>, dim3(sub_blocks(a.n, a.q)), dim3(kSubThreads), 0, st, a);
   return hipGetLastError();
 }
 

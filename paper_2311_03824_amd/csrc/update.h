@@ -80,6 +80,10 @@ __device__ __forceinline__ void urows_body(const UpdArgs& a, int jb, URowsShared
     urows_grad_r<kGradWaves>(a.H, a.B, n, r, jb, 0, a.q, S.red, [&](int, float v) { g = v; });
     __syncthreads();   // S is free
   }
+  if (!a.part) {   // no room for the parts (the entry point, grad given): k_uapply forms the Grams from the rows
+    if (tid < 64 * r && base + tid < nr) a.Uprev[base + tid] = a.U[base + tid];
+    return;
+  }
   if (tid < 64 * r) {
     double x = 0.0, y = 0.0;
     const long long i = base + tid;
@@ -138,8 +142,44 @@ struct UApplyShared {
   int mode;                                 // 0: the Gram is not positive definite, 1 or 2 passes
 };
 
+// S.W = the upper triangle of X^T X over all n rows of X, row i as row(i, y) puts it into y, rounded to
+// FP32 (rows at or beyond n count as zero, whatever y holds): 256 rows at a time through LDS, by
+// FP64 matrix products of four rows each.  Lane l holds column l % 16 of row l / 16 for both operands, and
+// column l % 16 of rows l / 16 + 4 v of the result.
+template <class Row>
+__device__ __forceinline__ void uapply_gram(int n, int r, UApplyShared& S, Row row) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+  for (int i0 = 0; i0 < n; i0 += kUApplyRows) {
+    double y[kRMax];
+    row(i0 + tid, y);
+#pragma unroll
+    for (int c = 0; c < kRMax; ++c) S.rows[tid][c] = c < r && i0 + tid < n ? (float)y[c] : 0.f;
+    __syncthreads();
+    float v[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) v[s] = S.rows[64 * wave + 4 * s + (lane >> 4)][lane & 15];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[s], (double)v[s], acc, 0, 0, 0);
+    __syncthreads();
+  }
+  double* sum = reinterpret_cast<double*>(&S.rows[0][0]);   // 4 x 256 of the waves
+#pragma unroll
+  for (int v = 0; v < 4; ++v) sum[wave * 256 + ((lane >> 4) + 4 * v) * 16 + (lane & 15)] = acc[v];
+  __syncthreads();
+  if (tid < r * (r + 1) / 2) {
+    int ra, rb;
+    tri_entry(tid, r, ra, rb);
+    const int e = ra * 16 + rb;
+    S.W[tid] = (sum[e] + sum[256 + e]) + (sum[512 + e] + sum[768 + e]);
+  }
+  __syncthreads();
+}
+
 // Workgroup jb < kUApplyRows-row blocks of n updates its rows; the one after them does the
 // bookkeeping.
+template <bool PARTS>
 __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShared& S) {
   const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
   const int n = a.n, r = a.r, rr = r * r, E = r * (r + 1) / 2, PE = 2 * E + rr, nb = (n + 63) / 64;
@@ -154,45 +194,66 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
     ru[c] = c < r && j < n ? a.Uprev[o + c] : 0.f;
     rg[c] = c < r && j < n ? a.gpart[o + c] : 0.f;
   }
-  // the Gram parts: entry e over a contiguous range of blocks per group of threads,
-  // then the groups in order
   const bool first = upd == UPD_FIRST;
-  const int used = first ? PE : E;
-  const int grp = sum_groups(kUApplyRows, used, nb);
-  for (int e = tid; e < used * grp; e += kUApplyRows) {
-    const int g = e / used, en = e - g * used;
-    const int b0 = nb * g / grp, b1 = nb * (g + 1) / grp;
-    S.sum[e] = sum_strided(a.part + (long long)b0 * PE + en, PE, b1 - b0);
-  }
-  __syncthreads();
-  for (int e = tid; e < used; e += kUApplyRows) {
-    double s = S.sum[e];
-    for (int g = 1; g < grp; ++g) s += S.sum[g * used + e];
-    S.W[e] = s;
-  }
-  __syncthreads();
   double* M = S.A;
-  if (wave == 0) {
+  if constexpr (PARTS) {
+    // the Gram parts: entry e over a contiguous range of blocks per group of threads,
+    // then the groups in order
+    const int used = first ? PE : E;
+    const int grp = sum_groups(kUApplyRows, used, nb);
+    for (int e = tid; e < used * grp; e += kUApplyRows) {
+      const int g = e / used, en = e - g * used;
+      const int b0 = nb * g / grp, b1 = nb * (g + 1) / grp;
+      S.sum[e] = sum_strided(a.part + (long long)b0 * PE + en, PE, b1 - b0);
+    }
+    __syncthreads();
+    for (int e = tid; e < used; e += kUApplyRows) {
+      double s = S.sum[e];
+      for (int g = 1; g < grp; ++g) s += S.sum[g * used + e];
+      S.W[e] = s;
+    }
+    __syncthreads();
+  } else if (first) {   // G^T G for eta
+    uapply_gram(n, r, S, [&](int i, double (&y)[kRMax]) {
+#pragma unroll
+      for (int c = 0; c < kRMax; ++c) y[c] = c < r && i < n ? (double)a.gpart[(long long)i * r + c] : 0.0;
+    });
+  }
+  // eta, and with parts the Gram of X = U - eta G: U^T U - eta (U^T G + G^T U) + eta^2 G^T G at t = 1
+  auto set_eta = [&]() {
     double eta = first ? 0.0 : (a.ctl ? a.ctl->eta : *a.eta_io);
     if (first) {
-      for (int e = lane; e < rr; e += 64) M[e] = S.W[E + tri_index(e / r, e % r, r)];
+      for (int e = lane; e < rr; e += 64) M[e] = S.W[(PARTS ? E : 0) + tri_index(e / r, e % r, r)];
       const double lam = wave_lambda_max(M, S.A + kRMax * kRMax, r);
       eta = lam > 0.0 ? a.eta_c / sqrt(lam) : 0.0;
       wave_lds_fence();
-      // X^T X = U^T U - eta (U^T G + G^T U) + eta^2 G^T G
+    }
+    if (lane == 0) S.eta = eta;
+    return eta;
+  };
+  auto row = [&](int i, double eta, double (&y)[kRMax]) {   // row i of X
+#pragma unroll
+    for (int c = 0; c < kRMax; ++c)
+      y[c] = c < r && i < n ? fma(-eta, (double)a.gpart[(long long)i * r + c], (double)a.Uprev[(long long)i * r + c]) : 0.0;
+  };
+  if constexpr (!PARTS) {   // the Gram of the rounded X: always two passes
+    if (wave == 0) set_eta();
+    __syncthreads();
+    uapply_gram(n, r, S, [&](int i, double (&y)[kRMax]) { row(i, S.eta, y); });
+  }
+  if (wave == 0) {
+    if (PARTS) {
+      const double eta = set_eta();
       for (int e = lane; e < rr; e += 64) {
         const int i = e / r, jj = e % r, t = tri_index(i, jj, r);
-        M[e] = S.W[t] - eta * (S.W[2 * E + i * r + jj] + S.W[2 * E + jj * r + i]) + eta * eta * S.W[E + t];
+        M[e] = !first ? S.W[t] : S.W[t] - eta * (S.W[2 * E + i * r + jj] + S.W[2 * E + jj * r + i]) + eta * eta * S.W[E + t];
       }
     } else {
       for (int e = lane; e < rr; e += 64) M[e] = S.W[tri_index(e / r, e % r, r)];
     }
     double lo, hi;
     const bool pd = wave_cholesky_span(M, S.rdiag, r, lo, hi);
-    if (lane == 0) {
-      S.eta = eta;
-      S.mode = !pd ? 0 : (lo >= kPivotSpan * hi ? 1 : 2);
-    }
+    if (lane == 0) S.mode = !pd ? 0 : (PARTS && lo >= kPivotSpan * hi ? 1 : 2);
   }
   __syncthreads();
   const double eta = S.eta;
@@ -206,43 +267,15 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
     solve_row(x, M, S.rdiag, r);
   }
   if (S.mode == 2 && rows) {   // an ill-conditioned X: once more on the rounded rows, each solved once
-    // their Gram by FP64 matrix products, four rows each: lane l holds column l % 16 of row l / 16 for both
-    // operands, and column l % 16 of rows l / 16 + 4 v of the result
-    typedef double f64x4 __attribute__((ext_vector_type(4)));
-    f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-    for (int i0 = 0; i0 < n; i0 += kUApplyRows) {
-      const int i = i0 + tid;
-      double y[kRMax];
+    uapply_gram(n, r, S, [&](int i, double (&y)[kRMax]) {
       if (i != j) {
-#pragma unroll
-        for (int c = 0; c < kRMax; ++c)
-          y[c] = c < r && i < n ? fma(-eta, (double)a.gpart[(long long)i * r + c], (double)a.Uprev[(long long)i * r + c]) : 0.0;
+        row(i, eta, y);
         solve_row(y, M, S.rdiag, r);
       } else {   // this workgroup's rows are in x
 #pragma unroll
         for (int c = 0; c < kRMax; ++c) y[c] = x[c];
       }
-#pragma unroll
-      for (int c = 0; c < kRMax; ++c) S.rows[tid][c] = c < r && i < n ? (float)y[c] : 0.f;
-      __syncthreads();
-      float v[16];
-#pragma unroll
-      for (int s = 0; s < 16; ++s) v[s] = S.rows[64 * wave + 4 * s + (lane >> 4)][lane & 15];
-#pragma unroll
-      for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)v[s], (double)v[s], acc, 0, 0, 0);
-      __syncthreads();
-    }
-    double* sum = reinterpret_cast<double*>(&S.rows[0][0]);   // 4 x 256 of the waves
-#pragma unroll
-    for (int v = 0; v < 4; ++v) sum[wave * 256 + ((lane >> 4) + 4 * v) * 16 + (lane & 15)] = acc[v];
-    __syncthreads();
-    if (tid < E) {
-      int ra, rb;
-      tri_entry(tid, r, ra, rb);
-      const int e = ra * 16 + rb;
-      S.W[tid] = (sum[e] + sum[256 + e]) + (sum[512 + e] + sum[768 + e]);
-    }
-    __syncthreads();
+    });
     if (wave == 0) {
       for (int e = lane; e < rr; e += 64) M[e] = S.W[tri_index(e / r, e % r, r)];
       double lo, hi;
@@ -307,16 +340,17 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
   }
 }
 
+template <bool PARTS>
 __global__ __launch_bounds__(kUApplyRows) void k_uapply(UpdArgs a) {
   __shared__ UApplyShared S;
-  uapply_body(a, blockIdx.x, S);
+  uapply_body<PARTS>(a, blockIdx.x, S);
 }
 
 __global__ __launch_bounds__(kUApplyRows) void k_uapply_grp(const UpdArgs* tab, const int2* map) {
   __shared__ UApplyShared S;
   const int2 mp = map[blockIdx.x];
   const UpdArgs a = tab[mp.x];
-  uapply_body(a, mp.y, S);
+  uapply_body<true>(a, mp.y, S);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -351,7 +385,7 @@ hipError_t launch_urows(const UpdArgs& a, hipStream_t st) {
 
 hipError_t launch_uapply(const UpdArgs& a, hipStream_t st) {
   (void)hipGetLastError();   // clear a stale error of an earlier, unrelated call
-  hipLaunchKernelGGL(k_uapply, dim3(uapply_blocks(a.n)), dim3(kUApplyRows), 0, st, a);
+  hipLaunchKernelGGL(a.part ? k_uapply<true> : k_uapply<false>, dim3(uapply_blocks(a.n)), dim3(kUApplyRows), 0, st, a);
   return hipGetLastError();
 }
 
