@@ -711,8 +711,9 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
   // mixed form, and at q = 125 from 0.173 to 0.105.  Above rho = n / 4 the support
   // columns are no longer a small part of a pass, and their list needs 2 rho words
   // of g's LDS.
-  float bnd = 0.f;
+  float bnd = 0.f, mu_last = 0.f;
   if (a.bound && a.project && 4 * rho <= n) {
+    if (a.step) mu_last = a.step[k];
     if (a.splits <= 1) {
       bnd = a.bound[k];
     } else {
@@ -721,7 +722,6 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
     }
   }
   const bool screen = bnd > 0.f && isfinite(bnd);
-  float mu_last = screen && a.step ? a.step[k] : 0.f;
   int* list = reinterpret_cast<int*>(gl);   // rho entries, then the rho values of g on T (2 rho <= n)
   float* gT = gl + rho;
   bool have_list = false;
@@ -757,7 +757,8 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
         for (int o = 32; o > 0; o >>= 1) smin = min(smin, (unsigned)__shfl_xor((int)smin, o));
         have_smin = true;
       }
-      on_T = (mu_last > 0.f ? 0.25 * (double)mu_last * (double)bnd * un : un / (double)bnd) < (double)__uint_as_float(smin);
+      const float uf = (float)un, sf = __uint_as_float(smin);
+      on_T = mu_last > 0.f ? 0.25f * mu_last * bnd * uf < sf : uf < bnd * sf;
     }
 
     // g = A_k^T u; w = A_k g_T on the current support; mu.  A step whose test holds

@@ -219,37 +219,37 @@ __device__ __forceinline__ void uapply_body(const UpdArgs& a, int jb, UApplyShar
       for (int c = 0; c < kRMax; ++c) y[c] = c < r && i < n ? (double)a.gpart[(long long)i * r + c] : 0.0;
     });
   }
-  // eta, and with parts the Gram of X = U - eta G: U^T U - eta (U^T G + G^T U) + eta^2 G^T G at t = 1
-  auto set_eta = [&]() {
-    double eta = first ? 0.0 : (a.ctl ? a.ctl->eta : *a.eta_io);
-    if (first) {
-      for (int e = lane; e < rr; e += 64) M[e] = S.W[(PARTS ? E : 0) + tri_index(e / r, e % r, r)];
-      const double lam = wave_lambda_max(M, S.A + kRMax * kRMax, r);
-      eta = lam > 0.0 ? a.eta_c / sqrt(lam) : 0.0;
-      wave_lds_fence();
-    }
-    if (lane == 0) S.eta = eta;
-    return eta;
-  };
   auto row = [&](int i, double eta, double (&y)[kRMax]) {   // row i of X
 #pragma unroll
     for (int c = 0; c < kRMax; ++c)
       y[c] = c < r && i < n ? fma(-eta, (double)a.gpart[(long long)i * r + c], (double)a.Uprev[(long long)i * r + c]) : 0.0;
   };
+  auto step_size = [&](int off) -> double {   // at t = 1, from G^T G at S.W + off, by wave 0
+    for (int e = lane; e < rr; e += 64) M[e] = S.W[off + tri_index(e / r, e % r, r)];
+    const double lam = wave_lambda_max(M, S.A + kRMax * kRMax, r);
+    wave_lds_fence();
+    return lam > 0.0 ? a.eta_c / sqrt(lam) : 0.0;
+  };
   if constexpr (!PARTS) {   // the Gram of the rounded X: always two passes
-    if (wave == 0) set_eta();
+    if (wave == 0) {
+      const double eta = first ? step_size(0) : (a.ctl ? a.ctl->eta : *a.eta_io);
+      if (lane == 0) S.eta = eta;
+    }
     __syncthreads();
     uapply_gram(n, r, S, [&](int i, double (&y)[kRMax]) { row(i, S.eta, y); });
   }
   if (wave == 0) {
-    if (PARTS) {
-      const double eta = set_eta();
+    if (PARTS && first) {
+      const double eta = step_size(E);
+      // X^T X = U^T U - eta (U^T G + G^T U) + eta^2 G^T G
       for (int e = lane; e < rr; e += 64) {
         const int i = e / r, jj = e % r, t = tri_index(i, jj, r);
-        M[e] = !first ? S.W[t] : S.W[t] - eta * (S.W[2 * E + i * r + jj] + S.W[2 * E + jj * r + i]) + eta * eta * S.W[E + t];
+        M[e] = S.W[t] - eta * (S.W[2 * E + i * r + jj] + S.W[2 * E + jj * r + i]) + eta * eta * S.W[E + t];
       }
+      if (lane == 0) S.eta = eta;
     } else {
       for (int e = lane; e < rr; e += 64) M[e] = S.W[tri_index(e / r, e % r, r)];
+      if (PARTS && lane == 0) S.eta = a.ctl ? a.ctl->eta : *a.eta_io;
     }
     double lo, hi;
     const bool pd = wave_cholesky_span(M, S.rdiag, r, lo, hi);
