@@ -181,7 +181,10 @@ int altgdmin_init(const altgdmin_problem* prob, const altgdmin_params* par, void
 
 /* Enqueues `iters` GDmin iterations of Alg. 1 (z_k/M_k from U, warm-started IHT
  * for s_k, LS for b_k (eq. (bk_LS)), grad_U f, eta at t = 1, U+ = QR(U - eta grad)).
- * The iteration is captured once as a HIP graph and replayed.  Asynchronous. */
+ * The iteration is captured once as a HIP graph and replayed.  Asynchronous.  Real
+ * forms: an IHT step that provably keeps its support reads the support columns of
+ * A_k alone, with the bits of a full pass (ALTGDMIN_FULL_STEPS in the environment at
+ * altgdmin_init: every step takes the full pass, for tests). */
 int altgdmin_step(altgdmin_handle* h, int32_t iters, void* stream);
 
 /* Copies the consistent state (U that B and S were fitted with, Bt, S) into

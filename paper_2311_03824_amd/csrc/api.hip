@@ -77,8 +77,10 @@ int grad_splits(int q) { return q >= 512 ? 4 : (q >= 64 ? 2 : 1); }
 
 // column splits of a GDmin iteration's gradient: none up to 256 columns (k_urows sums
 // all columns of its rows: the same 171 us an iteration at q = 125 with 1, 4 or 8
-// splits); above, about a 64-row workgroup per CU with at least 64 columns each (an
-// iteration at n = q = 1000 takes 626 us with 15 splits, 631 with 4, 632 with none)
+// splits); above, about a 64-row workgroup per CU with at least 64 columns each.  The
+// gradient with its Gram parts, with splits against none: n = 100, q = 20,000, r = 4 51
+// against 206 us, n = 1000, q = 3000, r = 10 20 against 51, n = q = 1000 16 against 24,
+// n = 300, q = 600 14 against 19, n = 4000, q = 400 the same 14.
 int upd_splits(int n, int q) {
   return q <= 256 ? 1 : std::max(2, std::min(std::min(16, 256 / ((n + 63) / 64)), q / 64));
 }
@@ -215,6 +217,7 @@ struct altgdmin_handle {
   int col_waves = kWaves;  // waves of the column workgroup (a property of the problem, see choose_col_waves)
   int au_waves = kWaves;   // waves of the A_k U workgroup and its row splits, taken once, at init (Ginv and
   int au_splits = 1;       // colbound hold a value per split)
+  bool short_steps = true; // hand the column kernel the norm bound (ALTGDMIN_FULL_STEPS=1 at init: no, for tests)
   int col_unroll = 0;      // autotuned JU of the column kernel (0: the default instantiation)
   int au_depth = 0;        // autotuned AUD of the A_k U kernel (0: the default instantiation)
   int colfmt = 0;          // format of the column kernel: fmt, or the mixed BF16 form
@@ -435,7 +438,7 @@ ColArgs col_args(const altgdmin_handle* h) {
 ColArgs gd_col_args(const altgdmin_handle* h) {
   ColArgs a = col_args(h);
   a.tau = h->par.tau; a.project = 1; a.has_support = 1; a.tail = TAIL_LSGRAD;
-  a.bound = h->colbound;
+  a.bound = h->short_steps ? h->colbound : nullptr;
   a.splits = h->au_splits;
   return a;
 }
@@ -781,6 +784,7 @@ int altgdmin_init(const altgdmin_problem* prob, const altgdmin_params* par, void
   h->auto_rank = prob->r == 0;
   if (h->fmt != FMT_PFOURIER) {
     h->col_waves = choose_col_waves(h->prob, h->colfmt == FMT_BF16MIX);
+    h->short_steps = std::getenv("ALTGDMIN_FULL_STEPS") == nullptr;
     h->au_waves = au_waves(h->prob);
     h->au_splits = au_splits(h->prob, h->au_waves);
     // a GDmin iteration's column workgroup (with P_k) may need more LDS than the

@@ -889,9 +889,11 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int k, unsigned char*
 }
 
 // Minimum waves per SIMD asked of the register allocator (4 waves: at most 128
-// VGPRs): as many as the column pass fits without spilling.  The loads in
-// flight grow with NC and JU; the two BF16 planes and the Philox rounds need
-// more registers than one FP32 or hi plane.
+// VGPRs): as many as the streaming loops fit.  The loads in flight grow with NC and
+// JU; the two BF16 planes and the Philox rounds need more registers than one FP32 or
+// hi plane.  Around the loops values go to scratch where the cap is tight: at two row
+// chunks 29 with 4 waves (FP32, hi plane, mixed form) and 39 to 74 with 8, two BF16 planes
+// at most 43, Philox 17 with 4 waves and 131 with 16.
 constexpr int col_min_waves(int fmt, int nc, int ju) {
   if (ju == 8) return nc == 1 ? 2 : 1;
   if (fmt == FMT_PHILOX) return nc <= 2 ? 2 : 1;
