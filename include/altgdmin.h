@@ -212,8 +212,8 @@ int altgdmin_solve(const altgdmin_problem* prob, const altgdmin_params* par, voi
                    float* S_val, altgdmin_report* rep);
 
 /* Measurement hook: runs `iters` GDmin iterations with eager launches and a
- * HIP event pair around each of the four kernels of an iteration (A_k U,
- * column kernel, gradient reduction, U update), on `stream`.  ms_out (host,
+ * HIP event pair around each of the four spans of an iteration (A_k U,
+ * column kernel, gradient with its Gram parts, U update), on `stream`.  ms_out (host,
  * 4 doubles) receives the average duration of each kernel in milliseconds.
  * Advances the solve like altgdmin_step.  Synchronises. */
 int altgdmin_profile_iteration(altgdmin_handle* h, int32_t iters, void* stream, double* ms_out);
@@ -253,11 +253,11 @@ int altgdmin_group_bytes(altgdmin_handle* const* hs, int32_t count, size_t* byte
  * column work of all problems batched into shared launches (per A format and
  * kernel instantiation -- ceil(m / 256) for the column kernel, r rounded up to
  * even for A_k U -- one A_k U launch and one column-kernel launch over the
- * columns of those problems; then one gradient-reduction launch and one
- * U-update launch with a workgroup per problem).  Each problem keeps its own
+ * columns of those problems; then two or three launches for the gradient and the
+ * U update of all problems, with a workgroup per row block).  Each problem keeps its own
  * U/B/S state in its workspace and follows exactly the arithmetic of
  * altgdmin_step (problems are also bucketed by their column-workgroup width, 8
- * waves for q <= 320 and 4 above: the width sets the order of the kernels'
+ * waves for q <= 512, 320 in the mixed form, and 4 above: the width sets the order of the kernels'
  * cross-wave sums).  A problem whose params have tol_resid > 0 is frozen from the
  * iteration after its residual first reaches tol_resid: its kernels skip it, so
  * its state, report.iterations and report.resid stay those of the first
@@ -367,8 +367,11 @@ int altgdmin_op_lsgrad(const altgdmin_problem* prob, const float* P, const doubl
 int altgdmin_op_backproject(const altgdmin_problem* prob, const int32_t* S_idx, const float* S_val,
                             float* L0t, void* stream);
 
-/* Device scratch (bytes) that altgdmin_op_grad, altgdmin_op_qr_step and
- * altgdmin_op_subspace need for sizes (n, q, r).  Host call. */
+/* Device scratch (bytes) for altgdmin_op_grad, altgdmin_op_qr_step and
+ * altgdmin_op_subspace at sizes (n, q, r).  The calls also run, more slowly, with
+ * the part of it that holds a control block of 256 bytes, S n r floats, n r floats
+ * and q r floats, each rounded up to 256 bytes but the last (S = 4 for q >= 512, 2 for
+ * q >= 64, 1 below).  Host call. */
 int altgdmin_op_scratch_bytes(int32_t n, int32_t q, int32_t r, size_t* bytes);
 
 /* grad_U f = sum_k h_k b_k^T (n x r row-major), summed in a fixed order (Sec. 2.1). */
@@ -376,8 +379,10 @@ int altgdmin_op_grad(const float* H, const float* Bt, int32_t n, int32_t q, int3
                      float* grad, void* scratch, size_t scratch_bytes, void* stream);
 
 /* Projected GD step: U_out = Q of the thin QR (positive diagonal R) of
- * U - eta*grad, by CholeskyQR2 with FP64 Gram and Cholesky.  If *eta_io <= 0
- * on entry (device double) it is first set to eta_c / ||grad||_2. */
+ * U - eta*grad, by CholeskyQR with FP64 Gram and Cholesky: one pass on the
+ * unrounded rows, two when the Gram's pivots span more than 1e6 (or the scratch is
+ * smaller than altgdmin_op_scratch_bytes).  If *eta_io <= 0 on entry (device double)
+ * it is first set to eta_c / ||grad||_2. */
 int altgdmin_op_qr_step(const float* U, const float* grad, int32_t n, int32_t r, double eta_c,
                         double* eta_io, float* U_out, void* scratch, size_t scratch_bytes,
                         void* stream);

@@ -327,6 +327,8 @@ def altgdmin_step_many(hs, iters: int, group_ws, stream=None) -> None:
                                    group_ws.numel() * group_ws.element_size(), stream_ptr(stream)))
 
 
+# The four spans of an iteration that altgdmin_profile_iteration times: A_k U, the column kernel, the
+# gradient ("k_grad": k_ugrad and k_urows; k_frows in the Fourier form) and the U update ("k_qr": k_uapply; k_fapply).
 KERNELS = ("k_au", "k_col", "k_grad", "k_qr")
 
 

@@ -40,10 +40,25 @@ def au_kernel_bytes(n, q, m, r, a_bytes=4.0):
 
 
 def iteration_bytes(n, q, m, r, rho, tau=3, mixed=False):
-    """A_k U plus the column kernel of one GDmin iteration.  FP32 plane and BF16 hi + lo:
-    4 bytes per element everywhere; the mixed BF16 form: 2 in the column passes."""
+    """A_k U plus the column kernel of one GDmin iteration whose IHT steps all take full passes.
+    FP32 plane and BF16 hi + lo: 4 bytes per element everywhere; the mixed BF16 form: 2 in the
+    column passes."""
     return (au_kernel_bytes(n, q, m, r, 4.0)
             + column_kernel_bytes(n, q, m, r, rho, tau, 2.0 if mixed else 4.0, 4.0))
+
+
+def settled_iteration_bytes(n, q, m, r, rho, tau=3, mixed=False):
+    """iteration_bytes of an iteration whose IHT steps all keep their support by the column norm
+    bound (settled_column_bytes): the least an iteration moves; one with full passes moves more."""
+    return (au_kernel_bytes(n, q, m, r, 4.0)
+            + settled_column_bytes(n, q, m, r, rho, tau, 2.0 if mixed else 4.0, 4.0))
+
+
+def settled_elements(n, q, m, rho, tau=3):
+    """Elements of A that the column kernel of a settled iteration generates in the Philox form (rows in
+    groups of four): the tail's pass, the tau + 1 support gathers and the tau support passes."""
+    m4 = 4 * ((m + 3) // 4)
+    return q * m4 * (n + (2 * tau + 1) * rho)
 
 
 def fourier_column_flops(n1, n2, q, m, r, transforms=8):

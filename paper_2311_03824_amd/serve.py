@@ -409,9 +409,10 @@ class GpuExecutor:
         return req.a_bytes() + 4 * req.q * req.m + 8 * req.q * req.n + self.workspace_bytes(req)
 
     def iteration_bytes(self, req) -> float:
-        """Algorithmic HBM bytes of one GDmin iteration of the request (its form's A reads)."""
-        return roofline.iteration_bytes(req.n, req.q, req.m, req.r, req.rho, 3,
-                                        mixed=req.a_format != "f32" and self.bf16_mixed)
+        """Algorithmic HBM bytes of one settled GDmin iteration of the request (its form's A reads): the
+        least that its iterations move."""
+        return roofline.settled_iteration_bytes(req.n, req.q, req.m, req.r, req.rho, 3,
+                                                mixed=req.a_format != "f32" and self.bf16_mixed)
 
     # -- lifecycle
     def start(self, req):
