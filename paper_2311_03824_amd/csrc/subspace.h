@@ -8,8 +8,9 @@
 // workgroup that orthonormalised), and the ones after the stop still cost their launches
 // (1.7 us each, at the host's 4.6 us): 1400 us for 6 steps.  Here sub_blocks() workgroups
 // stay and meet at a counter between the pieces (2.6 us for 32 workgroups, 3.3
-// for 64), and the loop ends when the rule fires: 59 us a step, 360 us in all; 20 us a
-// step at n = q = 100.
+// for 64), and the loop ends when the rule fires: 40 us for the start block and 56 us a
+// step there; 24 and 17 at n = q = 100, r = 2; 50 and 125 at n = 100, q = 50,000, r = 5;
+// 24 and 24 at n = 400, q = 700, r = 1, where three launches a step took 23.
 //
 // The workgroups need not all be resident (meet.h).  Rows are dealt to workgroups in units and
 // every sum runs in a fixed order, so results depend neither on timing nor on how many
