@@ -119,15 +119,21 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
         float x = 0.f;
         if (base + i < nr) {
           x = z[base + i];
-          int s = 1;
-          for (; s + 8 <= splits; s += 8) {   // in order, the loads eight at a time
-            float v[8];
+          if (splits <= 4) {
+            for (int s = 1; s < splits; ++s) x += z[s * nr + base + i];
+          } else {   // in FP64: U against FP64 at n = 100, q = 9000 0.64e-7, with FP32 sums 1.06e-7, with 4 splits 0.75e-7
+            double d = (double)x;
+            int s = 1;
+            for (; s + 8 <= splits; s += 8) {   // in order, the loads eight at a time
+              float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = z[(s + u) * nr + base + i];
+              for (int u = 0; u < 8; ++u) v[u] = z[(s + u) * nr + base + i];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) x += v[u];
+              for (int u = 0; u < 8; ++u) d += (double)v[u];
+            }
+            for (; s < splits; ++s) d += (double)z[s * nr + base + i];
+            x = (float)d;
           }
-          for (; s < splits; ++s) x += z[s * nr + base + i];
           if (splits > 1) z[base + i] = x;
         }
         S.rows.X[i] = (double)x;
