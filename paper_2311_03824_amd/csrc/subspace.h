@@ -226,12 +226,11 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
         const int k = kb + 16 * cg + i;
         const float* row = a.L0t + (long long)(k < q ? k : q - 1) * n;
         constexpr int SU = 4;   // 16-row groups in flight per wave
-        // eight sums of n / 32 terms per wave, added as a tree: one chain of n / 4 products rounds worse than
-        // the sums over lanes it replaced (U against FP64 at n = q = 1000: 1.3e-7 where those gave 0.93e-7 and these
-        // 0.96e-7; 12 us of 415)
-        f32x4 acc[2][4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[0][e] = acc[1][e] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        // the FP32 sums end with the loads in flight (16 products each) and are added in FP64: sums of n / 32
+        // products in FP32 round worse than the sums over lanes that they replaced (U against FP64 at
+        // n = q = 1000, mean of 40 draws: 1.13e-7, over lanes 0.96e-7, these 0.91e-7; ten steps 597 and 600 us,
+        // at n = 20,000, q = 50: 1393 and 1462).  All products in FP64: 671 and 2950 us.
+        double tot[4] = {0.0, 0.0, 0.0, 0.0};
         for (int s0 = wave * 16; s0 < n; s0 += kSubWaves * 16 * SU) {
           float x[SU][4], u[SU][4];
 #pragma unroll
@@ -247,26 +246,30 @@ __global__ __launch_bounds__(kSubThreads) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
             for (int e = 0; e < 4; ++e) u[g][e] = i < r && j + e < n ? cur[(long long)(j + e) * r + i] : 0.f;
           }
+          f32x4 acc[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int g = 0; g < SU; ++g)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              acc[g & 1][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[g][e], u[g][e], acc[g & 1][e], 0, 0, 0);
+              acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[g][e], u[g][e], acc[e], 0, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            tot[e] += ((double)acc[0][e] + (double)acc[1][e]) + ((double)acc[2][e] + (double)acc[3][e]);
         }
-        const f32x4 sum = ((acc[0][0] + acc[1][0]) + (acc[0][1] + acc[1][1])) +
-                          ((acc[0][2] + acc[1][2]) + (acc[0][3] + acc[1][3]));
         // lane (i, p) holds column i of rows 4 p .. 4 p + 3 of the 16 x 16 result
 #pragma unroll
-        for (int e = 0; e < 4; ++e) S.red[wave][16 * cg + p4 + e][i] = sum[e];
+        for (int e = 0; e < 4; ++e) S.red[wave][16 * cg + p4 + e][i] = (float)tot[e];
       }
       __syncthreads();
       for (int t = tid; t < 16 * CG * r; t += kSubThreads) {
         const int kk = t / r, c = t - kk * r;
         if (kb + kk < q) {
-          float v = S.red[0][kk][c];
+          double v = S.red[0][kk][c];
 #pragma unroll
-          for (int w = 1; w < kSubWaves; ++w) v += S.red[w][kk][c];
-          a.T[(long long)(kb + kk) * r + c] = v;
+          for (int w = 1; w < kSubWaves; ++w) v += (double)S.red[w][kk][c];
+          a.T[(long long)(kb + kk) * r + c] = (float)v;
         }
       }
     }
